@@ -29,7 +29,7 @@ struct BSmem {
 // Streams the systems' rows to write grad_H / grad_y; returns this lane's
 // share of grad_N0.
 template <int UT, class Seg>
-__device__ __forceinline__ float round_backward(const BwdArgs &a, BSmem<UT> &sm, LocalSolve<UT> &r,
+__device__ __forceinline__ float round_backward(const BwdArgs &a, BSmem<UT> &sm, FactorSolve<UT> &r,
                                                 int nvalid, Seg seg, float2 gzc, float gsc) {
   const int lane = lane_id();
   const int sme = lane / UT, i = lane % UT;
@@ -209,8 +209,8 @@ __device__ __forceinline__ float pd_backward_task(const BwdArgs &a, int task, BS
     r1 = a.B;
   };
   gram_round<UT>(a, sm, nvalid, seg);
-  LocalSolve<UT> r;
-  local_solve<UT>(r, sm.r, sme, i, a.U);
+  FactorSolve<UT> r;
+  factor_local<UT>(r, sm.r, sme, i, a.U);
   const bool live = sme < nvalid && i < a.U;
   const size_t w = (size_t)task * NSYS + sme;
   float2 gzc = make_float2(0.f, 0.f);
@@ -253,8 +253,8 @@ __device__ __forceinline__ float fd_backward_task(const BwdArgs &a, int task, BS
     for (int base = 0; base < ntot; base += NSYS) {
       const int nvalid = min(NSYS, ntot - base);
       gram_round<UT>(a, sm, nvalid, make_seg(base));
-      LocalSolve<UT> r;
-      local_solve<UT>(r, sm.r, sme, i, U);
+      FactorSolve<UT> r;
+      factor_local<UT>(r, sm.r, sme, i, U);
       const int idx = base + sme;
       if (sme < nvalid && i < U) {
         const int wl = idx / C, c = idx - wl * C;
@@ -289,8 +289,8 @@ __device__ __forceinline__ float fd_backward_task(const BwdArgs &a, int task, BS
     const int nvalid = min(NSYS, ntot - base);
     auto seg = make_seg(base);
     gram_round<UT>(a, sm, nvalid, seg);
-    LocalSolve<UT> r;
-    local_solve<UT>(r, sm.r, sme, i, U);
+    FactorSolve<UT> r;
+    factor_local<UT>(r, sm.r, sme, i, U);
     const int idx = base + sme;
     const int wl = idx / C, c = idx - wl * C;
     const size_t w = (size_t)(w0 + wl);

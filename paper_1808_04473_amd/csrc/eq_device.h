@@ -1066,6 +1066,283 @@ __device__ __forceinline__ float abs_row_acc(float acc, float2 v) {
   return fmaf(fabsf(v.y), kRowScale, fmaf(fabsf(v.x), kRowScale, acc));
 }
 
+// ---------------------------------------------------------------- factor, inverse and solve in one elimination
+// Lane i of a group owns row i of A (entries k <= i, zero for k > i) in v[].
+// Step J of the right-looking Cholesky A = L L^H subtracts l_iJ conj(l_kJ)
+// from a_ik in the lanes i >= k; step J of the inverse X = L^{-1} subtracts
+// L_kJ X_Ju from X_ku in the lanes u <= J.  With the columns of X kept
+// conjugated both are
+//     v[k] -= s conj(l_kJ),   k > J,
+// with s = l_iJ in the lanes past J and conj(X_Ju) in the others, and lane J,
+// whose row of L is used up after step J, starts column J of X in the
+// registers of that row: one set of registers and one pass of FMACs do both.
+// The right-hand side rides along: acc_i -= s t_J is the forward
+// substitution t = L^{-1} m in the lanes past J and, restarted from zero in
+// lane J, -z_u = -sum_J conj(X_Ju) t_J in the others; d_u = sum_J |X_Ju|^2.
+//
+// Lanes J < i < k take no part in the update of v[k] (lane i must find its
+// v[k] zero when its column starts): EXEC leaves them out.  It is set by
+// scalar moves inside the assembly block, which do not take vector issue
+// slots, and is all ones again at its end.  Callers run in wave-uniform
+// control flow with all 64 lanes active.
+
+// Lanes of each UT-lane group with index >= k, over 32 lanes.
+template <int UT>
+constexpr uint32_t lanes_ge(int k) {
+  if (UT == 32) return k >= 32 ? 0u : ~0u << k;
+  const uint32_t p = k >= 16 ? 0u : (0xffffu << k) & 0xffffu;
+  return p | p << 16;
+}
+// A lane predicate from its 32-lane pattern (the same in both halves of the
+// wave).  The scalar moves are volatile: as plain constants the compiler
+// keeps every pattern of the elimination live, and spills them.
+__device__ __forceinline__ bool lanes(uint32_t pattern) {
+  uint32_t lo, hi;
+  asm volatile("s_mov_b32 %0, %2\n\ts_mov_b32 %1, %2" : "=s"(lo), "=s"(hi) : "n"(pattern));
+  return __builtin_amdgcn_inverse_ballot_w64((uint64_t)hi << 32 | lo);
+}
+
+// v[k] -= s conj(b_k) for N consecutive columns from K0 (b_k: lane K0 + n of
+// the group, through the DPP row of bx, by) in the lanes i <= J and i >= k.
+// NOP: a leading s_nop for the DPP reads, where a block label may precede.
+#define EQ_COL_EXEC(M) "s_mov_b32 exec_lo, " M "\n\ts_mov_b32 exec_hi, " M "\n\t"
+#define EQ_COL_FMAC(X, Y, BX, BY, SX, SY, K)                                                      \
+  "v_fmac_f32_dpp " X ", -" BX ", " SX " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n\t"       \
+  "v_fmac_f32_dpp " Y ", -" BX ", " SY " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n\t"       \
+  "v_fmac_f32_dpp " X ", -" BY ", " SY " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n\t"       \
+  "v_fmac_f32_dpp " Y ", " BY ", " SX " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n\t"
+#define EQ_COL_TAIL "s_mov_b64 exec, -1"
+template <int UT, int J, int K0, int N, bool NOP>
+__device__ __forceinline__ void elim_cols(float2 *v, float bx, float by, float2 s) {
+  constexpr uint32_t le = ~lanes_ge<UT>(J + 1);
+  constexpr int m0 = (int)(le | lanes_ge<UT>(K0)), m1 = (int)(le | lanes_ge<UT>(K0 + 1));
+  constexpr int m2 = (int)(le | lanes_ge<UT>(K0 + 2)), m3 = (int)(le | lanes_ge<UT>(K0 + 3));
+  constexpr int k0 = K0 % 16;
+  if constexpr (NOP) asm volatile("s_nop 4");
+  if constexpr (N == 4) {
+    asm volatile(EQ_COL_EXEC("%12") EQ_COL_FMAC("%0", "%1", "%8", "%9", "%10", "%11", "%16")
+                     EQ_COL_EXEC("%13") EQ_COL_FMAC("%2", "%3", "%8", "%9", "%10", "%11", "%17")
+                     EQ_COL_EXEC("%14") EQ_COL_FMAC("%4", "%5", "%8", "%9", "%10", "%11", "%18")
+                     EQ_COL_EXEC("%15") EQ_COL_FMAC("%6", "%7", "%8", "%9", "%10", "%11", "%19") EQ_COL_TAIL
+                 : "+&v"(v[0].x), "+&v"(v[0].y), "+&v"(v[1].x), "+&v"(v[1].y), "+&v"(v[2].x), "+&v"(v[2].y),
+                   "+&v"(v[3].x), "+&v"(v[3].y)
+                 : "v"(bx), "v"(by), "v"(s.x), "v"(s.y), "n"(m0), "n"(m1), "n"(m2), "n"(m3), "n"(k0), "n"(k0 + 1),
+                   "n"(k0 + 2), "n"(k0 + 3));
+  } else if constexpr (N == 3) {
+    asm volatile(EQ_COL_EXEC("%10") EQ_COL_FMAC("%0", "%1", "%6", "%7", "%8", "%9", "%13")
+                     EQ_COL_EXEC("%11") EQ_COL_FMAC("%2", "%3", "%6", "%7", "%8", "%9", "%14")
+                     EQ_COL_EXEC("%12") EQ_COL_FMAC("%4", "%5", "%6", "%7", "%8", "%9", "%15") EQ_COL_TAIL
+                 : "+&v"(v[0].x), "+&v"(v[0].y), "+&v"(v[1].x), "+&v"(v[1].y), "+&v"(v[2].x), "+&v"(v[2].y)
+                 : "v"(bx), "v"(by), "v"(s.x), "v"(s.y), "n"(m0), "n"(m1), "n"(m2), "n"(k0), "n"(k0 + 1),
+                   "n"(k0 + 2));
+  } else if constexpr (N == 2) {
+    asm volatile(EQ_COL_EXEC("%8") EQ_COL_FMAC("%0", "%1", "%4", "%5", "%6", "%7", "%10")
+                     EQ_COL_EXEC("%9") EQ_COL_FMAC("%2", "%3", "%4", "%5", "%6", "%7", "%11") EQ_COL_TAIL
+                 : "+&v"(v[0].x), "+&v"(v[0].y), "+&v"(v[1].x), "+&v"(v[1].y)
+                 : "v"(bx), "v"(by), "v"(s.x), "v"(s.y), "n"(m0), "n"(m1), "n"(k0), "n"(k0 + 1));
+  } else if constexpr (N == 1) {
+    asm volatile(EQ_COL_EXEC("%6") EQ_COL_FMAC("%0", "%1", "%2", "%3", "%4", "%5", "%7") EQ_COL_TAIL
+                 : "+&v"(v[0].x), "+&v"(v[0].y)
+                 : "v"(bx), "v"(by), "v"(s.x), "v"(s.y), "n"(m0), "n"(k0));
+  }
+}
+#undef EQ_COL_EXEC
+#undef EQ_COL_FMAC
+#undef EQ_COL_TAIL
+
+// What the elimination carries besides the matrix rows.  npos counts, per
+// group (one 64 / NSYS-bit field each, scalar arithmetic), the leading
+// pivots that were positive; okm masks the groups whose pivots all were.
+struct Elim {
+  float2 acc;  // t of the lanes ahead, -z of the lanes done
+  float d;     // [A^{-1}]_uu of the lanes done
+  uint64_t okm, npos;
+};
+
+// Step J.  ZERO: v[J] is left as conj(X_Ju) in lane u (zero in lanes past J
+// of the same 16 rows), for callers that use X.
+template <int UT, int J, bool ZERO>
+__device__ __forceinline__ void elim_step(float2 (&v)[16], Elim &e, int U) {
+  constexpr int j = J % 16, P = J - j;
+  const float ajj = gbcast<UT, J>(v[j].x);
+  e.okm &= __ballot(ajj > 0.f);
+  e.npos += e.okm & (UT == 16 ? 0x0001000100010001ull : 0x0000000100000001ull);
+  // hardware reciprocal square root (about 1 ulp): 1 / L_JJ
+  const float inv = __builtin_amdgcn_rsqf(ajj);
+  const bool me = lanes(lanes_ge<UT>(J) & ~lanes_ge<UT>(J + 1));
+  float2 s = make_float2(v[j].x * inv, v[j].y * inv);
+  if (me) s = make_float2(inv, 0.f);
+  const float2 t = make_float2(e.acc.x * inv, e.acc.y * inv);
+  float2 acc = e.acc;
+  float d = e.d;
+  if (me) {
+    acc = make_float2(0.f, 0.f);
+    d = 0.f;
+  }
+  e.d = fmaf(s.x, s.x, fmaf(s.y, s.y, d));
+  const BSrc bx = bsrc<UT>(s.x), by = bsrc<UT>(s.y), tx = bsrc<UT>(t.x), ty = bsrc<UT>(t.y);
+  // acc -= s t_J, the product rounded before it is subtracted (the running
+  // sum is rounded once a step: 5% less error in z than four FMACs on it).
+  // The s_nop also covers the columns that follow.
+  float px, py;
+  asm volatile("s_nop 4\n\t"
+               "v_mul_f32_dpp %0, %2, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+               "v_mul_f32_dpp %1, %2, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+               "v_fmac_f32_dpp %0, -%3, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+               "v_fmac_f32_dpp %1, %3, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf"
+               : "=&v"(px), "=&v"(py)
+               : "v"(bpick<J>(tx)), "v"(bpick<J>(ty)), "v"(s.x), "v"(s.y), "n"(j), "v"(bpick<J>(bx)),
+                 "v"(bpick<J>(by)));
+  acc.x -= px;
+  acc.y -= py;
+  e.acc = acc;
+  sfor<4>([&](auto G) {
+    constexpr int g = G;
+    constexpr int k0 = j + 1 > 4 * g ? j + 1 : 4 * g, n = 4 * g + 4 - k0;
+    if constexpr (n > 0) {
+      // columns of padded users only: nothing to update
+      if (g == j / 4 || U > P + 4 * g) elim_cols<UT, J, P + k0, n, g != j / 4>(&v[k0], bpick<J>(bx), bpick<J>(by), s);
+    }
+  });
+  if constexpr (ZERO) {
+    constexpr uint32_t end = UT == 32 && P == 0 ? lanes_ge<UT>(16) : 0u;
+    v[j] = lanes(lanes_ge<UT>(J + 1) & ~end) ? make_float2(0.f, 0.f) : s;
+  }
+  step_fence();
+}
+
+// Steps P .. P+15, in fours; those of padded users only (from U on, where A
+// is the identity) are left out.  U is wave-uniform.
+template <int UT, int P, bool ZERO>
+__device__ __forceinline__ void elim_phase(float2 (&v)[16], Elim &e, int U) {
+  sfor<4>([&](auto Q) {
+    constexpr int q = Q;
+    if (q == 0 || U > P + 4 * q) {
+      elim_step<UT, P + 4 * q, ZERO>(v, e, U);
+      elim_step<UT, P + 4 * q + 1, ZERO>(v, e, U);
+      elim_step<UT, P + 4 * q + 2, ZERO>(v, e, U);
+      elim_step<UT, P + 4 * q + 3, ZERO>(v, e, U);
+    }
+  });
+}
+
+// Between the halves of a 32 x 32 elimination: with A = [A11 .; A21 A22] in
+// 16 x 16 blocks, S = A22 - L21 L21^H and conj(Y) = -conj(L21 X11) for the
+// NS systems of the wave, complex products on 16x16x4 FP32 MFMA (four real
+// products each).  The slot of a system holds conj(X11) (row u: column u) in
+// its block (0, 0), L21 in (1, 0) and A22 in (1, 1); S replaces A22 and
+// column u of conj(Y) goes to row u of the block (0, 1).
+template <int NS>
+__device__ __forceinline__ void elim_middle(float2 (*A)[32][32]) {
+  const int lane = lane_id();
+  const int lr = lane % 16, lg = lane / 16;
+#pragma unroll
+  for (int q = 0; q < NS; ++q) {
+    f4 sr, si, yr, yi;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float2 a22 = lds_el<32>(A[q], 16 + 4 * lg + r, 16 + lr);
+      sr[r] = a22.x;
+      si[r] = a22.y;
+      yr[r] = 0.f;
+      yi[r] = 0.f;
+    }
+#pragma unroll
+    for (int kc = 0; kc < 4; ++kc) {
+      const float2 l = lds_el<32>(A[q], 16 + lr, 4 * kc + lg);  // L21[lr][k]
+      const float2 x = lds_el<32>(A[q], lr, 4 * kc + lg);       // conj(X11)[k][lr]
+      // S -= l conj(l'),  conj(Y) -= conj(l) conj(x)
+      sr = mma32(-l.x, l.x, sr);
+      yr = mma32(-l.x, x.x, yr);
+      si = mma32(l.x, l.y, si);
+      yi = mma32(-l.x, x.y, yi);
+      sr = mma32(-l.y, l.y, sr);
+      yr = mma32(-l.y, x.y, yr);
+      si = mma32(-l.y, l.x, si);
+      yi = mma32(l.y, x.x, yi);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      lds_el<32>(A[q], 16 + 4 * lg + r, 16 + lr) = make_float2(sr[r], si[r]);
+      lds_el<32>(A[q], lr, 16 + 4 * lg + r) = make_float2(yr[r], yi[r]);
+    }
+  }
+}
+
+// The system of lane group `slot` of the LDS slots A (G + rho I, full
+// Hermitian rows; padded users carry the identity) with right-hand side m.
+template <int UT>
+struct LocalSolve {
+  float2 z;     // [A^{-1} m]_u
+  float d;      // [A^{-1}]_uu
+  float norm1;  // bound of ||A||_1
+  int fail;     // 0, or the first pivot that is not positive, + 1
+  bool bad;     // a non-finite entry in A or m
+};
+
+// KEEP: the slot is left holding X = L^{-1}, row u = conj of column u.
+template <int UT, bool KEEP, int NS>
+__device__ __forceinline__ void solve_slot(LocalSolve<UT> &r, float2 (*A)[UT][UT], int slot, int i, float2 m, int U) {
+  U = __builtin_amdgcn_readfirstlane(U);
+  float2(*As)[UT] = A[slot];
+  float2 v[16];
+  float rowsum = 0.f;
+  sfor<16>([&](auto K) {
+    constexpr int k = K;
+    const float2 a = lds_el<UT>(As, i, k);
+    rowsum = abs_row_acc(rowsum, a);
+    v[k] = lanes(lanes_ge<UT>(k)) ? a : make_float2(0.f, 0.f);
+  });
+  if constexpr (UT == 32) {
+    // the rest of the row counts for the norm; A22 stays in the slot
+    sfor<16>([&](auto K) {
+      constexpr int k = K;
+      rowsum = abs_row_acc(rowsum, lds_el<UT>(As, i, 16 + k));
+    });
+  }
+  r.bad = gany<UT>(!isfinite(abs_row_acc(rowsum, m)));
+  r.norm1 = gmax<UT>(i < U ? rowsum * (1.f / kRowScale) : 0.f);
+  Elim e;
+  e.acc = m;
+  e.d = 0.f;
+  e.okm = ~0ull;
+  e.npos = 0;
+  elim_phase<UT, 0, KEEP || UT == 32>(v, e, U);
+  if constexpr (UT == 32) {
+    // conj(X11) by columns from the first 16 lanes, L21 by rows from the others
+    sfor<16>([&](auto K) {
+      constexpr int k = K;
+      lds_el<UT>(As, i, k) = v[k];
+    });
+    __syncthreads();
+    elim_middle<NS>(A);
+    __syncthreads();
+    sfor<16>([&](auto K) {
+      constexpr int k = K;
+      const float2 a = lds_el<UT>(As, i, 16 + k);
+      v[k] = lanes(lanes_ge<UT>(16 + k) | ~lanes_ge<UT>(16)) ? a : make_float2(0.f, 0.f);
+    });
+    elim_phase<UT, 16, KEEP>(v, e, U);
+    if constexpr (KEEP) {
+      sfor<16>([&](auto K) {
+        constexpr int k = K;
+        lds_el<UT>(As, i, 16 + k) = v[k];
+        if (i >= 16) lds_el<UT>(As, i, k) = make_float2(0.f, 0.f);
+      });
+    }
+  } else if constexpr (KEEP) {
+    sfor<16>([&](auto K) {
+      constexpr int k = K;
+      lds_el<UT>(As, i, k) = v[k];
+    });
+  }
+  r.z = make_float2(-e.acc.x, -e.acc.y);
+  r.d = e.d;
+  const int steps = (U + 3) / 4 * 4;
+  const int npos = UT == 16 ? (int)(e.npos >> (16 * (lane_id() / 16))) & 0xffff : (int)(e.npos >> (32 * (lane_id() / 32)));
+  r.fail = npos == steps ? 0 : npos + 1;
+}
+
 // Unbiased L-MMSE: the L-MMSE estimate of user u has gain
 // mu_u = [(G + rho I)^{-1} G]_uu = 1 - rho d_u = 1 - sigma2_u / E_s; returns
 // 1 / mu_u for ub = 1/E_s, and exactly 1 for ub = 0 (biased L-MMSE, ZF).

@@ -28,7 +28,7 @@ __device__ __forceinline__ int slot_of(int g) {
 
 // Loads row i of system `sme` from LDS and factorises / solves it.
 template <int UT>
-struct LocalSolve {
+struct FactorSolve {
   Factor<UT> f;
   float2 z;
   float d;
@@ -42,7 +42,7 @@ struct LocalSolve {
 // (PAD & 1) or 8 in a 16-lane group (PAD & 2); the FD forms, which solve one
 // system per cluster, use it (PD measured no faster).
 template <int UT, int PAD = 0, class SM>
-__device__ __forceinline__ void local_solve(LocalSolve<UT> &r, SM &sm, int sme, int i, int U) {
+__device__ __forceinline__ void factor_local(FactorSolve<UT> &r, SM &sm, int sme, int i, int U) {
   float rowsum = 0.f;
 #pragma unroll
   for (int k = 0; k < UT; ++k) {
@@ -62,12 +62,19 @@ __device__ __forceinline__ void local_solve(LocalSolve<UT> &r, SM &sm, int sme, 
   r.d = inv_diag<UT>(r.f);
 }
 
+// Factorises and solves the system of lane group `sme` (slot `sme`); KEEP
+// leaves X = L^{-1} in the slot for the refinement step.
+template <int UT, bool KEEP = false, class SM>
+__device__ __forceinline__ void local_solve(LocalSolve<UT> &r, SM &sm, int sme, int i, int U) {
+  solve_slot<UT, KEEP, SM::NS>(r, sm.A, sme, i, sm.M[sme][i], U);
+}
+
 // One refinement step for the systems of a round: every group's z goes to
 // LDS, the residual pass streams the systems' rows again and each group
 // solves A dz = H^H (y - H z) - rho z as dz = X^H (X r) with X = L^{-1}
-// (A^{-1} = X^H X): the columns of X are parked in LDS during the pass,
-// t = X r is read back along rows of X and dz = X^H t uses the reloaded
-// columns, so the factor L is dead once the inverse is formed.
+// (A^{-1} = X^H X): local_solve left X in the slot (row u = conj of column u)
+// during the pass, t = X r is read along rows of X and dz = X^H t uses the
+// columns.
 template <int UT, class SM, class Rho, class Seg>
 __device__ __forceinline__ void refine_round(LocalSolve<UT> &r, SM &sm, int nvalid, int U,
                                              Rho rhof, Seg seg, bool live) {
@@ -75,9 +82,6 @@ __device__ __forceinline__ void refine_round(LocalSolve<UT> &r, SM &sm, int nval
   const int sme = slot_of<SM>(lane / UT), i = lane % UT;
   __syncthreads();
   sm.M[sme][i] = r.z;
-  // row u of the slot holds column u of X: lds_el(A, u, k) = X_ku
-#pragma unroll
-  for (int k = 0; k < UT; ++k) lds_el<UT>(sm.A[sme], i, k) = r.f.x[k];
   __syncthreads();
   residual_stream<UT>(
       nvalid, U, seg, [&](int s) { return sm.M[s][lane % UT]; },
@@ -87,19 +91,22 @@ __device__ __forceinline__ void refine_round(LocalSolve<UT> &r, SM &sm, int nval
         if (lane < UT) sm.F[s][lane] = make_float4(n.x - rho * zc.x, n.y - rho * zc.y, 0.f, 0.f);
       });
   __syncthreads();
-  asm volatile("" ::: "memory");  // reload the parked columns instead of keeping them live
   // t_j = sum_u X_ju r_u at lane j
   float tx = 0.f, ty = 0.f;
 #pragma unroll
   for (int u = 0; u < UT; ++u) {
-    const float2 x = lds_el<UT>(sm.A[sme], u, i);
+    const float2 x = lds_el<UT>(sm.A[sme], u, i);  // conj(X_iu)
     const float4 rv = sm.F[sme][u];
-    tx = fmaf(x.x, rv.x, fmaf(-x.y, rv.y, tx));
-    ty = fmaf(x.x, rv.y, fmaf(x.y, rv.x, ty));
+    tx = fmaf(x.x, rv.x, fmaf(x.y, rv.y, tx));
+    ty = fmaf(x.x, rv.y, fmaf(-x.y, rv.x, ty));
   }
+  Factor<UT> f;
 #pragma unroll
-  for (int k = 0; k < UT; ++k) r.f.x[k] = lds_el<UT>(sm.A[sme], i, k);
-  const float2 dz = apply_xh<UT>(r.f, make_float2(tx, ty));
+  for (int k = 0; k < UT; ++k) {
+    const float2 x = lds_el<UT>(sm.A[sme], i, k);
+    f.x[k] = make_float2(x.x, -x.y);
+  }
+  const float2 dz = apply_xh<UT>(f, make_float2(tx, ty));
   if (live) {
     r.z.x += dz.x;
     r.z.y += dz.y;
