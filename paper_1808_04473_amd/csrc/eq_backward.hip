@@ -184,8 +184,9 @@ __device__ __forceinline__ void gram_round(const BwdArgs &a, BSmem<UT> &sm, int 
   constexpr int NSYS = 64 / UT;
   const int lane = lane_id();
   gram_stream<UT, PREC_FP32, kLoadKeep>(nvalid, a.U, seg, [&](int s, const Acc<UT> &acc, float2 mf) {
-    store_gram<UT, PREC_FP32>(sm.r.A[s], acc, a.rho);
-    if (lane < UT) sm.r.M[s][lane] = mf;
+    store_gram_shift<UT, PREC_FP32>(sm.r.A[s], acc, a.rho);
+    const float2 mc = make_float2(colsum<UT>(mf.x), colsum<UT>(mf.y));
+    if (lane < UT) sm.r.M[s][lane] = mc;
   });
   for (int s = nvalid; s < NSYS; ++s) {
     store_identity<UT>(sm.r.A[s]);

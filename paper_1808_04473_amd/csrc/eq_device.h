@@ -144,11 +144,14 @@ __device__ __forceinline__ float gsum(float v) {
 }
 template <int UT>
 __device__ __forceinline__ float gmax(float v) {
-  v = fmaxf(v, __shfl_xor(v, 1));
-  v = fmaxf(v, __shfl_xor(v, 2));
-  v = fmaxf(v, __shfl_xor(v, 4));
-  v = fmaxf(v, __shfl_xor(v, 8));
-  if constexpr (UT == 32) v = fmaxf(v, __shfl_xor(v, 16));
+  v = fmaxf(v, dpp<DPP_QUAD_XOR1>(v));
+  v = fmaxf(v, dpp<DPP_QUAD_XOR2>(v));
+  v = fmaxf(v, dpp<DPP_ROW_HMIRROR>(v));
+  v = fmaxf(v, dpp<DPP_ROW_MIRROR>(v));
+  if constexpr (UT == 32) {
+    const BSrc r = bsrc<32>(v);
+    v = fmaxf(r.lo, r.hi);
+  }
   return v;
 }
 template <int UT>
@@ -459,7 +462,8 @@ __device__ __forceinline__ void gram_blk(const Slot &sl, int U, Acc<UT> &acc, fl
 }
 
 // Gram + matched filter of systems 0..ns-1; done(s, acc, mf) receives each
-// system's accumulators and its matched filter (reduced over a column).
+// system's accumulators and this lane's share of its matched filter (the sum
+// over the 64/UT lanes of a column, see colsum, is the matched filter).
 // AUX is the loads' cache policy (kLoadLast unless a later pass re-reads H).
 template <int UT, int PREC, int AUX, class Seg, class Done>
 __device__ __forceinline__ void gram_stream(int ns, int U, Seg seg, Done done) {
@@ -469,7 +473,7 @@ __device__ __forceinline__ void gram_stream(int ns, int U, Seg seg, Done done) {
   stream_blocks<UT, AUX>(
       ns, U, seg, [&](const Slot &b) { gram_blk<UT, PREC>(b, U, acc, mfx, mfy); },
       [&](int s) {
-        done(s, acc, make_float2(colsum<UT>(mfx), colsum<UT>(mfy)));
+        done(s, acc, make_float2(mfx, mfy));
         acc_zero<UT>(acc);
         mfx = 0.f;
         mfy = 0.f;
@@ -517,6 +521,86 @@ __device__ __forceinline__ float2 &lds_el(float2 (*As)[UT], int i, int k) {
   return As[i][k ^ i];
 }
 
+// LDS slot of a local solve: the 16 x 16 blocks (0, 0), and for 32 users
+// (1, 0) and (1, 1), of the Hermitian matrix, 2 KB each (a third less LDS
+// than the full matrix at 32 users: 12 instead of 9 waves per CU).  Swizzled
+// like lds_el.
+template <int UT>
+constexpr int kSlot = UT == 16 ? 256 : 768;
+__device__ __forceinline__ float2 &blk_el(float2 *As, int b, int i, int k) {
+  return As[256 * b + 16 * i + (k ^ i)];
+}
+
+// Orders this wave's LDS accesses before and after the point (they execute
+// in order; only the compiler must not move them).  Waves of a workgroup
+// that share nothing need no barrier.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Re G, Im G at the accumulator positions; the transposed ri comes through
+// UT x UT floats of LDS at `scratch` (swizzled like lds_el).
+template <int UT, int PREC, int NR>
+__device__ __forceinline__ void gram_values(float *scratch, const Acc<UT> &acc, float (&re)[NR], float (&im)[NR]) {
+  const int lane = lane_id();
+  sfor<NR>([&](auto R) {
+    constexpr int r = R;
+    int i, j;
+    acc_pos<UT>(lane, r, i, j);
+    scratch[UT * i + (j ^ i)] = acc.ri[r];
+  });
+  wave_sync();
+  sfor<NR>([&](auto R) {
+    constexpr int r = R;
+    int i, j;
+    acc_pos<UT>(lane, r, i, j);
+    const float rij = scratch[UT * j + (i ^ j)];  // (Hr^T Hi)[j][i]
+    im[r] = acc.ri[r] - rij;
+    re[r] = PREC == PREC_FP32 ? acc.rr[r] - acc.ri[r] - rij : acc.rr[r] + acc.ii[r];
+  });
+  wave_sync();
+}
+
+// Writes G of one system from the MFMA accumulators into LDS (full Hermitian
+// matrix, swizzled rows):
+//   Re G = Hr^T Hr + Hi^T Hi,   Im G[i][j] = (Hr^T Hi)[i][j] - (Hr^T Hi)[j][i],
+// with Re G = P - ri - ri^T for the two-product FP32 accumulators (see
+// gram_blk).  Rows and columns of padded users (i >= U) are zero.
+template <int UT, int PREC>
+__device__ __forceinline__ void store_gram(float2 (*As)[UT], const Acc<UT> &acc) {
+  constexpr int NR = UT == 16 ? 4 : 16;
+  const int lane = lane_id();
+  float im[NR], re[NR];
+  gram_values<UT, PREC>(&lds_el<UT>(As, 0, 0).x, acc, re, im);
+  sfor<NR>([&](auto R) {
+    constexpr int r = R;
+    int i, j;
+    acc_pos<UT>(lane, r, i, j);
+    lds_el<UT>(As, i, j) = make_float2(re[r], im[r]);
+  });
+}
+
+// The same into the packed slot of the local solves.
+template <int UT, int PREC>
+__device__ __forceinline__ void store_gram_packed(float2 *As, const Acc<UT> &acc) {
+  constexpr int NR = UT == 16 ? 4 : 16;
+  const int lane = lane_id();
+  float im[NR], re[NR];
+  gram_values<UT, PREC>(&As[0].x, acc, re, im);
+  sfor<NR>([&](auto R) {
+    constexpr int r = R;
+    int i, j;
+    acc_pos<UT>(lane, r, i, j);
+    if constexpr (UT == 16) {
+      blk_el(As, 0, i, j) = make_float2(re[r], im[r]);
+    } else {
+      // rows 0..15 are registers 0..7: of those only the block (0, 0) is kept
+      if (r >= 8 || j < 16) blk_el(As, r < 8 ? 0 : 1 + (j >> 4), i & 15, j & 15) = make_float2(re[r], im[r]);
+    }
+  });
+}
+
 // Writes G + rho I of one system from the MFMA accumulators into LDS
 // (full Hermitian matrix, swizzled rows):
 //   Re G = Hr^T Hr + Hi^T Hi,   Im G[i][j] = (Hr^T Hi)[i][j] - (Hr^T Hi)[j][i],
@@ -526,7 +610,7 @@ __device__ __forceinline__ float2 &lds_el(float2 (*As)[UT], int i, int k) {
 // (ZF).  That block is decoupled from the users' block, whose factor and
 // solves it leaves unchanged.
 template <int UT, int PREC>
-__device__ __forceinline__ void store_gram(float2 (*As)[UT], const Acc<UT> &acc, float rho, int U = UT) {
+__device__ __forceinline__ void store_gram_shift(float2 (*As)[UT], const Acc<UT> &acc, float rho, int U = UT) {
   constexpr int NR = UT == 16 ? 4 : 16;
   const int lane = lane_id();
   sfor<NR>([&](auto R) {
@@ -1162,9 +1246,10 @@ struct Elim {
 // Step J.  ZERO: v[J] is left as conj(X_Ju) in lane u (zero in lanes past J
 // of the same 16 rows), for callers that use X.
 template <int UT, int J, bool ZERO>
-__device__ __forceinline__ void elim_step(float2 (&v)[16], Elim &e, int U) {
+__device__ __forceinline__ void elim_step(float2 (&v)[16], Elim &e, float rho, int U) {
   constexpr int j = J % 16, P = J - j;
-  const float ajj = gbcast<UT, J>(v[j].x);
+  // the shift of A = G + rho I enters here: nothing else reads the diagonal
+  const float ajj = gbcast<UT, J>(v[j].x) + rho;
   e.okm &= __ballot(ajj > 0.f);
   e.npos += e.okm & (UT == 16 ? 0x0001000100010001ull : 0x0000000100000001ull);
   // hardware reciprocal square root (about 1 ulp): 1 / L_JJ
@@ -1211,37 +1296,33 @@ __device__ __forceinline__ void elim_step(float2 (&v)[16], Elim &e, int U) {
   step_fence();
 }
 
-// Steps P .. P+15, in fours; those of padded users only (from U on, where A
-// is the identity) are left out.  U is wave-uniform.
-template <int UT, int P, bool ZERO>
-__device__ __forceinline__ void elim_phase(float2 (&v)[16], Elim &e, int U) {
-  sfor<4>([&](auto Q) {
-    constexpr int q = Q;
-    if (q == 0 || U > P + 4 * q) {
-      elim_step<UT, P + 4 * q, ZERO>(v, e, U);
-      elim_step<UT, P + 4 * q + 1, ZERO>(v, e, U);
-      elim_step<UT, P + 4 * q + 2, ZERO>(v, e, U);
-      elim_step<UT, P + 4 * q + 3, ZERO>(v, e, U);
-    }
-  });
+// Steps J .. END-1 of those below U (wave-uniform).  The steps of padded users
+// are left out, so nothing reads their rows and columns.
+template <int UT, int J, int END, bool ZERO>
+__device__ __forceinline__ void elim_steps(float2 (&v)[16], Elim &e, float rho, int U) {
+  elim_step<UT, J, ZERO>(v, e, rho, U);
+  if constexpr (J + 1 < END) {
+    if (U > J + 1) elim_steps<UT, J + 1, END, ZERO>(v, e, rho, U);
+  }
 }
 
 // Between the halves of a 32 x 32 elimination: with A = [A11 .; A21 A22] in
 // 16 x 16 blocks, S = A22 - L21 L21^H and conj(Y) = -conj(L21 X11) for the
 // NS systems of the wave, complex products on 16x16x4 FP32 MFMA (four real
 // products each).  The slot of a system holds conj(X11) (row u: column u) in
-// its block (0, 0), L21 in (1, 0) and A22 in (1, 1); S replaces A22 and
-// column u of conj(Y) goes to row u of the block (0, 1).
+// its block 0, L21 in block 1 and A22 in block 2; S replaces A22 and conj(Y)
+// (row u: column u) replaces L21.
 template <int NS>
-__device__ __forceinline__ void elim_middle(float2 (*A)[32][32]) {
+__device__ __forceinline__ void elim_middle(float2 *A) {
   const int lane = lane_id();
   const int lr = lane % 16, lg = lane / 16;
 #pragma unroll
   for (int q = 0; q < NS; ++q) {
+    float2 *As = A + q * kSlot<32>;
     f4 sr, si, yr, yi;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const float2 a22 = lds_el<32>(A[q], 16 + 4 * lg + r, 16 + lr);
+      const float2 a22 = blk_el(As, 2, 4 * lg + r, lr);
       sr[r] = a22.x;
       si[r] = a22.y;
       yr[r] = 0.f;
@@ -1249,8 +1330,8 @@ __device__ __forceinline__ void elim_middle(float2 (*A)[32][32]) {
     }
 #pragma unroll
     for (int kc = 0; kc < 4; ++kc) {
-      const float2 l = lds_el<32>(A[q], 16 + lr, 4 * kc + lg);  // L21[lr][k]
-      const float2 x = lds_el<32>(A[q], lr, 4 * kc + lg);       // conj(X11)[k][lr]
+      const float2 l = blk_el(As, 1, lr, 4 * kc + lg);  // L21[lr][k]
+      const float2 x = blk_el(As, 0, lr, 4 * kc + lg);  // conj(X11)[k][lr]
       // S -= l conj(l'),  conj(Y) -= conj(l) conj(x)
       sr = mma32(-l.x, l.x, sr);
       yr = mma32(-l.x, x.x, yr);
@@ -1263,84 +1344,82 @@ __device__ __forceinline__ void elim_middle(float2 (*A)[32][32]) {
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      lds_el<32>(A[q], 16 + 4 * lg + r, 16 + lr) = make_float2(sr[r], si[r]);
-      lds_el<32>(A[q], lr, 16 + 4 * lg + r) = make_float2(yr[r], yi[r]);
+      blk_el(As, 2, 4 * lg + r, lr) = make_float2(sr[r], si[r]);
+      blk_el(As, 1, lr, 4 * lg + r) = make_float2(yr[r], yi[r]);
     }
   }
 }
 
-// The system of lane group `slot` of the LDS slots A (G + rho I, full
-// Hermitian rows; padded users carry the identity) with right-hand side m.
 template <int UT>
 struct LocalSolve {
-  float2 z;     // [A^{-1} m]_u
-  float d;      // [A^{-1}]_uu
-  float norm1;  // bound of ||A||_1
+  float2 z;     // [(G + rho I)^{-1} m]_u
+  float d;      // [(G + rho I)^{-1}]_uu
+  float norm1;  // bound of ||G + rho I||_1
   int fail;     // 0, or the first pivot that is not positive, + 1
-  bool bad;     // a non-finite entry in A or m
+  bool bad;     // a non-finite entry in G or m
 };
 
-// KEEP: the slot is left holding X = L^{-1}, row u = conj of column u.
+// Solves (G + rho I) z = m for the system of each lane group, G in the
+// group's packed slot (of NS slots from A; entries of padded users zero).
+// Lane i is user i; rho may differ between the groups.  KEEP: conj(X), X =
+// L^{-1}, is left in the slot: row u of blocks 0 and 1 (u < 16), or of block
+// 2, holds the rows 0..15 and 16..31 of column u (columns of padded users
+// are zero).
 template <int UT, bool KEEP, int NS>
-__device__ __forceinline__ void solve_slot(LocalSolve<UT> &r, float2 (*A)[UT][UT], int slot, int i, float2 m, int U) {
+__device__ __forceinline__ void solve_slot(LocalSolve<UT> &r, float2 *A, int slot, int i, float2 m, float rho, int U) {
   U = __builtin_amdgcn_readfirstlane(U);
-  float2(*As)[UT] = A[slot];
+  float2 *As = A + slot * kSlot<UT>;
+  const int h = UT == 32 ? i >> 4 : 0, ii = i & 15;
   float2 v[16];
   float rowsum = 0.f;
   sfor<16>([&](auto K) {
     constexpr int k = K;
-    const float2 a = lds_el<UT>(As, i, k);
+    const float2 a = blk_el(As, h, ii, k);
     rowsum = abs_row_acc(rowsum, a);
     v[k] = lanes(lanes_ge<UT>(k)) ? a : make_float2(0.f, 0.f);
   });
   if constexpr (UT == 32) {
-    // the rest of the row counts for the norm; A22 stays in the slot
+    // the rest of the row, for the norm (column ii of block 1 is its
+    // conjugate in the rows 0..15); A22 stays in the slot
     sfor<16>([&](auto K) {
       constexpr int k = K;
-      rowsum = abs_row_acc(rowsum, lds_el<UT>(As, i, 16 + k));
+      rowsum = abs_row_acc(rowsum, As[256 * (1 + h) + (h ? 16 * ii + (k ^ ii) : 16 * k + (ii ^ k))]);
     });
   }
   r.bad = gany<UT>(!isfinite(abs_row_acc(rowsum, m)));
-  r.norm1 = gmax<UT>(i < U ? rowsum * (1.f / kRowScale) : 0.f);
+  r.norm1 = gmax<UT>(i < U ? fmaf(rowsum, 1.f / kRowScale, rho) : 0.f);
   Elim e;
   e.acc = m;
   e.d = 0.f;
   e.okm = ~0ull;
   e.npos = 0;
-  elim_phase<UT, 0, KEEP || UT == 32>(v, e, U);
+  elim_steps<UT, 0, 16, KEEP || UT == 32>(v, e, rho, U);
   if constexpr (UT == 32) {
     // conj(X11) by columns from the first 16 lanes, L21 by rows from the others
     sfor<16>([&](auto K) {
       constexpr int k = K;
-      lds_el<UT>(As, i, k) = v[k];
+      blk_el(As, h, ii, k) = v[k];
     });
-    __syncthreads();
+    wave_sync();
     elim_middle<NS>(A);
-    __syncthreads();
+    wave_sync();
     sfor<16>([&](auto K) {
       constexpr int k = K;
-      const float2 a = lds_el<UT>(As, i, 16 + k);
+      const float2 a = blk_el(As, 1 + h, ii, k);
       v[k] = lanes(lanes_ge<UT>(16 + k) | ~lanes_ge<UT>(16)) ? a : make_float2(0.f, 0.f);
     });
-    elim_phase<UT, 16, KEEP>(v, e, U);
-    if constexpr (KEEP) {
-      sfor<16>([&](auto K) {
-        constexpr int k = K;
-        lds_el<UT>(As, i, 16 + k) = v[k];
-        if (i >= 16) lds_el<UT>(As, i, k) = make_float2(0.f, 0.f);
-      });
-    }
-  } else if constexpr (KEEP) {
+    elim_steps<UT, 16, 32, KEEP>(v, e, rho, U);
+  }
+  if constexpr (KEEP) {
     sfor<16>([&](auto K) {
       constexpr int k = K;
-      lds_el<UT>(As, i, k) = v[k];
+      blk_el(As, UT == 32 ? 1 + h : 0, ii, k) = v[k];
     });
   }
   r.z = make_float2(-e.acc.x, -e.acc.y);
   r.d = e.d;
-  const int steps = (U + 3) / 4 * 4;
   const int npos = UT == 16 ? (int)(e.npos >> (16 * (lane_id() / 16))) & 0xffff : (int)(e.npos >> (32 * (lane_id() / 32)));
-  r.fail = npos == steps ? 0 : npos + 1;
+  r.fail = npos == U ? 0 : npos + 1;
 }
 
 // Unbiased L-MMSE: the L-MMSE estimate of user u has gain

@@ -48,8 +48,8 @@ constexpr int pd_per() {
 // inverse columns alone take 129.
 template <int UT, int PREC, bool FD>
 constexpr int waves_target() {
-  if (UT == 32) return 2;
-  return (refines(PREC) || (FD && PREC == PREC_BF16X3_NR)) ? 3 : EQ_WAVES_PER_EU;
+  if (UT == 32) return refines(PREC) ? 2 : (FD ? 3 : 4);
+  return refines(PREC) ? 3 : EQ_WAVES_PER_EU;
 }
 
 template <int UT, int PREC, class SM>
@@ -69,20 +69,17 @@ __device__ __forceinline__ void pd_task(const FwdArgs &a, int w0, int nvalid, SM
   // ---- Gram + matched filter of the round's subcarriers (all clusters
   //      accumulate into one G and one y^MRC: the adder tree of eq. (fullMRC))
   gram_stream<UT, PREC, refines(PREC) ? kLoadKeep : kLoadLast>(nvalid, a.U, seg, [&](int s, const Acc<UT> &acc, float2 mf) {
-    store_gram<UT, PREC>(sm.A[s], acc, a.rho, a.U);
-    if (lane < UT) sm.M[s][lane] = mf;
+    store_gram_packed<UT, PREC>(sm.A + s * kSlot<UT>, acc);
+    sm.M[s][lane] = mf;
   });
-  for (int s = nvalid; s < SM::NS; ++s) {
-    store_identity<UT>(sm.A[s]);
-    if (lane < UT) sm.M[s][lane] = make_float2(0.f, 0.f);
-  }
-  __syncthreads();
+  wave_sync();
 
-  // ---- factor and solve: group sme, row/column i
+  // ---- factor and solve: group sme, row/column i (the groups past the last
+  //      system solve what is in their slot, and write nothing)
   const int w = w0 + sme;
   const bool live = sme < nvalid;
   LocalSolve<UT> r;
-  local_solve<UT, refines(PREC)>(r, sm, slot_of<SM>(sme), i, a.U);
+  local_solve<UT, refines(PREC)>(r, sm, slot_of<SM>(sme), i, a.rho, a.U);
   if constexpr (refines(PREC)) refine_round<UT>(r, sm, nvalid, a.U, [&](int) { return a.rho; }, seg, live);
 
   const float kappa = r.norm1 * gsum<UT>(i < a.U ? r.d : 0.f);
@@ -90,7 +87,7 @@ __device__ __forceinline__ void pd_task(const FwdArgs &a, int w0, int nvalid, SM
   if (live) {
     if (i < a.U) {
       const float nanv = __int_as_float(0x7fc00000);
-      const float s2 = a.n0 * r.d, k = unbias_factor(s2, a.ub);
+      const float s2 = a.n0 * r.d, k = a.ub != 0.f ? unbias_factor(s2, a.ub) : 1.f;
       a.z[(size_t)w * a.U + i] = r.bad ? make_float2(nanv, nanv) : make_float2(r.z.x * k, r.z.y * k);
       if (a.s2) a.s2[(size_t)w * a.U + i] = r.bad ? nanv : s2 * k;
     }
@@ -101,9 +98,28 @@ __device__ __forceinline__ void pd_task(const FwdArgs &a, int w0, int nvalid, SM
   }
 }
 
+// Sum over the gw lane groups that share a subcarrier (gw = 1, 2, 4 groups,
+// consecutive and aligned); every lane of them receives it.
+template <int UT>
+__device__ __forceinline__ float group_sum(float v, int gw) {
+  if (UT == 16 && gw > 1) {
+    const BSrc r = bsrc<32>(v);
+    v = r.lo + r.hi;
+  }
+  if (gw > (UT == 16 ? 2 : 1)) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  return v;
+}
+
+// All clusters of subcarriers w0 .. w0+nsub-1, NSYS clusters per round.  The
+// nw waves of the workgroup take the rounds in turn (nsub = 1 if nw > 1);
+// sms: the LDS of all of them.
 template <int UT, int PREC, class SM>
-__device__ __forceinline__ void fd_task(const FwdArgs &a, int w0, int nsub, SM &sm) {
+__device__ __forceinline__ void fd_task(const FwdArgs &a, int w0, int nsub, SM *sms, int wv, int nw) {
   constexpr int NSYS = 64 / UT;
+  SM &sm = sms[wv];
   const int lane = lane_id();
   const int sme = lane / UT;
   const int i = lane % UT;
@@ -113,13 +129,15 @@ __device__ __forceinline__ void fd_task(const FwdArgs &a, int w0, int nsub, SM &
   const int ntot = nsub * C;
   const bool user_nu = a.nu != nullptr;
   const float nanv = __int_as_float(0x7fc00000);
+  // lane groups per subcarrier of a round (C is 1 or 2 when it holds several)
+  const int gw = a.spw > 1 ? C : NSYS;
 
-  // fusion sums held by lane (wl = lane / UT, u = lane % UT)
-  const int wlf = lane / UT;
-  float sw = 0.f, szx = 0.f, szy = 0.f, sv = 0.f;
-  if (lane < NSYS) sm.routed[lane] = 0;
+  // fusion sums of user i of the group's subcarrier, and the lanes whose
+  // cluster was routed to FP64
+  float sw = 0.f, szx = 0.f, szy = 0.f;
+  unsigned long long routedm = 0;
 
-  for (int base = 0; base < ntot; base += NSYS) {
+  for (int base = wv * NSYS; base < ntot; base += nw * NSYS) {
     const int nvalid = min(NSYS, ntot - base);
     auto seg = [&](int s, const float2 *&Hw, const float2 *&yw, int &r0, int &r1) {
       const int idx = base + s;
@@ -132,14 +150,10 @@ __device__ __forceinline__ void fd_task(const FwdArgs &a, int w0, int nsub, SM &
     };
     // ---- local Gram + MRC of the clusters of this round
     gram_stream<UT, PREC, refines(PREC) ? kLoadKeep : kLoadLast>(nvalid, a.U, seg, [&](int s, const Acc<UT> &acc, float2 mf) {
-      store_gram<UT, PREC>(sm.A[s], acc, a.rho, a.U);
-      if (lane < UT) sm.M[s][lane] = mf;
+      store_gram_packed<UT, PREC>(sm.A + s * kSlot<UT>, acc);
+      sm.M[s][lane] = mf;
     });
-    for (int s = nvalid; s < NSYS; ++s) {
-      store_identity<UT>(sm.A[s]);
-      if (lane < UT) sm.M[s][lane] = make_float2(0.f, 0.f);
-    }
-    __syncthreads();
+    wave_sync();
 
     // ---- local L-MMSE of cluster (wl, c) by group sme
     const int idx = base + sme;
@@ -147,90 +161,88 @@ __device__ __forceinline__ void fd_task(const FwdArgs &a, int w0, int nsub, SM &
     const int w = w0 + wl;
     const bool live = sme < nvalid;
     LocalSolve<UT> r;
-    local_solve<UT, refines(PREC)>(r, sm, sme, i, a.U);
+    local_solve<UT, refines(PREC)>(r, sm, sme, i, a.rho, a.U);
     if constexpr (refines(PREC)) refine_round<UT>(r, sm, nvalid, a.U, [&](int) { return a.rho; }, seg, live);
 
     const float kappa = r.norm1 * gsum<UT>(i < a.U ? r.d : 0.f);
     const bool routed = live && !r.bad && (r.fail != 0 || !(kappa <= EQ_COND_LIMIT));
-    if (live && i == 0) {
-      if (a.info) a.info[(size_t)w * C + c] = (r.bad ? -1 : r.fail) | (routed ? EQ_INFO_FP64 : 0);
-      if (routed) sm.routed[wl] = 1;
-    }
-    // local estimate and variance (scaled to unit gain for the unbiased L-MMSE)
-    const float k = unbias_factor(a.n0 * r.d, a.ub);
+    if (live && i == 0 && a.info) a.info[(size_t)w * C + c] = (r.bad ? -1 : r.fail) | (routed ? EQ_INFO_FP64 : 0);
+    routedm |= __ballot(routed);
+    // ---- fusion terms of this cluster: its weight times the local estimate,
+    //      and the weight (optimal: 1 / sigma2_c) or nu^2 sigma2_c (given
+    //      weights); estimate and variance are scaled to unit gain for the
+    //      unbiased L-MMSE
+    const float k = a.ub != 0.f ? unbias_factor(a.n0 * r.d, a.ub) : 1.f;
     const float s2c = a.n0 * r.d * k;
-    __syncthreads();
-    sm.F[sme][i] = live ? (r.bad ? make_float4(nanv, nanv, nanv, 1.f) : make_float4(r.z.x * k, r.z.y * k, s2c, 1.f))
-                        : make_float4(0.f, 0.f, 0.f, 0.f);
-    __syncthreads();
-
-    // ---- fusion: lane (wlf, u) adds the clusters of its subcarrier, in c order
-    if (wlf < nsub && i < a.U) {
-      for (int s = 0; s < nvalid; ++s) {
-        const int idx3 = base + s;
-        if (idx3 / C != wlf) continue;
-        const float4 v = sm.F[s][i];
-        if (user_nu) {
-          const int c3 = idx3 - wlf * C;
-          const float nu = a.nu[((size_t)(w0 + wlf) * C + c3) * a.U + i];
-          szx += nu * v.x;
-          szy += nu * v.y;
-          sv += nu * nu * v.z;
-        } else {
-          const float p = 1.0f / v.z;
-          sw += p;
-          szx += p * v.x;
-          szy += p * v.y;
-        }
-      }
+    float p, q;
+    if (user_nu) {
+      p = live && i < a.U ? a.nu[((size_t)w * C + c) * a.U + i] : 0.f;
+      q = p * p * s2c;
+    } else {
+      p = q = 1.0f / s2c;
     }
-    __syncthreads();
+    const float pk = p * k;
+    float fx = r.bad ? nanv : pk * r.z.x, fy = r.bad ? nanv : pk * r.z.y;
+    if (r.bad) q = nanv;
+    if (!live) fx = fy = q = 0.f;
+    szx += group_sum<UT>(fx, gw);
+    szy += group_sum<UT>(fy, gw);
+    sw += group_sum<UT>(q, gw);
+    wave_sync();
   }
 
-  const int w = w0 + wlf;
-  if (wlf < nsub) {
+  if (nw > 1) {
+    // the waves' sums meet in wave order
+    float *part = &sm.M[0][0].x;
+    if (lane < UT) {
+      part[lane] = szx;
+      part[UT + lane] = szy;
+      part[2 * UT + lane] = sw;
+    }
+    if (lane == 0) part[3 * UT] = routedm != 0 ? 1.f : 0.f;
+    __syncthreads();
+    if (wv != 0) return;
+    szx = szy = sw = 0.f;
+    for (int q = 0; q < nw; ++q) {
+      const float *o = &sms[q].M[0][0].x;
+      szx += o[i];
+      szy += o[UT + i];
+      sw += o[2 * UT + i];
+      if (o[3 * UT] != 0.f) routedm = ~0ull;
+    }
+  }
+  const int wl = sme / gw;
+  if (sme == wl * gw && wl < nsub) {
+    const int w = w0 + wl;
     if (i < a.U) {
-      float2 zo;
-      float so;
-      if (user_nu) {
-        zo = make_float2(szx, szy);
-        so = sv;
-      } else {
-        const float inv = 1.0f / sw;
-        zo = make_float2(szx * inv, szy * inv);
-        so = inv;
-      }
-      a.z[(size_t)w * a.U + i] = zo;
-      if (a.s2) a.s2[(size_t)w * a.U + i] = so;
+      const float inv = 1.0f / sw;
+      a.z[(size_t)w * a.U + i] = user_nu ? make_float2(szx, szy) : make_float2(szx * inv, szy * inv);
+      if (a.s2) a.s2[(size_t)w * a.U + i] = user_nu ? sw : inv;
     }
-    if (i == 0 && sm.routed[wlf]) enqueue_fp64(a, w);
+    const unsigned long long mine = (gw * UT == 64 ? ~0ull : (1ull << (gw * UT)) - 1ull) << (sme * UT);
+    if (i == 0 && (routedm & mine)) enqueue_fp64(a, w);
   }
 }
 
-// Systems per work item: a round of subcarriers (PD) or `spw` subcarriers
-// with all their clusters (FD).
-template <int UT, int PREC, bool FD>
-__host__ __device__ constexpr int task_size(int spw) {
-  return FD ? spw : pd_per<UT, PREC>();
+// PD: one wave per workgroup; workgroup b takes systems b per .. of W.
+template <int UT, int PREC>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(waves_target<UT, PREC, false>(), 8))) void eq_forward_pd_kernel(const FwdArgs a) {
+  constexpr int per = pd_per<UT, PREC>();
+  // work items of fewer systems than lane groups need fewer matrix slots
+  __shared__ SolveSmem<UT, refines(PREC), (per < 64 / UT ? per : 64 / UT)> sm;
+  const int w0 = blockIdx.x * per;
+  pd_task<UT, PREC>(a, w0, min(per, a.W - w0), sm);
 }
 
-// One wave per workgroup.  Workgroup b of G takes the contiguous share
-// [b W / G, (b+1) W / G) of the systems, in work items of up to task_size
-// systems (with G = ceil(W / task_size), one work item each).
-template <int UT, int PREC, bool FD>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(waves_target<UT, PREC, FD>(), 8))) void eq_forward_kernel(const FwdArgs a) {
-  // PD work items of fewer systems than lane groups need fewer matrix slots
-  __shared__ Smem<UT, FD ? 64 / UT : (pd_per<UT, PREC>() < 64 / UT ? pd_per<UT, PREC>() : 64 / UT)> sm;
-  const int per = task_size<UT, PREC, FD>(a.spw);
-  const int lo = (int)((long long)blockIdx.x * a.W / gridDim.x);
-  const int hi = (int)((long long)(blockIdx.x + 1) * a.W / gridDim.x);
-  for (int w = lo; w < hi; w += per) {
-    const int n = min(per, hi - w);
-    if constexpr (FD)
-      fd_task<UT, PREC>(a, w, n, sm);
-    else
-      pd_task<UT, PREC>(a, w, n, sm);
-  }
+// FD: blockDim / 64 waves per workgroup (fd_waves), `spw` subcarriers.
+constexpr int kFdWaves = 4;
+template <int UT, int PREC>
+__global__ __launch_bounds__(64 * kFdWaves) __attribute__((amdgpu_waves_per_eu(waves_target<UT, PREC, true>(), 8))) void eq_forward_fd_kernel(const FwdArgs a) {
+  extern __shared__ float2 fd_lds[];
+  using SM = SolveSmem<UT, refines(PREC)>;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), nw = blockDim.x / 64;
+  const int w0 = blockIdx.x * a.spw;
+  fd_task<UT, PREC>(a, w0, min(a.spw, a.W - w0), reinterpret_cast<SM *>(fd_lds), wv, nw);
 }
 
 __global__ void zero_i32_kernel(int32_t *p, int n) {
@@ -243,14 +255,30 @@ hipError_t launch_zero_i32(int32_t *p, int n, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Waves per FD workgroup: one per round of a subcarrier, at most kFdWaves.  A
+// subcarrier of B = 1024, C = 16, U = 32 keeps one wave busy for about 0.2 ms
+// and 4,800 of them were barely more than two generations of one-wave
+// workgroups: 490 us with one wave each, 458 with two, 428 with four (the
+// 38,400 subcarriers of B = 256, C = 8, U = 16 take 317 us either way, the
+// 1,200 of one symbol 26.6 against 23.8 us).
+static int fd_waves(int UT, int C) {
+  const int rounds = (C * UT + 63) / 64;
+  return rounds < kFdWaves ? rounds : kFdWaves;
+}
+
 template <int UT, int PREC, bool FD>
 static hipError_t launch_one(const FwdArgs &a, hipStream_t s) {
   // one work item per workgroup: the hardware dispatcher refills a freed slot
   // at once (a one-generation grid with equal shares per workgroup measured
   // slower: its partial rounds add solves)
-  const int per = task_size<UT, PREC, FD>(a.spw);
-  const int grid = (a.W + per - 1) / per;
-  hipLaunchKernelGGL((eq_forward_kernel<UT, PREC, FD>), dim3(grid), dim3(64), 0, s, a);
+  if constexpr (FD) {
+    const int nw = a.spw > 1 ? 1 : fd_waves(UT, a.C);
+    hipLaunchKernelGGL((eq_forward_fd_kernel<UT, PREC>), dim3((a.W + a.spw - 1) / a.spw), dim3(64 * nw),
+                       nw * sizeof(SolveSmem<UT, refines(PREC)>), s, a);
+  } else {
+    constexpr int per = pd_per<UT, PREC>();
+    hipLaunchKernelGGL((eq_forward_pd_kernel<UT, PREC>), dim3((a.W + per - 1) / per), dim3(64), 0, s, a);
+  }
   return hipGetLastError();
 }
 

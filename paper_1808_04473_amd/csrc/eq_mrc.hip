@@ -60,8 +60,9 @@ __device__ __forceinline__ void mrc_pd_task(const FwdArgs &a, int w0, int nvalid
     r1 = a.B;
   };
   gram_stream<UT, PREC, kLoadLast>(nvalid, a.U, seg, [&](int s, const Acc<UT> &acc, float2 mf) {
-    store_gram<UT, PREC>(sm.A[s], acc, 0.f);
-    if (lane < UT) sm.M[s][lane] = mf;
+    store_gram<UT, PREC>(sm.A[s], acc);
+    const float2 mc = make_float2(colsum<UT>(mf.x), colsum<UT>(mf.y));
+      if (lane < UT) sm.M[s][lane] = mc;
   });
   __syncthreads();
   const MrcOut o = mrc_local<UT>(sm, g, i, a.U, a.n0, a.es);
@@ -95,8 +96,9 @@ __device__ __forceinline__ void mrc_fd_task(const FwdArgs &a, int w, Smem<UT> &s
       r1 = a.off[base + s + 1];
     };
     gram_stream<UT, PREC, kLoadLast>(nvalid, a.U, seg, [&](int s, const Acc<UT> &acc, float2 mf) {
-      store_gram<UT, PREC>(sm.A[s], acc, 0.f);
-      if (lane < UT) sm.M[s][lane] = mf;
+      store_gram<UT, PREC>(sm.A[s], acc);
+      const float2 mc = make_float2(colsum<UT>(mf.x), colsum<UT>(mf.y));
+      if (lane < UT) sm.M[s][lane] = mc;
     });
     __syncthreads();
     const int c = base + g;

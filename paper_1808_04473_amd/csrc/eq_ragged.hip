@@ -52,19 +52,16 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 // G + rho I and matched filters in sm.A / sm.M; seg re-streams them for the
 // refinement step.
 template <int UT, int PREC, class SysK, class Seg>
-__device__ __forceinline__ void pd_solve_round(const RaggedArgs &a, Smem<UT> &sm, int n, int U, SysK sysk,
+__device__ __forceinline__ void pd_solve_round(const RaggedArgs &a, SolveSmem<UT, refines(PREC)> &sm, int n, int U, SysK sysk,
                                                Seg seg) {
   constexpr int NSYS = 64 / UT;
   const int lane = lane_id();
   const int sme = lane / UT, i = lane % UT;
-  for (int s = n; s < NSYS; ++s) {
-    store_identity<UT>(sm.A[s]);
-    if (lane < UT) sm.M[s][lane] = make_float2(0.f, 0.f);
-  }
-  __syncthreads();
+  wave_sync();
   const bool live = sme < n;
+  const float rho = a.sys[sysk(live ? sme : 0)].rho;
   LocalSolve<UT> r;
-  local_solve<UT, refines(PREC)>(r, sm, sme, i, U);
+  local_solve<UT, refines(PREC)>(r, sm, sme, i, rho, U);
   if constexpr (refines(PREC))
     refine_round<UT>(r, sm, n, U, [&](int s) { return a.sys[sysk(s)].rho; }, seg, live);
   const float kappa = r.norm1 * gsum<UT>(i < U ? r.d : 0.f);
@@ -88,7 +85,7 @@ __device__ __forceinline__ void pd_solve_round(const RaggedArgs &a, Smem<UT> &sm
 }
 
 template <int UT, int PREC>
-__device__ __forceinline__ void pd_group(const RaggedArgs &a, const RTask &task, Smem<UT> &sm) {
+__device__ __forceinline__ void pd_group(const RaggedArgs &a, const RTask &task, SolveSmem<UT, refines(PREC)> &sm) {
   const int lane = lane_id();
   const int n = task.count;
   const int U = task.U;
@@ -101,14 +98,14 @@ __device__ __forceinline__ void pd_group(const RaggedArgs &a, const RTask &task,
     r1 = d.B;
   };
   gram_stream<UT, PREC, refines(PREC) ? kLoadKeep : kLoadLast>(n, U, seg, [&](int s, const Acc<UT> &acc, float2 mf) {
-    store_gram<UT, PREC>(sm.A[s], acc, a.sys[sysk(s)].rho);
-    if (lane < UT) sm.M[s][lane] = mf;
+    store_gram_packed<UT, PREC>(sm.A + s * kSlot<UT>, acc);
+    sm.M[s][lane] = mf;
   });
   pd_solve_round<UT, PREC>(a, sm, n, U, sysk, seg);
 }
 
 template <int UT, int PREC>
-__device__ __forceinline__ void pd_piece(const RaggedArgs &a, const RTask &task, Smem<UT> &sm) {
+__device__ __forceinline__ void pd_piece(const RaggedArgs &a, const RTask &task, SolveSmem<UT, refines(PREC)> &sm) {
   constexpr int R = acc_regs<UT>();
   constexpr bool II = PREC != PREC_FP32;  // the FP32 Gram keeps two accumulator arrays
   const int lane = lane_id();
@@ -155,8 +152,8 @@ __device__ __forceinline__ void pd_piece(const RaggedArgs &a, const RTask &task,
     mf.x += ld_dev(q + 3 * R * 64 + lane);
     mf.y += ld_dev(q + (3 * R + 1) * 64 + lane);
   }
-  store_gram<UT, PREC>(sm.A[0], acc, d.rho);
-  if (lane < UT) sm.M[0][lane] = mf;
+  store_gram_packed<UT, PREC>(sm.A, acc);
+  sm.M[0][lane] = mf;
   auto seg_whole = [&](int, const float2 *&Hw, const float2 *&yw, int &r0, int &r1) {
     Hw = a.Hpool + d.h_off;
     yw = a.ypool + d.y_off;
@@ -167,7 +164,7 @@ __device__ __forceinline__ void pd_piece(const RaggedArgs &a, const RTask &task,
 }
 
 template <int UT, int PREC>
-__device__ __forceinline__ void fd_round(const RaggedArgs &a, const RTask &task, Smem<UT> &sm) {
+__device__ __forceinline__ void fd_round(const RaggedArgs &a, const RTask &task, SolveSmem<UT, refines(PREC)> &sm) {
   constexpr int NSYS = 64 / UT;
   const int lane = lane_id();
   const int sme = lane / UT, i = lane % UT;
@@ -186,17 +183,14 @@ __device__ __forceinline__ void fd_round(const RaggedArgs &a, const RTask &task,
     r1 = a.offs[d.off_first + c + 1];
   };
   gram_stream<UT, PREC, refines(PREC) ? kLoadKeep : kLoadLast>(n, U, seg, [&](int s, const Acc<UT> &acc, float2 mf) {
-    store_gram<UT, PREC>(sm.A[s], acc, a.sys[sysk(s)].rho);
-    if (lane < UT) sm.M[s][lane] = mf;
+    store_gram_packed<UT, PREC>(sm.A + s * kSlot<UT>, acc);
+    sm.M[s][lane] = mf;
   });
-  for (int s = n; s < NSYS; ++s) {
-    store_identity<UT>(sm.A[s]);
-    if (lane < UT) sm.M[s][lane] = make_float2(0.f, 0.f);
-  }
-  __syncthreads();
+  wave_sync();
   const bool live = sme < n;
+  const float rho = a.sys[sysk(live ? sme : 0)].rho;
   LocalSolve<UT> r;
-  local_solve<UT, refines(PREC)>(r, sm, sme, i, U);
+  local_solve<UT, refines(PREC)>(r, sm, sme, i, rho, U);
   if constexpr (refines(PREC))
     refine_round<UT>(r, sm, n, U, [&](int s) { return a.sys[sysk(s)].rho; }, seg, live);
   const float kappa = r.norm1 * gsum<UT>(i < U ? r.d : 0.f);
@@ -267,11 +261,11 @@ __device__ __forceinline__ void fd_round(const RaggedArgs &a, const RTask &task,
 }
 
 template <int PREC, bool FD>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(refines(PREC) ? 1 : 2, 8))) void eq_ragged_kernel(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void eq_ragged_kernel(
     const RaggedArgs a) {
   __shared__ union {
-    Smem<16> s16;
-    Smem<32> s32;
+    SolveSmem<16, refines(PREC)> s16;
+    SolveSmem<32, refines(PREC)> s32;
   } sm;
   const int lane = lane_id();
   const int q = (int)(blockIdx.x % kQueues);
@@ -298,7 +292,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(refines(PREC
       else
         pd_group<32, PREC>(a, task, sm.s32);
     }
-    __syncthreads();
+    wave_sync();
   }
 }
 

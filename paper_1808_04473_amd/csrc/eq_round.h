@@ -2,6 +2,8 @@
 // staging of a round of NSYS = 64/UT small systems and the per-group
 // factorisation of one system.
 #pragma once
+#include <type_traits>
+
 #include "eq_device.h"
 
 namespace dbpeq {
@@ -62,49 +64,89 @@ __device__ __forceinline__ void factor_local(FactorSolve<UT> &r, SM &sm, int sme
   r.d = inv_diag<UT>(r.f);
 }
 
+// LDS of one wave of the local solves: NSLOT packed matrix slots (one per
+// system of a round by default; fewer when the work items hold fewer systems
+// than there are lane groups) and, per system, every lane's share of the
+// matched filter: 10 KB at 16 users, so 16 waves per CU, and 13 KB (12 waves)
+// at 32.  R: right-hand sides of the refinement step.
+template <int UT, int NS>
+struct RefineRhs {
+  float2 R[NS][UT];
+};
+struct NoRefineRhs {};
+template <int UT, bool REFINE, int NSLOT = 64 / UT>
+struct SolveSmem : std::conditional_t<REFINE, RefineRhs<UT, NSLOT>, NoRefineRhs> {
+  static constexpr int NS = NSLOT;
+  float2 A[NS * kSlot<UT>];
+  float2 M[NS][64];
+};
+
 // Factorises and solves the system of lane group `sme` (slot `sme`); KEEP
 // leaves X = L^{-1} in the slot for the refinement step.
-template <int UT, bool KEEP = false, class SM>
-__device__ __forceinline__ void local_solve(LocalSolve<UT> &r, SM &sm, int sme, int i, int U) {
-  solve_slot<UT, KEEP, SM::NS>(r, sm.A, sme, i, sm.M[sme][i], U);
+template <int UT, bool KEEP, class SM>
+__device__ __forceinline__ void local_solve(LocalSolve<UT> &r, SM &sm, int sme, int i, float rho, int U) {
+  float2 m = sm.M[sme][i];
+#pragma unroll
+  for (int g = 1; g < 64 / UT; g += 2) {
+    const float2 p = sm.M[sme][g * UT + i];
+    float2 q = make_float2(0.f, 0.f);
+    if (g + 1 < 64 / UT) q = sm.M[sme][(g + 1) * UT + i];
+    // (p0 + p1) + (p2 + p3)
+    if (g == 1) m = make_float2(m.x + p.x, m.y + p.y);
+    if (g + 1 < 64 / UT) {
+      const float2 t = sm.M[sme][(g + 2) * UT + i];
+      m = make_float2(m.x + (q.x + t.x), m.y + (q.y + t.y));
+      break;
+    }
+  }
+  solve_slot<UT, KEEP, SM::NS>(r, sm.A, sme, i, m, rho, U);
 }
 
 // One refinement step for the systems of a round: every group's z goes to
 // LDS, the residual pass streams the systems' rows again and each group
 // solves A dz = H^H (y - H z) - rho z as dz = X^H (X r) with X = L^{-1}
-// (A^{-1} = X^H X): local_solve left X in the slot (row u = conj of column u)
-// during the pass, t = X r is read along rows of X and dz = X^H t uses the
-// columns.
+// (A^{-1} = X^H X): local_solve left X in the slot during the pass, t = X r
+// is read along rows of X and dz = X^H t uses the columns.
 template <int UT, class SM, class Rho, class Seg>
 __device__ __forceinline__ void refine_round(LocalSolve<UT> &r, SM &sm, int nvalid, int U,
                                              Rho rhof, Seg seg, bool live) {
   const int lane = lane_id();
   const int sme = slot_of<SM>(lane / UT), i = lane % UT;
-  __syncthreads();
+  wave_sync();
   sm.M[sme][i] = r.z;
-  __syncthreads();
+  wave_sync();
   residual_stream<UT>(
       nvalid, U, seg, [&](int s) { return sm.M[s][lane % UT]; },
       [&](int s, float2 n) {
         const float2 zc = sm.M[s][lane % UT];
         const float rho = rhof(s);
-        if (lane < UT) sm.F[s][lane] = make_float4(n.x - rho * zc.x, n.y - rho * zc.y, 0.f, 0.f);
+        if (lane < UT) sm.R[s][lane] = make_float2(n.x - rho * zc.x, n.y - rho * zc.y);
       });
-  __syncthreads();
-  // t_j = sum_u X_ju r_u at lane j
+  wave_sync();
+  float2 *As = sm.A + sme * kSlot<UT>;
+  const int h = UT == 32 ? i >> 4 : 0, ii = i & 15;
+  // t_j = sum_u X_ju r_u at lane j; the slot holds conj(X_ju) in row u
   float tx = 0.f, ty = 0.f;
-#pragma unroll
-  for (int u = 0; u < UT; ++u) {
-    const float2 x = lds_el<UT>(sm.A[sme], u, i);  // conj(X_iu)
-    const float4 rv = sm.F[sme][u];
+  auto add = [&](float2 x, float2 rv) {
     tx = fmaf(x.x, rv.x, fmaf(x.y, rv.y, tx));
     ty = fmaf(x.x, rv.y, fmaf(-x.y, rv.x, ty));
+  };
+#pragma unroll
+  for (int u = 0; u < 16; ++u) add(blk_el(As, h, u, ii), sm.R[sme][u]);
+  if (UT == 32 && h) {
+#pragma unroll
+    for (int u = 0; u < 16; ++u) add(blk_el(As, 2, u, ii), sm.R[sme][16 + u]);
   }
   Factor<UT> f;
 #pragma unroll
-  for (int k = 0; k < UT; ++k) {
-    const float2 x = lds_el<UT>(sm.A[sme], i, k);
+  for (int k = 0; k < 16; ++k) {
+    float2 x = blk_el(As, 0, ii, k);
+    if (h) x = make_float2(0.f, 0.f);
     f.x[k] = make_float2(x.x, -x.y);
+    if constexpr (UT == 32) {
+      x = blk_el(As, 1 + h, ii, k);
+      f.x[16 + k] = make_float2(x.x, -x.y);
+    }
   }
   const float2 dz = apply_xh<UT>(f, make_float2(tx, ty));
   if (live) {

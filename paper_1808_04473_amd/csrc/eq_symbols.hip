@@ -399,7 +399,7 @@ __device__ __forceinline__ void pd_sym_task(const FwdArgs &a, int w0, int nvalid
     r1 = a.B;
   };
   gram_mf_stream<UT, PREC>(nvalid, a.U, a.B, a.nsym, seg, [&](int s, const Acc<UT> &acc, const MAcc<UT> &m) {
-    store_gram<UT, PREC>(sm.A[s], acc, a.rho, a.U);
+    store_gram_shift<UT, PREC>(sm.A[s], acc, a.rho, a.U);
     store_msym<UT, PREC>(sm, s, m);
   });
   for (int s = nvalid; s < SM::NS; ++s) store_identity<UT>(sm.A[s]);
@@ -522,7 +522,7 @@ __device__ __forceinline__ void fd_sym_task(const FwdArgs &a, int w, SM &sm) {
       r1 = a.off[base + s + 1];
     };
     gram_mf_stream<UT, PREC>(nvalid, a.U, a.B, a.nsym, seg, [&](int s, const Acc<UT> &acc, const MAcc<UT> &m) {
-      store_gram<UT, PREC>(sm.A[s], acc, a.rho, a.U);
+      store_gram_shift<UT, PREC>(sm.A[s], acc, a.rho, a.U);
       store_msym<UT, PREC>(sm, s, m);
     });
     for (int s = nvalid; s < NSYS; ++s) store_identity<UT>(sm.A[s]);
@@ -647,7 +647,7 @@ __device__ __forceinline__ void pd_sym_lama_task(const FwdArgs &a, int w0, int n
     r1 = a.B;
   };
   gram_mf_stream<UT, PREC>(nvalid, a.U, a.B, a.nsym, seg, [&](int s, const Acc<UT> &acc, const MAcc<UT> &m) {
-    store_gram<UT, PREC>(sm.A[s], acc, 0.f, a.U);
+    store_gram_shift<UT, PREC>(sm.A[s], acc, 0.f, a.U);
     store_msym<UT, PREC>(sm, s, m);
   });
   for (int s = nvalid; s < SM::NS; ++s) store_identity<UT>(sm.A[s]);
@@ -704,7 +704,7 @@ __device__ __forceinline__ void fd_sym_lama_task(const FwdArgs &a, int w, SM &sm
       r1 = a.off[base + s + 1];
     };
     gram_mf_stream<UT, PREC>(nvalid, a.U, a.B, a.nsym, seg, [&](int s, const Acc<UT> &acc, const MAcc<UT> &m) {
-      store_gram<UT, PREC>(sm.A[s], acc, 0.f, a.U);
+      store_gram_shift<UT, PREC>(sm.A[s], acc, 0.f, a.U);
       store_msym<UT, PREC>(sm, s, m);
     });
     for (int s = nvalid; s < NSYS; ++s) store_identity<UT>(sm.A[s]);
