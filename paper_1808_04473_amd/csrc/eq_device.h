@@ -131,6 +131,12 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v;
 }
 
+// Sum of the lane and the one 32 lanes away; both receive it.
+__device__ __forceinline__ float xor32_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // Sum / max / any over an aligned group of UT lanes; all lanes get the result.
 template <int UT>
 __device__ __forceinline__ float gsum(float v) {
@@ -1245,7 +1251,7 @@ struct Elim {
 
 // Step J.  ZERO: v[J] is left as conj(X_Ju) in lane u (zero in lanes past J
 // of the same 16 rows), for callers that use X.
-template <int UT, int J, bool ZERO>
+template <int UT, int J, bool ZERO, bool RHS>
 __device__ __forceinline__ void elim_step(float2 (&v)[16], Elim &e, float rho, int U) {
   constexpr int j = J % 16, P = J - j;
   // the shift of A = G + rho I enters here: nothing else reads the diagonal
@@ -1257,30 +1263,30 @@ __device__ __forceinline__ void elim_step(float2 (&v)[16], Elim &e, float rho, i
   const bool me = lanes(lanes_ge<UT>(J) & ~lanes_ge<UT>(J + 1));
   float2 s = make_float2(v[j].x * inv, v[j].y * inv);
   if (me) s = make_float2(inv, 0.f);
-  const float2 t = make_float2(e.acc.x * inv, e.acc.y * inv);
-  float2 acc = e.acc;
   float d = e.d;
-  if (me) {
-    acc = make_float2(0.f, 0.f);
-    d = 0.f;
-  }
+  if (me) d = 0.f;
   e.d = fmaf(s.x, s.x, fmaf(s.y, s.y, d));
-  const BSrc bx = bsrc<UT>(s.x), by = bsrc<UT>(s.y), tx = bsrc<UT>(t.x), ty = bsrc<UT>(t.y);
-  // acc -= s t_J, the product rounded before it is subtracted (the running
-  // sum is rounded once a step: 5% less error in z than four FMACs on it).
-  // The s_nop also covers the columns that follow.
-  float px, py;
-  asm volatile("s_nop 4\n\t"
-               "v_mul_f32_dpp %0, %2, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-               "v_mul_f32_dpp %1, %2, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-               "v_fmac_f32_dpp %0, -%3, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-               "v_fmac_f32_dpp %1, %3, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf"
-               : "=&v"(px), "=&v"(py)
-               : "v"(bpick<J>(tx)), "v"(bpick<J>(ty)), "v"(s.x), "v"(s.y), "n"(j), "v"(bpick<J>(bx)),
-                 "v"(bpick<J>(by)));
-  acc.x -= px;
-  acc.y -= py;
-  e.acc = acc;
+  const BSrc bx = bsrc<UT>(s.x), by = bsrc<UT>(s.y);
+  if constexpr (RHS) {
+    const BSrc tx = bsrc<UT>(e.acc.x * inv), ty = bsrc<UT>(e.acc.y * inv);
+    if (me) e.acc = make_float2(0.f, 0.f);
+    // acc -= s t_J, the product rounded before it is subtracted (the running
+    // sum is rounded once a step: 5% less error in z than four FMACs on it).
+    // The s_nop also covers the columns that follow.
+    float px, py;
+    asm volatile("s_nop 4\n\t"
+                 "v_mul_f32_dpp %0, %2, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_mul_f32_dpp %1, %2, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %0, -%3, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %1, %3, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf"
+                 : "=&v"(px), "=&v"(py)
+                 : "v"(bpick<J>(tx)), "v"(bpick<J>(ty)), "v"(s.x), "v"(s.y), "n"(j), "v"(bpick<J>(bx)),
+                   "v"(bpick<J>(by)));
+    e.acc.x -= px;
+    e.acc.y -= py;
+  } else {
+    asm volatile("s_nop 4" : : "v"(bpick<J>(bx)), "v"(bpick<J>(by)));
+  }
   sfor<4>([&](auto G) {
     constexpr int g = G;
     constexpr int k0 = j + 1 > 4 * g ? j + 1 : 4 * g, n = 4 * g + 4 - k0;
@@ -1298,11 +1304,11 @@ __device__ __forceinline__ void elim_step(float2 (&v)[16], Elim &e, float rho, i
 
 // Steps J .. END-1 of those below U (wave-uniform).  The steps of padded users
 // are left out, so nothing reads their rows and columns.
-template <int UT, int J, int END, bool ZERO>
+template <int UT, int J, int END, bool ZERO, bool RHS>
 __device__ __forceinline__ void elim_steps(float2 (&v)[16], Elim &e, float rho, int U) {
-  elim_step<UT, J, ZERO>(v, e, rho, U);
+  elim_step<UT, J, ZERO, RHS>(v, e, rho, U);
   if constexpr (J + 1 < END) {
-    if (U > J + 1) elim_steps<UT, J + 1, END, ZERO>(v, e, rho, U);
+    if (U > J + 1) elim_steps<UT, J + 1, END, ZERO, RHS>(v, e, rho, U);
   }
 }
 
@@ -1365,7 +1371,8 @@ struct LocalSolve {
 // L^{-1}, is left in the slot: row u of blocks 0 and 1 (u < 16), or of block
 // 2, holds the rows 0..15 and 16..31 of column u (columns of padded users
 // are zero).
-template <int UT, bool KEEP, int NS>
+// Without RHS, m and z are not used.
+template <int UT, bool KEEP, int NS, bool RHS = true>
 __device__ __forceinline__ void solve_slot(LocalSolve<UT> &r, float2 *A, int slot, int i, float2 m, float rho, int U) {
   U = __builtin_amdgcn_readfirstlane(U);
   float2 *As = A + slot * kSlot<UT>;
@@ -1393,7 +1400,7 @@ __device__ __forceinline__ void solve_slot(LocalSolve<UT> &r, float2 *A, int slo
   e.d = 0.f;
   e.okm = ~0ull;
   e.npos = 0;
-  elim_steps<UT, 0, 16, KEEP || UT == 32>(v, e, rho, U);
+  elim_steps<UT, 0, 16, KEEP || UT == 32, RHS>(v, e, rho, U);
   if constexpr (UT == 32) {
     // conj(X11) by columns from the first 16 lanes, L21 by rows from the others
     sfor<16>([&](auto K) {
@@ -1408,7 +1415,7 @@ __device__ __forceinline__ void solve_slot(LocalSolve<UT> &r, float2 *A, int slo
       const float2 a = blk_el(As, 1 + h, ii, k);
       v[k] = lanes(lanes_ge<UT>(16 + k) | ~lanes_ge<UT>(16)) ? a : make_float2(0.f, 0.f);
     });
-    elim_steps<UT, 16, 32, KEEP>(v, e, rho, U);
+    elim_steps<UT, 16, 32, KEEP, RHS>(v, e, rho, U);
   }
   if constexpr (KEEP) {
     sfor<16>([&](auto K) {

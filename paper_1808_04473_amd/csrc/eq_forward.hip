@@ -106,10 +106,7 @@ __device__ __forceinline__ float group_sum(float v, int gw) {
     const BSrc r = bsrc<32>(v);
     v = r.lo + r.hi;
   }
-  if (gw > (UT == 16 ? 2 : 1)) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  }
+  if (gw > (UT == 16 ? 2 : 1)) v = xor32_sum(v);
   return v;
 }
 

@@ -3,57 +3,79 @@
 // The OFDM symbols of one coherence interval share the channel, so the Gram
 // matrix of a subcarrier (PD) or cluster (FD) and its factor are formed once
 // and applied to every symbol; only the matched filter is formed per symbol.
-// The matched filters of a tile of up to UT symbols, H_c^H [y_1 .. y_S], are a
-// second MFMA product in the same pass over H: lane (g, j) of the streaming
-// layout loads rows 8g .. 8g+7 of receive vector j, which is the B operand
-// for the same K (row) index as the lane's H value is for the Gram.  H and
-// the receive vectors are each read from HBM once per tile.
+// The matched filters of a tile of up to 16 symbols, H_c^H [y_1 .. y_S], are a
+// second MFMA product in the same pass over H, and H and the receive vectors
+// are each read from HBM once per tile.
 //
-// After the pass a lane group factors its system and forms X = L^{-1}.
-// With 16 users the estimates of all symbols, Z = X^H (X M), are two
-// complex 16 x 16 x 16 products on FP32 MFMA per system; with 32 users each
-// lane group computes, per symbol, t = X m_s (rows of X read back from LDS)
-// and z_s = X^H t (columns of X in registers).  FD weights every cluster's
-// estimates with the weights of Lemma 1 (or given ones), which do not depend
-// on the symbol, and sums them over the clusters in cluster order.
+// Tile layout.  Everything runs in 16 x 16 tiles: NT = 1 or 2 tiles of users
+// (U <= 16, U <= 32) and one of symbols.  Lane (g, c) = (lane / 16, lane % 16)
+// loads rows of its group for user c (and 16 + c) of H and for symbol c: the
+// A and B operands of the products over rows.  Of the Gram matrix only the
+// blocks (0, 0), (1, 0) and (1, 1) are formed (seven real FP32 products at 32
+// users where full 32 x 32 tiles take eight, and twice the symbols).  Results
+// come in MFMA accumulator layout, lane (kk, c) holding rows 4 kk + r of
+// column c.  A result in that layout is the B operand of a next product whose
+// k index runs as (register, lane group), so matched filters and estimates go
+// from product to product in registers.
 //
-// LAMA (Algorithm 1) runs on the same pass, the iteration once per vector
-// with the system's Gram row held in registers (eq_symbols_lama_kernel).
+// L-MMSE / ZF: each lane group factors its system (solve_slot) and leaves X =
+// L^{-1} in LDS; the estimates of all symbols are Z = X^H (X M), two products
+// per system.  MRC and LAMA (Algorithm 1) need no factor and work on one
+// system at a time as its stream ends, for all symbols at once.
 //
-// Forms: FP32 MFMA (the matched filter as three real products), and
-// split-BF16 MFMA (three products per real product) without refinement; the refining forms are not offered for several
-// symbols.  Ill-conditioned systems go to the FP64 re-solve queue as in the
-// single-vector kernels; the re-solve recomputes every symbol of the tile.
+// FD weights every cluster's estimates with the weights of Lemma 1 (or given
+// ones) and sums them over the clusters: each wave of the workgroup takes a
+// share of them in cluster order, and the waves' sums are added in order.
+//
+// Forms: FP32 MFMA and split-BF16 MFMA (three products per real product)
+// without refinement.  Ill-conditioned systems go to the FP64 re-solve queue
+// as in the single-vector kernels; the re-solve recomputes every symbol of
+// the tile.
 #include "eq_lama.h"
 
 namespace dbpeq {
 
+constexpr int kSymTile = 16;  // symbols per launch
+
 // ---------------------------------------------------------------- streaming
-// One row block: H as in the single-vector stream, and rows 8g .. 8g+7 of
-// receive vector j = lane % UT of the tile.
-struct SymSlot {
-  float2 h[8];
+// Rows per lane group and row block, and row e of group g within the block
+// (the products sum over rows: any order will do that H and Y share).  At 16
+// users the rows go to the groups in pairs: a 16-byte load of Y then covers
+// two rows, and the four groups 64 consecutive bytes of a vector (14 vectors,
+// PD 38,400 / 4 subcarriers of B = 256, U = 16: 113 against 121 us with eight
+// rows per group; at 32 users, with half the rows, it was 5% slower).
+template <int NT>
+constexpr int kRows = 8 / NT;
+template <int NT>
+__device__ __forceinline__ constexpr int tile_row(int e, int g) {
+  return NT == 1 ? 8 * (e / 2) + 2 * g + e % 2 : 4 * g + e;
+}
+
+struct TileSlot {
+  float2 h[8];  // row e of the group: h[e], or h[2 e] and h[2 e + 1] (users c, 16 + c)
   float2 y[8];
   int s;
-  int nv;  // rows of this lane's group, from its first, inside the system
+  int nv;     // rows from the group's first to the end of the system
+  bool full;  // the whole block is inside the system
   bool last;
 };
 
-template <int UT>
-struct SymLaneOff {
-  unsigned h;  // as LaneOff::h
-  unsigned y;  // (j B + 8 g) * 8 for symbols j < nsym, else out of range
-  int g;
+template <int NT>
+struct TileOff {
+  unsigned h, h1;  // users c and 16 + c of the group's first row, or out of range
+  unsigned y;      // the same row of symbol c < nsym, else out of range
+  int row;         // the group's first row within a block
 };
 
-template <int UT>
-__device__ __forceinline__ SymLaneOff<UT> sym_lane_offsets(int U, int B, int nsym) {
+template <int NT>
+__device__ __forceinline__ TileOff<NT> tile_offsets(int U, int B, int nsym) {
   const int lane = lane_id();
-  const int col = lane % UT, g = lane / UT;
-  SymLaneOff<UT> o;
-  o.h = col < U ? (unsigned)((slot_row(0, g) * U + col) * 8) : kOutOfRange;
-  o.y = col < nsym ? (unsigned)(((unsigned)col * (unsigned)B + (unsigned)slot_row(0, g)) * 8u) : kOutOfRange;
-  o.g = g;
+  const int c = lane % 16, row = tile_row<NT>(0, lane / 16);
+  TileOff<NT> o;
+  o.h = c < U ? (unsigned)((row * U + c) * 8) : kOutOfRange;
+  o.h1 = 16 + c < U ? (unsigned)((row * U + 16 + c) * 8) : kOutOfRange;
+  o.y = c < nsym ? (unsigned)(((unsigned)c * (unsigned)B + (unsigned)row) * 8u) : kOutOfRange;
+  o.row = row;
   return o;
 }
 
@@ -61,11 +83,15 @@ __device__ __forceinline__ SymLaneOff<UT> sym_lane_offsets(int U, int B, int nsy
 // tile's receive vectors (vector stride B, Yw = vector 0 of the tile).  The Y
 // descriptor spans from row r0 of the first vector to row r1 of the last one:
 // rows past r1 of the other vectors are in range and are masked by nv when
-// the block is consumed.
-template <int UT>
-__device__ __forceinline__ void load_sym_slot(SymSlot &b, const SymLaneOff<UT> &lo, const float2 *__restrict__ Hw,
-                                              const float2 *__restrict__ Yw, int U, int B, int nsym, int rb,
-                                              int r0, int r1, bool live) {
+// the block is consumed.  Each load is wholly inside or wholly outside its
+// descriptor (the 16-byte loads are those of full blocks).  The loads of Y
+// use the default policy: they share cache lines (with the nontemporal one
+// the lines were fetched again, 22-28% more bytes than the algorithm reads).
+template <int NT>
+__device__ __forceinline__ void load_tile_slot(TileSlot &b, const TileOff<NT> &lo, const float2 *__restrict__ Hw,
+                                               const float2 *__restrict__ Yw, int U, int B, int nsym, int rb,
+                                               int r0, int r1, bool live) {
+  constexpr int E = kRows<NT>;
   const int nrow = live ? r1 - r0 : 0;
   const int ylen = live ? ((nsym - 1) * B + (r1 - r0)) * 8 : 0;
   const __amdgpu_buffer_rsrc_t rh =
@@ -74,121 +100,216 @@ __device__ __forceinline__ void load_sym_slot(SymSlot &b, const SymLaneOff<UT> &
   const unsigned rowb = (unsigned)((rb - r0) * U * 8);
   const unsigned step = (unsigned)(U * 8);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) b.h[e] = buf_ld2<kLoadLast>(rh, lo.h + rowb + e * step);
-  // one 8-byte load per row: a load is then either wholly inside the
-  // descriptor's range or wholly outside it.  The eight loads of a lane read
-  // one 64-byte span, so consecutive loads share cache lines: these use the
-  // default policy (with the nontemporal one the lines were fetched from
-  // HBM again, 22-28% more bytes than the algorithm reads).
+  for (int e = 0; e < E; ++e) {
+    if constexpr (NT == 1) {
+      b.h[e] = buf_ld2<kLoadLast>(rh, lo.h + rowb + tile_row<NT>(e, 0) * step);
+    } else {
+      b.h[2 * e] = buf_ld2<kLoadLast>(rh, lo.h + rowb + tile_row<NT>(e, 0) * step);
+      b.h[2 * e + 1] = buf_ld2<kLoadLast>(rh, lo.h1 + rowb + tile_row<NT>(e, 0) * step);
+    }
+  }
   const unsigned yb = lo.y + (unsigned)((rb - r0) * 8);
+  b.full = live && rb + 4 * E <= r1;
+  if (NT == 1 && b.full) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) b.y[e] = buf_ld2<kLoadKeep>(ry, yb + 8u * e);
-  b.nv = r1 - (rb + slot_row(0, lo.g));
+    for (int e = 0; e < E; e += 2) {
+      const f4 v = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(ry, yb + 8u * tile_row<NT>(e, 0), 0, kLoadKeep));
+      b.y[e] = make_float2(v.x, v.y);
+      b.y[e + 1] = make_float2(v.z, v.w);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < E; ++e) b.y[e] = buf_ld2<kLoadKeep>(ry, yb + 8u * tile_row<NT>(e, 0));
+  }
+  b.nv = r1 - (rb + lo.row);
 }
 
-// Matched-filter accumulators, element (u, j) at the position acc_pos gives
-// for (i, j).  FP32 forms the complex product H^H Y with three real MFMA
-// products (Gauss):
+// ---------------------------------------------------------------- Gram and matched filters
+// Accumulators of the Gram blocks 0 = (0, 0), 1 = (1, 0), 2 = (1, 1).  FP32:
+// rr = P = (Hr + Hi)^T (Hr + Hi) and ri = Hr^T Hi; block 1 also ir = Hi^T Hr
+// (the diagonal blocks take it from the transpose of ri).  Split BF16: rr, ii
+// and ri, block 1 also ir.
+template <int NT>
+struct TileAcc {
+  f4 rr[2 * NT - 1], ri[2 * NT - 1], ii[2 * NT - 1], ir;
+};
+// Matched filters.  FP32 forms H^H Y with three real products (Gauss):
 //   k1 = (Hr - Hi)^T Yr,  k2 = Hr^T (Yi - Yr),  k3 = Hi^T (Yr + Yi),
-//   Re M = Hr^T Yr + Hi^T Yi = k1 + k3,   Im M = Hr^T Yi - Hi^T Yr = k1 + k2;
+//   Re M = k1 + k3,   Im M = k1 + k2;
 // the split-BF16 form accumulates Re M in k1 and Im M in k2 directly.
-template <int UT> struct MAcc;
-template <> struct MAcc<16> { f4 k1, k2, k3; };
-template <> struct MAcc<32> { f16v k1, k2, k3; };
+template <int NT>
+struct TileMf {
+  f4 k1[NT], k2[NT], k3[NT];
+};
 
-template <int UT>
-__device__ __forceinline__ void macc_zero(MAcc<UT> &m) {
-  constexpr int NR = UT == 16 ? 4 : 16;
+template <int NT>
+__device__ __forceinline__ void tile_zero(TileAcc<NT> &a, TileMf<NT> &m) {
+  const f4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int r = 0; r < NR; ++r) { m.k1[r] = 0.f; m.k2[r] = 0.f; m.k3[r] = 0.f; }
+  for (int b = 0; b < 2 * NT - 1; ++b) a.rr[b] = a.ri[b] = a.ii[b] = z;
+  a.ir = z;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) m.k1[t] = m.k2[t] = m.k3[t] = z;
 }
 
-template <int PREC, int UT>
-__device__ __forceinline__ float2 macc_value(const MAcc<UT> &m, int r) {
-  if constexpr (PREC == PREC_FP32) return make_float2(m.k1[r] + m.k3[r], m.k1[r] + m.k2[r]);
-  else return make_float2(m.k1[r], m.k2[r]);
+// BF16 operands of one row block: 8 rows per lane at NT = 1 (K = 32), 4 at
+// NT = 2 (K = 16).
+typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
+typedef short s4 __attribute__((ext_vector_type(4)));
+template <int NT>
+using BfVec = std::conditional_t<NT == 1, bf8, bf4>;
+__device__ __forceinline__ f4 mma16(bf4 a, bf4 b, f4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s4, a), __builtin_bit_cast(s4, b), c, 0, 0, 0);
 }
 
-// acc += the block's Gram products (as gram_blk: P and ri in FP32, the
-// split products otherwise); m += H^H Y of the block.
-template <int UT, int PREC>
-__device__ __forceinline__ void gram_mf_blk(const SymSlot &sl, Acc<UT> &acc, MAcc<UT> &m) {
-  float2 y[8];
+template <int NT>
+struct Split {
+  BfVec<NT> h, l;
+};
+// acc += a b with both operands split: hi lo + lo hi + hi hi
+template <int NT>
+__device__ __forceinline__ f4 mma_split(const Split<NT> &a, const Split<NT> &b, f4 c) {
+  c = mma16(a.h, b.l, c);
+  c = mma16(a.l, b.h, c);
+  return mma16(a.h, b.h, c);
+}
+
+template <int NT, int PREC>
+__device__ __forceinline__ void gram_mf_tile(TileSlot &sl, TileAcc<NT> &acc, TileMf<NT> &m) {
+  constexpr int E = kRows<NT>;
+  if (!sl.full) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) y[e] = e < sl.nv ? sl.y[e] : make_float2(0.f, 0.f);
+    for (int e = 0; e < E; ++e)
+      if (tile_row<NT>(e, 0) >= sl.nv) sl.y[e] = make_float2(0.f, 0.f);
+  }
   if constexpr (PREC == PREC_FP32) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float2 h = sl.h[e];
-      const float sum = h.x + h.y;
-      acc.rr = mma32(sum, sum, acc.rr);
-      m.k1 = mma32(h.x - h.y, y[e].x, m.k1);
-      acc.ri = mma32(h.x, h.y, acc.ri);
-      m.k2 = mma32(h.x, y[e].y - y[e].x, m.k2);
-      m.k3 = mma32(h.y, y[e].x + y[e].y, m.k3);
+    for (int e = 0; e < E; ++e) {
+      const float2 y = sl.y[e];
+      const float ydif = y.y - y.x, ysum = y.x + y.y;
+      float sum[NT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const float2 h = sl.h[NT * e + t];
+        sum[t] = h.x + h.y;
+        acc.rr[2 * t] = mma32(sum[t], sum[t], acc.rr[2 * t]);
+        m.k1[t] = mma32(h.x - h.y, y.x, m.k1[t]);
+        acc.ri[2 * t] = mma32(h.x, h.y, acc.ri[2 * t]);
+        m.k2[t] = mma32(h.x, ydif, m.k2[t]);
+        m.k3[t] = mma32(h.y, ysum, m.k3[t]);
+      }
+      if constexpr (NT == 2) {
+        const float2 h0 = sl.h[2 * e], h1 = sl.h[2 * e + 1];
+        acc.rr[1] = mma32(sum[1], sum[0], acc.rr[1]);
+        acc.ri[1] = mma32(h1.x, h0.y, acc.ri[1]);
+        acc.ir = mma32(h1.y, h0.x, acc.ir);
+      }
     }
   } else {
     static_assert(PREC == PREC_BF16X3_NR, "one-pass forms only");
-    bf8 rh, rl, ih, il, yrh, yrl, yih, yil, nrh, nrl;
+    Split<NT> hr[NT], hi[NT], yr, yi, ny;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float2 h = sl.h[e];
-      rh[e] = (__bf16)h.x;
-      rl[e] = (__bf16)(h.x - (float)rh[e]);
-      ih[e] = (__bf16)h.y;
-      il[e] = (__bf16)(h.y - (float)ih[e]);
-      yrh[e] = (__bf16)y[e].x;
-      yrl[e] = (__bf16)(y[e].x - (float)yrh[e]);
-      yih[e] = (__bf16)y[e].y;
-      yil[e] = (__bf16)(y[e].y - (float)yih[e]);
+    for (int e = 0; e < E; ++e) {
+      const float2 y = sl.y[e];
+      yr.h[e] = (__bf16)y.x;
+      yr.l[e] = (__bf16)(y.x - (float)yr.h[e]);
+      yi.h[e] = (__bf16)y.y;
+      yi.l[e] = (__bf16)(y.y - (float)yi.h[e]);
       // round-to-nearest-even is symmetric: the split of -yr is the negated split
-      nrh[e] = -yrh[e];
-      nrl[e] = -yrl[e];
+      ny.h[e] = -yr.h[e];
+      ny.l[e] = -yr.l[e];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const float2 h = sl.h[NT * e + t];
+        hr[t].h[e] = (__bf16)h.x;
+        hr[t].l[e] = (__bf16)(h.x - (float)hr[t].h[e]);
+        hi[t].h[e] = (__bf16)h.y;
+        hi[t].l[e] = (__bf16)(h.y - (float)hi[t].h[e]);
+      }
     }
-    acc.rr = mma16(rh, rl, acc.rr);
-    m.k1 = mma16(rh, yrl, m.k1);
-    acc.ri = mma16(rh, il, acc.ri);
-    m.k2 = mma16(rh, yil, m.k2);
-    acc.ii = mma16(ih, il, acc.ii);
-    m.k1 = mma16(rl, yrh, m.k1);
-    acc.rr = mma16(rl, rh, acc.rr);
-    m.k2 = mma16(rl, yih, m.k2);
-    acc.ri = mma16(rl, ih, acc.ri);
-    m.k1 = mma16(rh, yrh, m.k1);
-    acc.ii = mma16(il, ih, acc.ii);
-    m.k2 = mma16(rh, yih, m.k2);
-    acc.rr = mma16(rh, rh, acc.rr);
-    m.k1 = mma16(ih, yil, m.k1);
-    acc.ri = mma16(rh, ih, acc.ri);
-    m.k2 = mma16(ih, nrl, m.k2);
-    acc.ii = mma16(ih, ih, acc.ii);
-    m.k1 = mma16(il, yih, m.k1);
-    m.k2 = mma16(il, nrh, m.k2);
-    m.k1 = mma16(ih, yih, m.k1);
-    m.k2 = mma16(ih, nrh, m.k2);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      acc.rr[2 * t] = mma_split<NT>(hr[t], hr[t], acc.rr[2 * t]);
+      m.k1[t] = mma_split<NT>(hr[t], yr, m.k1[t]);
+      acc.ri[2 * t] = mma_split<NT>(hr[t], hi[t], acc.ri[2 * t]);
+      m.k2[t] = mma_split<NT>(hr[t], yi, m.k2[t]);
+      acc.ii[2 * t] = mma_split<NT>(hi[t], hi[t], acc.ii[2 * t]);
+      m.k1[t] = mma_split<NT>(hi[t], yi, m.k1[t]);
+      m.k2[t] = mma_split<NT>(hi[t], ny, m.k2[t]);
+    }
+    if constexpr (NT == 2) {
+      acc.rr[1] = mma_split<NT>(hr[1], hr[0], acc.rr[1]);
+      acc.ri[1] = mma_split<NT>(hr[1], hi[0], acc.ri[1]);
+      acc.ii[1] = mma_split<NT>(hi[1], hi[0], acc.ii[1]);
+      acc.ir = mma_split<NT>(hi[1], hr[0], acc.ir);
+    }
   }
 }
 
-// Gram + matched filters of systems 0..ns-1 (seg(s, Hw, Yw, r0, r1) as in
-// stream_blocks, Yw = vector 0 of the tile); done(s, acc, m) follows the last
-// block of system s while the next blocks' loads are in flight.
-template <int UT, int PREC, class Seg, class Done>
+// Complex tiles in accumulator layout (register r of lane (kk, c): row
+// 4 kk + r, column c).
+template <int N>
+struct Tiles {
+  f4 re[N], im[N];
+};
+
+// The Gram blocks; the transposes of the diagonal ones go through 256 floats
+// of LDS.
+template <int NT, int PREC>
+__device__ __forceinline__ void tile_gram(float *scratch, const TileAcc<NT> &a, Tiles<2 * NT - 1> &G) {
+  const int lane = lane_id();
+  const int kk = lane / 16, c = lane % 16;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int b = 2 * t;
+    wave_sync();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) scratch[16 * (4 * kk + r) + (c ^ (4 * kk + r))] = a.ri[b][r];
+    wave_sync();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float rij = scratch[16 * c + ((4 * kk + r) ^ c)];
+      G.im[b][r] = a.ri[b][r] - rij;
+      G.re[b][r] = PREC == PREC_FP32 ? a.rr[b][r] - a.ri[b][r] - rij : a.rr[b][r] + a.ii[b][r];
+    }
+  }
+  if constexpr (NT == 2) {
+    G.im[1] = a.ri[1] - a.ir;
+    G.re[1] = PREC == PREC_FP32 ? a.rr[1] - a.ri[1] - a.ir : a.rr[1] + a.ii[1];
+  }
+}
+
+template <int NT, int PREC>
+__device__ __forceinline__ void tile_mf(const TileMf<NT> &m, Tiles<NT> &M) {
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    M.re[t] = PREC == PREC_FP32 ? m.k1[t] + m.k3[t] : m.k1[t];
+    M.im[t] = PREC == PREC_FP32 ? m.k1[t] + m.k2[t] : m.k2[t];
+  }
+}
+
+// Gram + matched filters of systems 0..ns-1 (seg(s, Hw, Yw, r0, r1), Yw =
+// vector 0 of the tile); done(s, acc, m) follows the last block of system s
+// while the next block's loads are in flight.  Two slots (a block is 4 to
+// 7.5 KB): with four nothing was faster and LAMA lost a wave (104 against
+// 98 us), and one stream over all rounds of an FD wave, which loads the next
+// round's first rows during a solve, was 2-8% slower.
+template <int NT, int PREC, class Seg, class Done>
 __device__ __forceinline__ void gram_mf_stream(int ns, int U, int B, int nsym, Seg seg, Done done) {
-  constexpr int RPB = 8 * (64 / UT);
-  Acc<UT> acc;
-  acc_zero<UT>(acc);
-  MAcc<UT> m;
-  macc_zero<UT>(m);
-  const SymLaneOff<UT> lo = sym_lane_offsets<UT>(U, B, nsym);
+  constexpr int RPB = 4 * kRows<NT>;
+  TileAcc<NT> acc;
+  TileMf<NT> m;
+  tile_zero<NT>(acc, m);
+  const TileOff<NT> lo = tile_offsets<NT>(U, B, nsym);
   SysRef cur;
   seg(0, cur.Hw, cur.yw, cur.r0, cur.r1);
   cur.s = 0;
   int next = 1;
   int crb = cur.r0;
   bool more = true;
-  auto issue = [&](SymSlot &sl) -> bool {
+  auto issue = [&](TileSlot &sl) -> bool {
     const bool valid = more;
-    load_sym_slot<UT>(sl, lo, cur.Hw, cur.yw, U, B, nsym, crb, cur.r0, cur.r1, valid);
+    load_tile_slot<NT>(sl, lo, cur.Hw, cur.yw, U, B, nsym, crb, cur.r0, cur.r1, valid);
     sl.s = cur.s;
     sl.last = crb + RPB >= cur.r1;
     if (valid) {
@@ -204,180 +325,109 @@ __device__ __forceinline__ void gram_mf_stream(int ns, int U, int B, int nsym, S
     }
     return valid;
   };
-  auto body = [&](const SymSlot &b) { gram_mf_blk<UT, PREC>(b, acc, m); };
-  auto fin = [&](const SymSlot &b) {
-    done(b.s, acc, m);
-    acc_zero<UT>(acc);
-    macc_zero<UT>(m);
+  auto consume = [&](TileSlot &b) {
+    gram_mf_tile<NT, PREC>(b, acc, m);
+    if (b.last) {
+      done(b.s, acc, m);
+      tile_zero<NT>(acc, m);
+    }
   };
-  stream_ring3<SymSlot>(issue, body, fin);
+  TileSlot sa, sb;
+  issue(sa);
+  while (true) {
+    const bool vb = issue(sb);
+    __builtin_amdgcn_sched_barrier(0);
+    consume(sa);
+    if (!vb) break;
+    const bool va = issue(sa);
+    __builtin_amdgcn_sched_barrier(0);
+    consume(sb);
+    if (!va) break;
+  }
 }
 
-// ---------------------------------------------------------------- LDS staging
-// NS matrix slots: A (G + rho I, then X), the matched filters of the tile
-// (rows = symbols, padded by two entries so the MFMA-layout stores hit
-// distinct banks, slots offset by 8 banks so the groups' broadcast reads do
-// too), and per-group fusion terms (FD).
-template <int UT, int NSLOT>
-struct SymSmem {
-  static constexpr int NSYS = 64 / UT;
-  static constexpr int NS = NSLOT;
-  static constexpr int MROW = UT + 2;
-  static constexpr int MSLOT = UT * MROW + 4;
-  float2 A[NS][UT][UT];
-  float2 Mv[NS * MSLOT];
-  float2 F[NS][UT];
-  __device__ __forceinline__ float2 &m(int slot, int s, int u) { return Mv[slot * MSLOT + s * MROW + u]; }
+// Sum over the four lane groups, lane by lane of a group.
+__device__ __forceinline__ float groups_sum(float v) {
+  const BSrc r = bsrc<32>(v);
+  return xor32_sum(r.lo + r.hi);
+}
+
+// ---------------------------------------------------------------- outputs
+// FD sums in accumulator layout: weighted estimates, and weights (optimal:
+// the fused variance is 1 / tk) or nu^2 sigma2_c (given weights: the fused
+// variance itself).
+template <int NT>
+struct FuseSum {
+  Tiles<NT> z;
+  f4 tk[NT];
 };
 
-template <int UT, int PREC, class SM>
-__device__ __forceinline__ void store_msym(SM &sm, int slot, const MAcc<UT> &m) {
-  constexpr int NR = UT == 16 ? 4 : 16;
+template <int NT>
+__device__ __forceinline__ void fuse_zero(FuseSum<NT> &f) {
+  const f4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < NT; ++t) f.z.re[t] = f.z.im[t] = f.tk[t] = z;
+}
+
+// Adds the waves' sums in wave order; part(q) is 12 NT * 64 floats of LDS of
+// wave q.  Returns true in the wave that holds the result.
+template <int NT, int NW, class Part>
+__device__ __forceinline__ bool fuse_waves(FuseSum<NT> &f, int wv, Part part) {
+  if constexpr (NW == 1) {
+    return true;
+  } else {
+    const int lane = lane_id();
+    float *o = part(wv);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        o[(12 * t + r) * 64 + lane] = f.z.re[t][r];
+        o[(12 * t + 4 + r) * 64 + lane] = f.z.im[t][r];
+        o[(12 * t + 8 + r) * 64 + lane] = f.tk[t][r];
+      }
+    __syncthreads();
+    if (wv != 0) return false;
+    fuse_zero<NT>(f);
+    for (int q = 0; q < NW; ++q) {
+      const float *p = part(q);
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          f.z.re[t][r] += p[(12 * t + r) * 64 + lane];
+          f.z.im[t][r] += p[(12 * t + 4 + r) * 64 + lane];
+          f.tk[t][r] += p[(12 * t + 8 + r) * 64 + lane];
+        }
+    }
+    return true;
+  }
+}
+
+// Writes the fused estimates of subcarrier w, and sigma2 as [W][U] or (PERSYM)
+// [W][S][U].
+template <int NT, bool PERSYM>
+__device__ __forceinline__ void fuse_write(const FwdArgs &a, int w, const FuseSum<NT> &f) {
   const int lane = lane_id();
-  sfor<NR>([&](auto R) {
-    constexpr int r = R;
-    int i, j;
-    acc_pos<UT>(lane, r, i, j);
-    sm.m(slot, j, i) = macc_value<PREC>(m, r);
-  });
-}
-
-// ---------------------------------------------------------------- solve
-template <int UT>
-struct SymSolve {
-  Factor<UT> f;
-  float2 xr[UT];  // row i of X (lane i; 32-lane groups only)
-  float d;        // [A^{-1}]_ii
-  float norm1;
-  int fail;
-  bool bad;
-};
-
-// Loads row i of the slot's A, factors it, forms X = L^{-1} (columns in
-// f.x) and parks X in the slot (row u holds column u); 32-lane groups then
-// read row i of X back.
-template <int UT, class SM>
-__device__ __forceinline__ void sym_factor(SymSolve<UT> &r, SM &sm, int slot, int i, int U) {
-  float rowsum = 0.f;
+  const int kk = lane / 16, c = lane % 16;
+  const bool user_nu = a.nu != nullptr;
+  const size_t ob = (size_t)w * a.zsw + (size_t)c * a.U;
 #pragma unroll
-  for (int k = 0; k < UT; ++k) {
-    r.f.a[k] = lds_el<UT>(sm.A[slot], i, k);
-    rowsum = abs_row_acc(rowsum, r.f.a[k]);
-  }
-  r.bad = gany<UT>(!isfinite(rowsum));
-  r.norm1 = gmax<UT>(i < U ? rowsum * (1.f / kRowScale) : 0.f);
-  // with a slot per system, the 32 x 32 factor and inverse run their two
-  // block products on MFMA through the slots (read above, free until X is
-  // parked)
-  float2 *split = nullptr;
-  if constexpr (UT == 32 && SM::NS == SM::NSYS) split = &sm.A[0][0][0];
-  r.fail = factor_inverse<UT>(r.f, i, SM::NS < SM::NSYS ? sm.A[slot] : nullptr, split);
-  r.d = inv_diag<UT>(r.f);
-  __syncthreads();
-  // row u of the slot holds column u of X: lds_el(A, u, k) = X_ku
+  for (int t = 0; t < NT; ++t)
 #pragma unroll
-  for (int k = 0; k < UT; ++k) lds_el<UT>(sm.A[slot], i, k) = r.f.x[k];
-  __syncthreads();
-  if constexpr (UT == 32) {
-#pragma unroll
-    for (int u = 0; u < UT; ++u) r.xr[u] = lds_el<UT>(sm.A[slot], u, i);
-  }
-}
-
-// 16 x 16 systems: Z = X^H (X M) for the slot's system and the tile's
-// symbols on FP32 MFMA (16x16x4), the whole wave on one system.  Each complex
-// product takes three real products (Gauss).  X comes from the slot (row u
-// holds column u of X), M from its matched-filter rows, which T = X M then
-// replaces.  On return lane (kk, c) = (lane / 16, lane % 16) holds
-// Z[4 kk + r][c] in (zr[r], zi[r]), r = 0..3: four users of symbol c.
-template <class SM>
-__device__ __forceinline__ void sym_mfma16(SM &sm, int slot, f4 &zr, f4 &zi) {
-  const int lane = lane_id();
-  const int kk = lane >> 4, c = lane & 15;
-  f4 k1, k2, k3;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) { k1[r] = 0.f; k2[r] = 0.f; k3[r] = 0.f; }
-  // T = X M: operand A[c][u] = X_cu, B[u][c] = M[u][c] (u = 4q + kk);
-  //   Re T = k1 - k3, Im T = k1 + k2 with k1 = (Xr + Xi) Mr,
-  //   k2 = Xr (Mi - Mr), k3 = Xi (Mr + Mi)
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int u = 4 * q + kk;
-    const float2 x = lds_el<16>(sm.A[slot], u, c);
-    const float2 mv = sm.m(slot, c, u);
-    k1 = mma32(x.x + x.y, mv.x, k1);
-    k2 = mma32(x.x, mv.y - mv.x, k2);
-    k3 = mma32(x.y, mv.x + mv.y, k3);
-  }
-  // T replaces M (the wave's LDS accesses are performed in order, so every
-  // read of M above precedes these writes)
-#pragma unroll
-  for (int r = 0; r < 4; ++r) sm.m(slot, c, 4 * kk + r) = make_float2(k1[r] - k3[r], k1[r] + k2[r]);
-  __syncthreads();
-#pragma unroll
-  for (int r = 0; r < 4; ++r) { k1[r] = 0.f; k2[r] = 0.f; k3[r] = 0.f; }
-  // Z = X^H T: operand A[c][i] = conj(X_ic), B[i][c] = T[i][c] (i = 4q + kk);
-  //   Re Z = k1 + k3, Im Z = k1 + k2 with k1 = (Xr - Xi) Tr,
-  //   k2 = Xr (Ti - Tr), k3 = Xi (Tr + Ti)
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int i = 4 * q + kk;
-    const float2 x = lds_el<16>(sm.A[slot], c, i);
-    const float2 tv = sm.m(slot, c, i);
-    k1 = mma32(x.x - x.y, tv.x, k1);
-    k2 = mma32(x.x, tv.y - tv.x, k2);
-    k3 = mma32(x.y, tv.x + tv.y, k3);
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    zr[r] = k1[r] + k3[r];
-    zi[r] = k1[r] + k2[r];
-  }
-}
-
-// z_s = X^H (X m_s) at lane i for the matched filter m_s of the slot.
-template <int UT, class SM>
-__device__ __forceinline__ float2 sym_apply(const SymSolve<UT> &r, SM &sm, int slot, int s) {
-  float tx = 0.f, ty = 0.f;
-#pragma unroll
-  for (int u = 0; u < UT; ++u) {
-    const float2 mv = sm.m(slot, s, u);
-    tx = fmaf(r.xr[u].x, mv.x, fmaf(-r.xr[u].y, mv.y, tx));
-    ty = fmaf(r.xr[u].x, mv.y, fmaf(r.xr[u].y, mv.x, ty));
-  }
-  return apply_xh<UT>(r.f, make_float2(tx, ty));
-}
-
-// MRC (Section III-A) on the slot's G (stored unshifted): lane i gets
-// 1 / G_ii and sigma2_i = N0 / G_ii + E_s sum_{k != i} |G_ik|^2 / G_ii^2;
-// fail = u + 1 for the group's first user with G_uu <= 0.
-struct SymMrc {
-  float inv_gii;
-  float s2;
-  int fail;
-  bool bad;
-};
-
-template <int UT, class SM>
-__device__ __forceinline__ SymMrc sym_mrc_row(SM &sm, int slot, int i, int U, float n0, float es) {
-  float gii = 0.f, off = 0.f;
-  bool bad = false;
-#pragma unroll
-  for (int k = 0; k < UT; ++k) {
-    const float2 g = lds_el<UT>(sm.A[slot], i, k);
-    bad |= !finite2(g);
-    if (k == i) gii = g.x;
-    else off = fmaf(g.x, g.x, fmaf(g.y, g.y, off));
-  }
-  SymMrc o;
-  o.bad = gany<UT>(bad);
-  const int base = (lane_id() / UT) * UT;
-  const unsigned long long gm = ((UT == 64 ? ~0ull : ((1ull << UT) - 1ull)) << base);
-  const unsigned long long fm = __ballot(i < U && !(gii > 0.f)) & gm;
-  o.fail = fm ? __builtin_ctzll(fm) - base + 1 : 0;
-  o.inv_gii = 1.0f / gii;
-  o.s2 = n0 * o.inv_gii + es * off * o.inv_gii * o.inv_gii;
-  return o;
+    for (int r = 0; r < 4; ++r) {
+      const int u = 16 * t + 4 * kk + r;
+      const float inv = 1.0f / f.tk[t][r];
+      const float s = user_nu ? f.tk[t][r] : inv;
+      if (u < a.U) {
+        if (c < a.nsym) {
+          a.z[ob + u] = user_nu ? make_float2(f.z.re[t][r], f.z.im[t][r])
+                                : make_float2(f.z.re[t][r] * inv, f.z.im[t][r] * inv);
+          if (PERSYM && a.s2) a.s2[ob + u] = s;
+        }
+        if (!PERSYM && c == 0 && a.s2) a.s2[(size_t)w * a.U + u] = s;
+      }
+    }
 }
 
 __device__ __forceinline__ void enqueue_fp64_sym(const FwdArgs &a, int w) {
@@ -385,78 +435,204 @@ __device__ __forceinline__ void enqueue_fp64_sym(const FwdArgs &a, int w) {
   if (pos >= 0 && pos < a.W) a.fb_list[pos] = w;  // capacity W
 }
 
-// PD: systems w0 .. w0+nvalid-1, one per lane group.
-template <int UT, int PREC, bool MRC, class SM>
-__device__ __forceinline__ void pd_sym_task(const FwdArgs &a, int w0, int nvalid, SM &sm) {
-  const int lane = lane_id();
-  const int g = lane / UT, i = lane % UT;
-  const size_t HB = (size_t)a.B * a.U;
-  auto seg = [&](int s, const float2 *&Hw, const float2 *&Yw, int &r0, int &r1) {
+// Rows of system s of a list: whole subcarriers from w0 (PD), or clusters
+// from c0 of subcarrier w0 (FD).
+__device__ __forceinline__ auto pd_seg(const FwdArgs &a, int w0) {
+  return [&a, w0](int s, const float2 *&Hw, const float2 *&Yw, int &r0, int &r1) {
     const size_t w = (size_t)w0 + s;
-    Hw = a.H + w * HB;
+    Hw = a.H + w * ((size_t)a.B * a.U);
     Yw = a.y + w * (size_t)a.ysw;
     r0 = 0;
     r1 = a.B;
   };
-  gram_mf_stream<UT, PREC>(nvalid, a.U, a.B, a.nsym, seg, [&](int s, const Acc<UT> &acc, const MAcc<UT> &m) {
-    store_gram_shift<UT, PREC>(sm.A[s], acc, a.rho, a.U);
-    store_msym<UT, PREC>(sm, s, m);
-  });
-  for (int s = nvalid; s < SM::NS; ++s) store_identity<UT>(sm.A[s]);
-  __syncthreads();
+}
+// cluster(s): the s-th of them
+template <class Cluster>
+__device__ __forceinline__ auto fd_seg(const FwdArgs &a, int w, Cluster cluster) {
+  return [&a, w, cluster](int s, const float2 *&Hw, const float2 *&Yw, int &r0, int &r1) {
+    Hw = a.H + (size_t)w * ((size_t)a.B * a.U);
+    Yw = a.y + (size_t)w * (size_t)a.ysw;
+    r0 = a.off[cluster(s)];
+    r1 = a.off[cluster(s) + 1];
+  };
+}
 
-  const int slot = slot_of<SM>(g);
-  const bool live = g < nvalid;
-  if constexpr (MRC) {
-    const SymMrc o = sym_mrc_row<UT>(sm, slot, i, a.U, a.n0, a.es);
-    const bool out_nan = o.bad || o.fail;
-    const float nanv = __int_as_float(0x7fc00000);
-    const int w = w0 + g;
-    if (live && i < a.U) {
-      float2 *zw = a.z + (size_t)w * a.zsw;
-      for (int s = 0; s < a.nsym; ++s) {
-        const float2 mv = sm.m(slot, s, i);
-        zw[(size_t)s * a.U + i] = out_nan ? make_float2(nanv, nanv) : make_float2(mv.x * o.inv_gii, mv.y * o.inv_gii);
-      }
-      if (a.s2) a.s2[(size_t)w * a.U + i] = out_nan ? nanv : o.s2;
+// ---------------------------------------------------------------- L-MMSE, ZF
+// LDS of one wave: packed matrix slots, and at 32 users the matched filters
+// (accumulator layout, one 16-byte word per lane and tile part).  At 16 users
+// the matched filters of the round's four systems stay in 32 registers: 8 KB
+// of LDS instead of 16 (LDS comes in units of 1,280 bytes: 9 waves per CU).
+template <int NT, int NSLOT>
+struct SymLds;
+template <int NSLOT>
+struct SymLds<1, NSLOT> {
+  static constexpr int NS = NSLOT;
+  float2 A[NS * kSlot<16>];
+};
+template <int NSLOT>
+struct SymLds<2, NSLOT> {
+  static constexpr int NS = NSLOT;
+  float2 A[NS * kSlot<32>];
+  f4 M[NS][4][64];
+};
+
+// Matched filters of the systems of a round.
+template <int NT, int NS>
+struct SymMf {
+  Tiles<1> m[NT == 1 ? NS : 1];
+};
+
+template <int NT, int PREC, class SM>
+__device__ __forceinline__ void store_system(SM &sm, SymMf<NT, SM::NS> &mf, int s, const TileAcc<NT> &acc,
+                                             const TileMf<NT> &m) {
+  const int lane = lane_id();
+  const int kk = lane / 16, c = lane % 16;
+  float2 *As = sm.A + s * kSlot<16 * NT>;
+  Tiles<2 * NT - 1> G;
+  tile_gram<NT, PREC>(&As[0].x, acc, G);
+  wave_sync();
+#pragma unroll
+  for (int b = 0; b < 2 * NT - 1; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) blk_el(As, b, 4 * kk + r, c) = make_float2(G.re[b][r], G.im[b][r]);
+  Tiles<NT> M;
+  tile_mf<NT, PREC>(m, M);
+  if constexpr (NT == 1) {
+    sfor<SM::NS>([&](auto Q) {
+      if (s == Q) mf.m[Q] = M;
+    });
+  } else {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      sm.M[s][2 * t][lane] = M.re[t];
+      sm.M[s][2 * t + 1][lane] = M.im[t];
     }
-    if (live && i == 0 && a.info) a.info[w] = o.bad ? -1 : o.fail;
-    return;
   }
-  SymSolve<UT> r;
-  sym_factor<UT>(r, sm, slot, i, a.U);
+}
+
+// out += X M (HERM = false) or X^H M (HERM = true) for one 16 x 16 block of X,
+// whose conjugate the slot holds transposed (row u: column u).  16 users take
+// three real products (Gauss), 32 users four: the Gauss form is 25% fewer
+// MFMAs of a product that is a tenth of the work there, and rounds more.
+template <bool HERM, bool GAUSS>
+__device__ __forceinline__ void block_mul(float2 *As, int b, const f4 &mr, const f4 &mi, f4 &k1, f4 &k2, f4 &k3) {
+  const int lane = lane_id();
+  const int kk = lane / 16, c = lane % 16;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    // A operand [i = c][k = (r, kk)]: X[c][4 kk + r], or conj(X[4 kk + r][c])
+    const float2 x = HERM ? blk_el(As, b, c, 4 * kk + r) : blk_el(As, b, 4 * kk + r, c);
+    if constexpr (GAUSS) {
+      // xr = x.x, xi = +-x.y: k1 = (xr + xi) mr, k2 = xr (mi - mr), k3 = xi (mr + mi);
+      // Re = k1 - k3, Im = k1 + k2
+      const float xi = HERM ? x.y : -x.y;
+      k1 = mma32(x.x + xi, mr[r], k1);
+      k2 = mma32(x.x, mi[r] - mr[r], k2);
+      k3 = mma32(xi, mr[r] + mi[r], k3);
+    } else {
+      // k1 = Re, k2 = Im
+      k1 = mma32(x.x, mr[r], k1);
+      k2 = mma32(x.x, mi[r], k2);
+      k1 = mma32(HERM ? -x.y : x.y, mi[r], k1);
+      k2 = mma32(HERM ? x.y : -x.y, mr[r], k2);
+    }
+  }
+}
+
+// Z = X^H (X M) for slot q and every symbol of the tile, the whole wave on one
+// system.
+template <int NT, class SM>
+__device__ __forceinline__ void sym_apply(SM &sm, const Tiles<1> &m0, int q, Tiles<NT> &Z) {
+  constexpr bool GAUSS = NT == 1;
+  const int lane = lane_id();
+  float2 *As = sm.A + q * kSlot<16 * NT>;
+  const f4 z0 = {0.f, 0.f, 0.f, 0.f};
+  Tiles<NT> T;
+  f4 mr[NT], mi[NT], k1, k2, k3;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    if constexpr (NT == 1) {
+      mr[t] = m0.re[0];
+      mi[t] = m0.im[0];
+    } else {
+      mr[t] = sm.M[q][2 * t][lane];
+      mi[t] = sm.M[q][2 * t + 1][lane];
+    }
+  }
+  auto out = [&](f4 &re, f4 &im) {
+    re = GAUSS ? k1 - k3 : k1;
+    im = GAUSS ? k1 + k2 : k2;
+  };
+  // T: rows of X (blocks 0; 1, 2)
+  k1 = k2 = k3 = z0;
+  block_mul<false, GAUSS>(As, 0, mr[0], mi[0], k1, k2, k3);
+  out(T.re[0], T.im[0]);
+  if constexpr (NT == 2) {
+    k1 = k2 = k3 = z0;
+    block_mul<false, GAUSS>(As, 1, mr[0], mi[0], k1, k2, k3);
+    block_mul<false, GAUSS>(As, 2, mr[1], mi[1], k1, k2, k3);
+    out(T.re[1], T.im[1]);
+  }
+  // Z: columns of X (blocks 0, 1; 2)
+  k1 = k2 = k3 = z0;
+  block_mul<true, GAUSS>(As, 0, T.re[0], T.im[0], k1, k2, k3);
+  if constexpr (NT == 2) block_mul<true, GAUSS>(As, 1, T.re[1], T.im[1], k1, k2, k3);
+  out(Z.re[0], Z.im[0]);
+  if constexpr (NT == 2) {
+    k1 = k2 = k3 = z0;
+    block_mul<true, GAUSS>(As, 2, T.re[1], T.im[1], k1, k2, k3);
+    out(Z.re[1], Z.im[1]);
+  }
+}
+
+// Value v of lane group q's user 16 t + 4 kk + r, in accumulator layout.
+template <int NT>
+__device__ __forceinline__ void to_tiles(float v, int q, f4 (&o)[NT]) {
+  const int kk = lane_id() / 16;
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) o[t][r] = __shfl(v, q * 16 * NT + 16 * t + 4 * kk + r);
+}
+
+// PD: systems w0 .. w0+nvalid-1, one per lane group.
+template <int NT, int PREC, class SM>
+__device__ __forceinline__ void pd_sym_task(const FwdArgs &a, int w0, int nvalid, SM &sm) {
+  constexpr int UT = 16 * NT;
+  const int lane = lane_id();
+  const int g = lane / UT, i = lane % UT;
+  SymMf<NT, SM::NS> mf;
+  gram_mf_stream<NT, PREC>(nvalid, a.U, a.B, a.nsym, pd_seg(a, w0),
+                           [&](int s, const TileAcc<NT> &acc, const TileMf<NT> &m) { store_system<NT, PREC>(sm, mf, s, acc, m); });
+  wave_sync();
+  LocalSolve<UT> r;
+  solve_slot<UT, true, SM::NS, false>(r, sm.A, slot_of<SM>(g), i, make_float2(0.f, 0.f), a.rho, a.U);
+  wave_sync();
+  const bool live = g < nvalid;
   const float kappa = r.norm1 * gsum<UT>(i < a.U ? r.d : 0.f);
   const bool routed = live && !r.bad && (r.fail != 0 || !(kappa <= EQ_COND_LIMIT));
   const int w = w0 + g;
   const float nanv = __int_as_float(0x7fc00000);
   // gain factor of user i (1 unless the unbiased L-MMSE)
-  const float ku = unbias_factor(a.n0 * r.d, a.ub);
-  if constexpr (UT == 16) {
-    // one system at a time on MFMA; slot q holds system w0 + q.  Lane
-    // (kk, c) writes users 4 kk + r, whose factors it reads from F (the
-    // barrier inside the first product orders these writes before the reads)
-    sm.F[g][i] = make_float2(ku, 0.f);
-    const unsigned long long badm = __ballot(r.bad);
-    const int kk = lane >> 4, c = lane & 15;
-    for (int q = 0; q < nvalid; ++q) {
-      f4 zr, zi;
-      sym_mfma16(sm, q, zr, zi);
-      const bool bq = (badm >> (16 * q)) & 1ull;
-      float2 *zw = a.z + (size_t)(w0 + q) * a.zsw + (size_t)c * a.U;
+  const float ku = a.ub != 0.f ? unbias_factor(a.n0 * r.d, a.ub) : 1.f;
+  const float kz = r.bad ? nanv : ku;
+  const int kk = lane / 16, c = lane % 16;
+  sfor<SM::NS>([&](auto Q) {
+    constexpr int q = Q;
+    if (q >= nvalid) return;
+    Tiles<NT> Z;
+    sym_apply<NT>(sm, mf.m[NT == 1 ? q : 0], q, Z);
+    f4 k[NT];
+    to_tiles<NT>(kz, q, k);
+    float2 *zw = a.z + (size_t)(w0 + q) * a.zsw + (size_t)c * a.U;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
       for (int rr = 0; rr < 4; ++rr) {
-        const int u = 4 * kk + rr;
-        const float kq = sm.F[q][u].x;
-        if (c < a.nsym && u < a.U) zw[u] = bq ? make_float2(nanv, nanv) : make_float2(zr[rr] * kq, zi[rr] * kq);
+        const int u = 16 * t + 4 * kk + rr;
+        if (c < a.nsym && u < a.U) zw[u] = make_float2(Z.re[t][rr] * k[t][rr], Z.im[t][rr] * k[t][rr]);
       }
-    }
-  } else {
-    float2 *zw = a.z + (size_t)w * a.zsw;
-    for (int s = 0; s < a.nsym; ++s) {
-      const float2 z = sym_apply<UT>(r, sm, slot, s);
-      if (live && i < a.U) zw[(size_t)s * a.U + i] = r.bad ? make_float2(nanv, nanv) : make_float2(z.x * ku, z.y * ku);
-    }
-  }
+  });
   if (live) {
     if (i < a.U && a.s2) a.s2[(size_t)w * a.U + i] = r.bad ? nanv : a.n0 * r.d * ku;
     if (i == 0) {
@@ -466,381 +642,457 @@ __device__ __forceinline__ void pd_sym_task(const FwdArgs &a, int w0, int nvalid
   }
 }
 
-// FD: all clusters of subcarrier w, NSYS local systems per round.  The
-// fusion sums (eq. (fusionrule)) run over the clusters in cluster order.
-// MRC (no factor) fuses m_s / G_uu with the 32-lane layout's LDS fusion at
-// every width.
-// 16-lane groups: Z of each cluster comes from MFMA in accumulator layout,
-// and lane (kk, c) keeps the sums of users 4 kk + r of symbol c.  32-lane
-// groups: lane (q, u) = (lane / UT, lane % UT) keeps the sums of user u for
-// the symbols q, q + NSYS, q + 2 NSYS, ...
-template <int UT, int PREC, bool MRC, class SM>
-__device__ __forceinline__ void fd_sym_task(const FwdArgs &a, int w, SM &sm) {
-  constexpr int NSYS = 64 / UT;
-  constexpr int KS = UT == 16 ? 4 : UT / NSYS;  // sums per lane
+// FD: all clusters of subcarrier w, in rounds of NSYS that the NW waves take
+// in turn.
+template <int NT, int PREC, int NW, class SM>
+__device__ __forceinline__ void fd_sym_task(const FwdArgs &a, int w, SM *sms, int wv) {
+  constexpr int UT = 16 * NT, NSYS = 64 / UT;
+  SM &sm = sms[wv];
   const int lane = lane_id();
-  const int g = lane / UT, i = lane % UT;
-  const size_t HB = (size_t)a.B * a.U;
   const int C = a.C;
   const bool user_nu = a.nu != nullptr;
   const float nanv = __int_as_float(0x7fc00000);
-  // F[g][i] = (weight of cluster g's estimate of user i, its term of tk):
-  // tk sums the weights (optimal fusion: the fused variance is 1 / tk) or,
-  // with given weights, nu^2 sigma2_c (the fused variance itself)
-  float2 zf[KS];
-  float tk[UT == 16 ? 4 : 1];
-#pragma unroll
-  for (int k = 0; k < KS; ++k) zf[k] = make_float2(0.f, 0.f);
-#pragma unroll
-  for (int k = 0; k < (UT == 16 ? 4 : 1); ++k) tk[k] = 0.f;
-  bool routed_any = false;
-  // MRC keeps the sums in the (lane / UT, lane % UT) layout at every width
-  constexpr bool mrc = MRC;
-  // fusion of the round's weighted estimates (rows of the slots' matched
-  // filters) and weights (F) by lane (g, i): symbols g, g + NSYS, ...
-  auto valu_fuse = [&](int nvalid) {
-#pragma unroll
-    for (int k = 0; k < KS; ++k) {
-      const int s = g + NSYS * k;
-      if (s < a.nsym) {
-        for (int q = 0; q < nvalid; ++q) {
-          const float2 v = sm.m(q, s, i);
-          zf[k].x += v.x;
-          zf[k].y += v.y;
-        }
-      }
-    }
-    for (int q = 0; q < nvalid; ++q) tk[0] += sm.F[q][i].y;
-  };
-
-  for (int base = 0; base < C; base += NSYS) {
+  FuseSum<NT> f;
+  fuse_zero<NT>(f);
+  float tk = 0.f;  // the weights' sum of user i, clusters of this lane's group
+  bool any = false;
+  const int g = lane / UT, i = lane % UT;
+  for (int base = wv * NSYS; base < C; base += NW * NSYS) {
     const int nvalid = min(NSYS, C - base);
-    auto seg = [&](int s, const float2 *&Hw, const float2 *&Yw, int &r0, int &r1) {
-      Hw = a.H + (size_t)w * HB;
-      Yw = a.y + (size_t)w * a.ysw;
-      r0 = a.off[base + s];
-      r1 = a.off[base + s + 1];
-    };
-    gram_mf_stream<UT, PREC>(nvalid, a.U, a.B, a.nsym, seg, [&](int s, const Acc<UT> &acc, const MAcc<UT> &m) {
-      store_gram_shift<UT, PREC>(sm.A[s], acc, a.rho, a.U);
-      store_msym<UT, PREC>(sm, s, m);
-    });
-    for (int s = nvalid; s < NSYS; ++s) store_identity<UT>(sm.A[s]);
-    __syncthreads();
-
+    SymMf<NT, SM::NS> mf;
+    gram_mf_stream<NT, PREC>(nvalid, a.U, a.B, a.nsym, fd_seg(a, w, [base](int s) { return base + s; }),
+                             [&](int s, const TileAcc<NT> &acc, const TileMf<NT> &m) { store_system<NT, PREC>(sm, mf, s, acc, m); });
+    wave_sync();
+    LocalSolve<UT> r;
+    solve_slot<UT, true, SM::NS, false>(r, sm.A, g, i, make_float2(0.f, 0.f), a.rho, a.U);
+    wave_sync();
     const int c = base + g;
     const bool live = g < nvalid;
-    if constexpr (MRC) {
-      const SymMrc o = sym_mrc_row<UT>(sm, g, i, a.U, a.n0, a.es);
-      if (live && i == 0 && a.info) a.info[(size_t)w * C + c] = o.bad ? -1 : o.fail;
-      const bool out_nan = o.bad || o.fail;
-      float p = 0.f;
-      if (live && i < a.U) p = user_nu ? a.nu[((size_t)w * C + c) * a.U + i] : 1.0f / o.s2;
-      const float q = p * o.inv_gii;
-      for (int s = 0; s < a.nsym; ++s) {
-        const float2 mv = sm.m(g, s, i);
-        sm.m(g, s, i) = out_nan ? make_float2(nanv, nanv) : make_float2(q * mv.x, q * mv.y);
-      }
-      sm.F[g][i] = out_nan ? make_float2(nanv, nanv) : make_float2(p, user_nu ? p * p * o.s2 : p);
-      __syncthreads();
-      valu_fuse(nvalid);
-      __syncthreads();
-      continue;
-    }
-    SymSolve<UT> r;
-    sym_factor<UT>(r, sm, g, i, a.U);
     const float kappa = r.norm1 * gsum<UT>(i < a.U ? r.d : 0.f);
     const bool routed = live && !r.bad && (r.fail != 0 || !(kappa <= EQ_COND_LIMIT));
     if (live && i == 0 && a.info) a.info[(size_t)w * C + c] = (r.bad ? -1 : r.fail) | (routed ? EQ_INFO_FP64 : 0);
-    routed_any |= __ballot(routed) != 0ull;
+    any |= __ballot(routed) != 0ull;
     // local variance (of the estimate scaled to unit gain for the unbiased
     // L-MMSE: estimate and variance times ku) and fusion weight p; the
     // estimate's weight is p ku
-    const float ku = unbias_factor(a.n0 * r.d, a.ub);
+    const float ku = a.ub != 0.f ? unbias_factor(a.n0 * r.d, a.ub) : 1.f;
     const float s2c = a.n0 * r.d * ku;
     float p = 0.f;
     if (live && i < a.U) p = user_nu ? a.nu[((size_t)w * C + c) * a.U + i] : 1.0f / s2c;
-    const float pz = p * ku;
-    const float2 fterm = r.bad ? make_float2(nanv, nanv) : make_float2(pz, user_nu ? p * p * s2c : p);
-    if constexpr (UT == 16) {
-      sm.F[g][i] = fterm;
-      __syncthreads();
-      const int kk = lane >> 4;
-      for (int q = 0; q < nvalid; ++q) {
-        f4 zr, zi;
-        sym_mfma16(sm, q, zr, zi);
+    if (live) tk += r.bad ? nanv : (user_nu ? p * p * s2c : p);
+    const float pz = r.bad ? nanv : p * ku;
+    sfor<SM::NS>([&](auto Q) {
+      constexpr int q = Q;
+      if (q >= nvalid) return;
+      Tiles<NT> Z;
+      sym_apply<NT>(sm, mf.m[NT == 1 ? q : 0], q, Z);
+      f4 wq[NT];
+      to_tiles<NT>(pz, q, wq);
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-          const float2 fv = sm.F[q][4 * kk + rr];
-          zf[rr].x += fv.x * zr[rr];
-          zf[rr].y += fv.x * zi[rr];
-          tk[rr] += fv.y;
-        }
+      for (int t = 0; t < NT; ++t) {
+        f.z.re[t] += wq[t] * Z.re[t];
+        f.z.im[t] += wq[t] * Z.im[t];
       }
-    } else {
-      // weighted estimates replace the group's matched filters, row by row
-      // (each row is read by the whole group before its lane i overwrites it)
-      for (int s = 0; s < a.nsym; ++s) {
-        const float2 z = sym_apply<UT>(r, sm, g, s);
-        sm.m(g, s, i) = r.bad ? make_float2(nanv, nanv) : make_float2(pz * z.x, pz * z.y);
-      }
-      sm.F[g][i] = fterm;
-      __syncthreads();
-      valu_fuse(nvalid);
-    }
-    __syncthreads();
+    });
+    wave_sync();
   }
-
-  float2 *zw = a.z + (size_t)w * a.zsw;
-  bool mfma_layout = false;
-  if constexpr (UT == 16) mfma_layout = !mrc;
-  if (mfma_layout) {
-    const int kk = lane >> 4, cs = lane & 15;
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      const int u = 4 * kk + rr;
-      const float inv = 1.0f / tk[rr];
-      if (cs < a.nsym && u < a.U)
-        zw[(size_t)cs * a.U + u] = user_nu ? zf[rr] : make_float2(zf[rr].x * inv, zf[rr].y * inv);
-      if (cs == 0 && u < a.U && a.s2) a.s2[(size_t)w * a.U + u] = user_nu ? tk[rr] : inv;
-    }
-  } else if (i < a.U) {
-    const float inv = 1.0f / tk[0];
-#pragma unroll
-    for (int k = 0; k < KS; ++k) {
-      const int s = g + NSYS * k;
-      if (s < a.nsym) zw[(size_t)s * a.U + i] = user_nu ? zf[k] : make_float2(zf[k].x * inv, zf[k].y * inv);
-    }
-    if (g == 0 && a.s2) a.s2[(size_t)w * a.U + i] = user_nu ? tk[0] : inv;
-  }
-  if (lane == 0 && routed_any) enqueue_fp64_sym(a, w);
+  tk = UT == 16 ? groups_sum(tk) : xor32_sum(tk);
+  to_tiles<NT>(tk, 0, f.tk);
+  if (NW > 1 && lane == 0) sm.A[0].x = any ? 1.f : 0.f;
+  if (!fuse_waves<NT, NW>(f, wv, [&](int q) { return (float *)sms[q].A + 64; })) return;
+  fuse_write<NT, false>(a, w, f);
+  if (NW > 1)
+    for (int q = 0; q < NW; ++q) any |= sms[q].A[0].x != 0.f;
+  if (lane == 0 && any) enqueue_fp64_sym(a, w);
 }
 
-// ---------------------------------------------------------------- LAMA
-// LAMA (Algorithm 1) for every receive vector of the tile: one Gram per
-// subcarrier (PD) or cluster (FD), the iteration per vector.  LAMA's
-// variance N0 + beta phi depends on the vector, so sigma2 is [W][S][U] here.
+// ---------------------------------------------------------------- MRC (Section III-A)
+// 1 / G_uu and sigma2_u = N0 / G_uu + E_s sum_{k != u} |G_uk|^2 / G_uu^2 in
+// accumulator layout (equal in every column); fail = u + 1 for the first user
+// with G_uu <= 0.
+template <int NT>
+struct TileMrc {
+  f4 inv[NT], s2[NT];
+  int fail;
+  bool bad;
+};
 
-// Lane i of group g: f.x = conj(row i of the slot's G) * scale.
-template <int UT, class SM>
-__device__ __forceinline__ bool lama_load_row(Factor<UT> &f, SM &sm, int slot, int i, float scale) {
+template <int N>
+__device__ __forceinline__ bool tiles_bad(const Tiles<N> &G) {
   bool bad = false;
 #pragma unroll
-  for (int k = 0; k < UT; ++k) {
-    const float2 g = lds_el<UT>(sm.A[slot], i, k);
-    bad |= !finite2(g);
-    f.x[k] = make_float2(g.x * scale, -g.y * scale);
-  }
-  return gany<UT>(bad);
+  for (int b = 0; b < N; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) bad |= !isfinite(G.re[b][r]) || !isfinite(G.im[b][r]);
+  return __ballot(bad) != 0ull;
 }
 
-template <int UT, int PREC, int M, class SM>
-__device__ __forceinline__ void pd_sym_lama_task(const FwdArgs &a, int w0, int nvalid, SM &sm) {
+template <int NT>
+__device__ __forceinline__ TileMrc<NT> tile_mrc(const Tiles<2 * NT - 1> &G, int U, float n0, float es) {
   const int lane = lane_id();
-  const int g = lane / UT, i = lane % UT;
-  const size_t HB = (size_t)a.B * a.U;
-  auto seg = [&](int s, const float2 *&Hw, const float2 *&Yw, int &r0, int &r1) {
-    const size_t w = (size_t)w0 + s;
-    Hw = a.H + w * HB;
-    Yw = a.y + w * (size_t)a.ysw;
-    r0 = 0;
-    r1 = a.B;
-  };
-  gram_mf_stream<UT, PREC>(nvalid, a.U, a.B, a.nsym, seg, [&](int s, const Acc<UT> &acc, const MAcc<UT> &m) {
-    store_gram_shift<UT, PREC>(sm.A[s], acc, 0.f, a.U);
-    store_msym<UT, PREC>(sm, s, m);
-  });
-  for (int s = nvalid; s < SM::NS; ++s) store_identity<UT>(sm.A[s]);
-  __syncthreads();
-  const int slot = slot_of<SM>(g);
-  const bool live = g < nvalid;
-  const int w = w0 + g;
-  Factor<UT> f;
-  const bool bad = lama_load_row<UT>(f, sm, slot, i, 1.0f);
-  const float beta = (float)a.U / (float)a.B;
-  const float nanv = __int_as_float(0x7fc00000);
-  const size_t ob = (size_t)w * a.zsw;
-  for (int s = 0; s < a.nsym; ++s) {
-    float2 z;
-    float tau;
-    lama_iterate<UT, M>(f, sm.m(slot, s, i), i, a.U, a.n0, beta, a.es, a.lama_t, z, tau);
-    if (live && i < a.U) {
-      a.z[ob + (size_t)s * a.U + i] = bad ? make_float2(nanv, nanv) : z;
-      if (a.s2) a.s2[ob + (size_t)s * a.U + i] = bad ? nanv : tau;
-    }
+  const int kk = lane / 16, c = lane % 16;
+  TileMrc<NT> o;
+  o.bad = tiles_bad<2 * NT - 1>(G);
+  float below = 0.f;  // NT = 2: sum_k |G_{16 + k, c}|^2, user c of the first tile
+  if constexpr (NT == 2) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) below = fmaf(G.re[1][r], G.re[1][r], fmaf(G.im[1][r], G.im[1][r], below));
+    below = groups_sum(below);
   }
-  if (live && i == 0 && a.info) a.info[w] = bad ? -1 : 0;
+  int fail = 4 * EQ_MAX_U;
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int u = 16 * t + 4 * kk + r;
+      const float re = G.re[2 * t][r], im = G.im[2 * t][r];
+      const bool diag = c == 4 * kk + r;
+      float off = diag ? 0.f : fmaf(re, re, im * im);
+      if (NT == 2 && t == 1) off = fmaf(G.re[1][r], G.re[1][r], fmaf(G.im[1][r], G.im[1][r], off));
+      off = row16_sum(off);
+      if (NT == 2 && t == 0) off += __shfl(below, 4 * kk + r);
+      const float gii = row16_sum(diag ? re : 0.f);
+      if (u < U && !(gii > 0.f)) fail = min(fail, u + 1);
+      const float inv = 1.0f / gii;
+      o.inv[t][r] = inv;
+      o.s2[t][r] = n0 * inv + es * off * inv * inv;
+    }
+  fail = min(fail, __shfl_xor(fail, 16));
+  fail = min(fail, __shfl_xor(fail, 32));
+  o.fail = fail <= EQ_MAX_U ? fail : 0;
+  return o;
 }
 
-// FD: rounds of NSYS clusters.  After a cluster's iteration for vector s,
-// lane (g, i) leaves nu z in the slot's matched-filter row s and (nu,
-// nu^2 sigma2_c) in row s of the slot's (no longer needed) G; fusion lane
-// (g, i) then sums user i of the vectors g, g + NSYS, ... over the clusters.
-template <int UT, int PREC, int M, class SM>
-__device__ __forceinline__ void fd_sym_lama_task(const FwdArgs &a, int w, SM &sm) {
-  constexpr int NSYS = 64 / UT;
-  constexpr int KS = UT / NSYS;
-  const int lane = lane_id();
-  const int g = lane / UT, i = lane % UT;
-  const size_t HB = (size_t)a.B * a.U;
-  const int C = a.C;
-  const bool user_nu = a.nu != nullptr;
-  const float nanv = __int_as_float(0x7fc00000);
-  const float beta = (float)a.U / (float)a.B;
-  float2 zf[KS];
-  float swk[KS], svk[KS];
+// ---------------------------------------------------------------- LAMA (Algorithm 1)
+// t_max iterations for one system and every symbol of the tile:
+//     z = y^MRC + (I - G) s + v,   tau = N0 + beta phi,
+//     s' = F(z, tau),   phi' = <G(z, tau)>,   v' = beta phi' / tau (z - s),
+// G s on MFMA (the Gram registers are their own A operand: lane (kk, c) holds
+// G_{4 kk + r, c} = conj(G_{c, 4 kk + r})), the rest per element.  The first
+// iteration has s = v = 0, so z = y^MRC; the last one ends with z and tau.
+// Returns z in Z and the symbol's variance N0 + beta phi.
+template <int NT, int M>
+__device__ __forceinline__ float tile_lama(const Tiles<2 * NT - 1> &G, const Tiles<1> &G01t, const Tiles<NT> &Y, int U,
+                                           float n0, float beta, float es, int t_max, Tiles<NT> &Z) {
+  const int kk = lane_id() / 16;
+  const float lvl = sqrtf(3.0f * es / (2.0f * (float)(M * M - 1)));
+  const float inv_u = 1.0f / (float)U;
+  Tiles<NT> S, V;
+  Z = Y;
+  float tau = n0 + beta * es;
+  for (int it = 1; it < t_max; ++it) {
+    // posterior of the previous z
+    const float inv_tau = 1.0f / tau;
+    float g = 0.f;
+    Tiles<NT> N;
 #pragma unroll
-  for (int k = 0; k < KS; ++k) {
-    zf[k] = make_float2(0.f, 0.f);
-    swk[k] = 0.f;
-    svk[k] = 0.f;
-  }
-  for (int base = 0; base < C; base += NSYS) {
-    const int nvalid = min(NSYS, C - base);
-    auto seg = [&](int s, const float2 *&Hw, const float2 *&Yw, int &r0, int &r1) {
-      Hw = a.H + (size_t)w * HB;
-      Yw = a.y + (size_t)w * a.ysw;
-      r0 = a.off[base + s];
-      r1 = a.off[base + s + 1];
-    };
-    gram_mf_stream<UT, PREC>(nvalid, a.U, a.B, a.nsym, seg, [&](int s, const Acc<UT> &acc, const MAcc<UT> &m) {
-      store_gram_shift<UT, PREC>(sm.A[s], acc, 0.f, a.U);
-      store_msym<UT, PREC>(sm, s, m);
-    });
-    for (int s = nvalid; s < NSYS; ++s) store_identity<UT>(sm.A[s]);
-    __syncthreads();
-    const int c = base + g;
-    const bool live = g < nvalid;
-    const float wc = live ? (float)(a.off[c + 1] - a.off[c]) / (float)a.B : 1.0f;
-    const float iw = 1.0f / wc;
-    Factor<UT> f;
-    const bool bad = lama_load_row<UT>(f, sm, g, i, iw);
-    if (live && i == 0 && a.info) a.info[(size_t)w * C + c] = bad ? -1 : 0;
-    float nu = 0.f;
-    if (user_nu && live && i < a.U) nu = a.nu[((size_t)w * C + c) * a.U + i];
-    __syncthreads();  // every row of G is in registers: the slots' G rows are free
-    for (int s = 0; s < a.nsym; ++s) {
-      const float2 mv = sm.m(g, s, i);
-      float2 z;
-      float tau;
-      lama_iterate<UT, M>(f, make_float2(mv.x * iw, mv.y * iw), i, a.U, a.n0 * iw, beta * iw, a.es, a.lama_t, z, tau);
-      const float p = (live && i < a.U) ? (user_nu ? nu : 1.0f / tau) : 0.f;
-      sm.m(g, s, i) = bad ? make_float2(nanv, nanv) : make_float2(p * z.x, p * z.y);
-      lds_el<UT>(sm.A[g], s, i) = bad ? make_float2(nanv, nanv) : make_float2(p, p * p * tau);
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float mr, qr, mi, qi;
+        pam_posterior<M>(Z.re[t][r], inv_tau, lvl, mr, qr);
+        pam_posterior<M>(Z.im[t][r], inv_tau, lvl, mi, qi);
+        const bool user = 16 * t + 4 * kk + r < U;
+        N.re[t][r] = user ? mr : 0.f;
+        N.im[t][r] = user ? mi : 0.f;
+        g += user ? (qr - mr * mr) + (qi - mi * mi) : 0.f;
+      }
+    const float phi = groups_sum(g) * inv_u;
+    const float k = beta * phi * inv_tau;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      if (it == 1) {
+        V.re[t] = k * Z.re[t];
+        V.im[t] = k * Z.im[t];
+      } else {
+        V.re[t] = k * (Z.re[t] - S.re[t]);
+        V.im[t] = k * (Z.im[t] - S.im[t]);
+      }
     }
-    __syncthreads();
+    S = N;
+    tau = n0 + beta * phi;
+    // z = y^MRC + s - G s + v
+    Tiles<NT> P;
+    const f4 z0 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int k = 0; k < KS; ++k) {
-      const int s = g + NSYS * k;
-      if (s < a.nsym) {
-        for (int q = 0; q < nvalid; ++q) {
-          const float2 v = sm.m(q, s, i);
-          const float2 pw = lds_el<UT>(sm.A[q], s, i);
-          zf[k].x += v.x;
-          zf[k].y += v.y;
-          swk[k] += pw.x;
-          svk[k] += pw.y;
+    for (int t = 0; t < NT; ++t) {
+      f4 pr = z0, pi = z0;
+#pragma unroll
+      for (int b = 0; b < NT; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          // G_{16 t + c, 16 b + 4 kk + r}
+          const bool low = NT == 2 && t == 1 && b == 0;
+          const int blk = t == b ? 2 * t : 1;
+          const float gr = low ? G01t.re[0][r] : G.re[blk][r];
+          const float gi = low ? G01t.im[0][r] : -G.im[blk][r];
+          pr = mma32(gr, S.re[b][r], pr);
+          pi = mma32(gr, S.im[b][r], pi);
+          pr = mma32(-gi, S.im[b][r], pr);
+          pi = mma32(gi, S.re[b][r], pi);
+        }
+      P.re[t] = pr;
+      P.im[t] = pi;
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      Z.re[t] = Y.re[t] + S.re[t] - P.re[t] + V.re[t];
+      Z.im[t] = Y.im[t] + S.im[t] - P.im[t] + V.im[t];
+    }
+  }
+  return tau;
+}
+
+// NT = 2: block (1, 0) with rows and columns exchanged, G_{16 + c, 4 kk + r} at
+// lane (kk, c), through 512 floats of LDS.
+template <int NT>
+__device__ __forceinline__ void tile_turn(float *scratch, const Tiles<2 * NT - 1> &G, Tiles<1> &o) {
+  if constexpr (NT == 2) {
+    const int lane = lane_id();
+    const int kk = lane / 16, c = lane % 16;
+    wave_sync();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int u = 4 * kk + r;
+      scratch[16 * u + (c ^ u)] = G.re[1][r];
+      scratch[256 + 16 * u + (c ^ u)] = G.im[1][r];
+    }
+    wave_sync();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int u = 4 * kk + r;
+      o.re[0][r] = scratch[16 * c + (u ^ c)];
+      o.im[0][r] = scratch[256 + 16 * c + (u ^ c)];
+    }
+  }
+}
+
+// ---------------------------------------------------------------- MRC and LAMA kernels
+// M = 0: MRC; else LAMA with M levels per coordinate.  LDS of one wave: the
+// transposes' scratch and, at the end, the wave's fusion sums.
+template <int NT>
+struct DirectLds {
+  float f[12 * NT * 64];
+};
+
+// One system (PD): estimates and variances to their rows.
+template <int NT, int PREC, int M>
+__device__ __forceinline__ void pd_direct_task(const FwdArgs &a, int w0, int nvalid, DirectLds<NT> &sm) {
+  const int lane = lane_id();
+  const int kk = lane / 16, c = lane % 16;
+  const float nanv = __int_as_float(0x7fc00000);
+  gram_mf_stream<NT, PREC>(nvalid, a.U, a.B, a.nsym, pd_seg(a, w0), [&](int s, const TileAcc<NT> &acc, const TileMf<NT> &m) {
+    const int w = w0 + s;
+    Tiles<2 * NT - 1> G;
+    Tiles<NT> Y, Z;
+    tile_gram<NT, PREC>(sm.f, acc, G);
+    tile_mf<NT, PREC>(m, Y);
+    f4 s2[NT];
+    int code;
+    bool out_nan;
+    if constexpr (M == 0) {
+      const TileMrc<NT> o = tile_mrc<NT>(G, a.U, a.n0, a.es);
+      code = o.bad ? -1 : o.fail;
+      out_nan = code != 0;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        Z.re[t] = Y.re[t] * o.inv[t];
+        Z.im[t] = Y.im[t] * o.inv[t];
+        s2[t] = o.s2[t];
+      }
+    } else {
+      Tiles<1> T;
+      tile_turn<NT>(sm.f, G, T);
+      out_nan = tiles_bad<2 * NT - 1>(G);
+      code = out_nan ? -1 : 0;
+      const float tau =
+          tile_lama<NT, M>(G, T, Y, a.U, a.n0, (float)a.U / (float)a.B, a.es, a.lama_t, Z);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) s2[t] = tau;
+    }
+    const size_t ob = (size_t)w * a.zsw + (size_t)c * a.U;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int u = 16 * t + 4 * kk + r;
+        if (u < a.U) {
+          const float v = out_nan ? nanv : s2[t][r];
+          if (c < a.nsym) {
+            a.z[ob + u] = out_nan ? make_float2(nanv, nanv) : make_float2(Z.re[t][r], Z.im[t][r]);
+            if (M != 0 && a.s2) a.s2[ob + u] = v;
+          }
+          if (M == 0 && c == 0 && a.s2) a.s2[(size_t)w * a.U + u] = v;
         }
       }
-    }
-    __syncthreads();
-  }
-  if (i < a.U) {
-    const size_t ob = (size_t)w * a.zsw;
+    if (lane == 0 && a.info) a.info[w] = code;
+  });
+}
+
+// All clusters of subcarrier w, shared among the NW waves.  LAMA-FD runs on
+// the statistics normalised by 1 / w_c, w_c = B_c / B.
+template <int NT, int PREC, int M, int NW>
+__device__ __forceinline__ void fd_direct_task(const FwdArgs &a, int w, DirectLds<NT> *sms, int wv) {
+  DirectLds<NT> &sm = sms[wv];
+  const int lane = lane_id();
+  const int kk = lane / 16;
+  const bool user_nu = a.nu != nullptr;
+  const float nanv = __int_as_float(0x7fc00000);
+  const int C = a.C;
+  FuseSum<NT> f;
+  fuse_zero<NT>(f);
+  const int ncl = wv < C ? (C - wv + NW - 1) / NW : 0;
+  auto cluster = [wv](int s) { return wv + NW * s; };
+  if (ncl > 0)
+    gram_mf_stream<NT, PREC>(ncl, a.U, a.B, a.nsym, fd_seg(a, w, cluster), [&](int s, const TileAcc<NT> &acc, const TileMf<NT> &m) {
+      const int c = cluster(s);
+      Tiles<2 * NT - 1> G;
+      Tiles<NT> Y, Z;
+      tile_gram<NT, PREC>(sm.f, acc, G);
+      tile_mf<NT, PREC>(m, Y);
+      f4 s2[NT];
+      int code;
+      if constexpr (M == 0) {
+        const TileMrc<NT> o = tile_mrc<NT>(G, a.U, a.n0, a.es);
+        code = o.bad ? -1 : o.fail;
 #pragma unroll
-    for (int k = 0; k < KS; ++k) {
-      const int s = g + NSYS * k;
-      if (s < a.nsym) {
-        const float inv = 1.0f / swk[k];
-        a.z[ob + (size_t)s * a.U + i] = user_nu ? zf[k] : make_float2(zf[k].x * inv, zf[k].y * inv);
-        if (a.s2) a.s2[ob + (size_t)s * a.U + i] = user_nu ? svk[k] : inv;
+        for (int t = 0; t < NT; ++t) {
+          Z.re[t] = Y.re[t] * o.inv[t];
+          Z.im[t] = Y.im[t] * o.inv[t];
+          s2[t] = o.s2[t];
+        }
+      } else {
+        const float iw = 1.0f / ((float)(a.off[c + 1] - a.off[c]) / (float)a.B);
+#pragma unroll
+        for (int b = 0; b < 2 * NT - 1; ++b) {
+          G.re[b] *= iw;
+          G.im[b] *= iw;
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          Y.re[t] *= iw;
+          Y.im[t] *= iw;
+        }
+        Tiles<1> T;
+        tile_turn<NT>(sm.f, G, T);
+        code = tiles_bad<2 * NT - 1>(G) ? -1 : 0;
+        const float tau = tile_lama<NT, M>(G, T, Y, a.U, a.n0 * iw, (float)a.U / (float)a.B * iw, a.es, a.lama_t, Z);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) s2[t] = tau;
       }
-    }
-  }
+      if (lane == 0 && a.info) a.info[(size_t)w * C + c] = code;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int u = 16 * t + 4 * kk + r;
+          float p = 0.f;
+          if (u < a.U) p = user_nu ? a.nu[((size_t)w * C + c) * a.U + u] : 1.0f / s2[t][r];
+          if (code != 0) p = nanv;
+          f.z.re[t][r] += p * Z.re[t][r];
+          f.z.im[t][r] += p * Z.im[t][r];
+          f.tk[t][r] += user_nu ? p * p * s2[t][r] : p;
+        }
+    });
+  if (!fuse_waves<NT, NW>(f, wv, [&](int q) { return sms[q].f; })) return;
+  fuse_write<NT, M != 0>(a, w, f);
 }
 
-// PD systems per work item.
-template <int UT>
+// ---------------------------------------------------------------- kernels
+// PD systems per work item: a round of lane groups.
+template <int NT>
 constexpr int sym_pd_per() {
-  return UT == 32 ? 1 : 4;
+  return NT == 1 ? 4 : 1;
 }
 
-// One wave per workgroup, one work item per workgroup.  The LDS staging
-// (about 17 KB UT = 16, 17 KB PD / 35 KB FD at UT = 32) bounds occupancy to
-// two waves per SIMD or fewer, which the register target matches.
-template <int UT, int PREC, bool FD, bool MRC>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void eq_symbols_kernel(const FwdArgs a) {
-  __shared__ SymSmem<UT, FD ? 64 / UT : sym_pd_per<UT>()> sm;
-  if constexpr (FD) {
-    fd_sym_task<UT, PREC, MRC>(a, blockIdx.x, sm);
-  } else {
-    const int w0 = blockIdx.x * sym_pd_per<UT>();
-    pd_sym_task<UT, PREC, MRC>(a, w0, min(sym_pd_per<UT>(), a.W - w0), sm);
+template <int NT, int PREC>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void eq_symbols_pd_kernel(const FwdArgs a) {
+  __shared__ SymLds<NT, sym_pd_per<NT>()> sm;
+  const int w0 = blockIdx.x * sym_pd_per<NT>();
+  pd_sym_task<NT, PREC>(a, w0, min(sym_pd_per<NT>(), a.W - w0), sm);
+}
+
+template <int NT, int PREC, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 8))) void eq_symbols_fd_kernel(const FwdArgs a) {
+  __shared__ SymLds<NT, 4 / NT> sm[NW];
+  fd_sym_task<NT, PREC, NW>(a, blockIdx.x, sm, __builtin_amdgcn_readfirstlane(threadIdx.x / 64));
+}
+
+template <int NT, int PREC, int M>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void eq_direct_pd_kernel(const FwdArgs a) {
+  __shared__ DirectLds<NT> sm;
+  const int w0 = blockIdx.x * sym_pd_per<NT>();
+  pd_direct_task<NT, PREC, M>(a, w0, min(sym_pd_per<NT>(), a.W - w0), sm);
+}
+
+template <int NT, int PREC, int M, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 8))) void eq_direct_fd_kernel(const FwdArgs a) {
+  __shared__ DirectLds<NT> sm[NW];
+  fd_direct_task<NT, PREC, M, NW>(a, blockIdx.x, sm, __builtin_amdgcn_readfirstlane(threadIdx.x / 64));
+}
+
+template <int NT, int PREC, int NW>
+static void launch_fd(const FwdArgs &a, hipStream_t s) {
+  hipLaunchKernelGGL((eq_symbols_fd_kernel<NT, PREC, NW>), dim3(a.W), dim3(64 * NW), 0, s, a);
+}
+
+template <int NT, int PREC>
+static hipError_t launch_lmmse(const FwdArgs &a, bool fd, hipStream_t s) {
+  if (!fd) {
+    constexpr int per = sym_pd_per<NT>();
+    hipLaunchKernelGGL((eq_symbols_pd_kernel<NT, PREC>), dim3((a.W + per - 1) / per), dim3(64), 0, s, a);
+    return hipGetLastError();
   }
-}
-
-template <int UT, int PREC, bool FD>
-static hipError_t launch_sym_one(const FwdArgs &a, hipStream_t s) {
-  const int per = FD ? 1 : sym_pd_per<UT>();
-  const int grid = (a.W + per - 1) / per;
-  if (a.eqz == EQZ_MRC)
-    hipLaunchKernelGGL((eq_symbols_kernel<UT, PREC, FD, true>), dim3(grid), dim3(64), 0, s, a);
+  // waves per subcarrier: its rounds of clusters, at most 2 (16 users) or 4.
+  // 14 vectors of 1,200 subcarriers of B = 1024, C = 16, U = 32 take 282 us
+  // with one wave each, 230 with two, 191 with four (4,800 of them 716, 709,
+  // 684); of 9,600 of B = 256, C = 8, U = 16, 196, 182 and 182
+  const int rounds = (a.C * NT + 3) / 4;
+  if (rounds == 1)
+    launch_fd<NT, PREC, 1>(a, s);
+  else if (NT == 1 || rounds <= 3)
+    launch_fd<NT, PREC, 2>(a, s);
   else
-    hipLaunchKernelGGL((eq_symbols_kernel<UT, PREC, FD, false>), dim3(grid), dim3(64), 0, s, a);
+    launch_fd<NT, PREC, NT == 1 ? 2 : 4>(a, s);
   return hipGetLastError();
 }
 
-template <int UT, bool FD>
-static hipError_t launch_sym_prec(const FwdArgs &a, int prec, hipStream_t s) {
-  return prec == PREC_FP32 ? launch_sym_one<UT, PREC_FP32, FD>(a, s) : launch_sym_one<UT, PREC_BF16X3_NR, FD>(a, s);
-}
-
-template <int UT, int PREC, bool FD, int M>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void eq_symbols_lama_kernel(const FwdArgs a) {
-  __shared__ SymSmem<UT, FD ? 64 / UT : sym_pd_per<UT>()> sm;
-  if constexpr (FD) {
-    fd_sym_lama_task<UT, PREC, M>(a, blockIdx.x, sm);
+template <int NT, int PREC, int M>
+static hipError_t launch_direct(const FwdArgs &a, bool fd, hipStream_t s) {
+  if (!fd) {
+    constexpr int per = sym_pd_per<NT>();
+    hipLaunchKernelGGL((eq_direct_pd_kernel<NT, PREC, M>), dim3((a.W + per - 1) / per), dim3(64), 0, s, a);
+  } else if (a.C > 1) {
+    hipLaunchKernelGGL((eq_direct_fd_kernel<NT, PREC, M, 2>), dim3(a.W), dim3(128), 0, s, a);
   } else {
-    const int w0 = blockIdx.x * sym_pd_per<UT>();
-    pd_sym_lama_task<UT, PREC, M>(a, w0, min(sym_pd_per<UT>(), a.W - w0), sm);
+    hipLaunchKernelGGL((eq_direct_fd_kernel<NT, PREC, M, 1>), dim3(a.W), dim3(64), 0, s, a);
   }
+  return hipGetLastError();
 }
 
-template <int UT, int PREC, bool FD>
-static hipError_t launch_sym_lama_one(const FwdArgs &a, hipStream_t s) {
-  const int per = FD ? 1 : sym_pd_per<UT>();
-  const dim3 grid((a.W + per - 1) / per), block(64);
+template <int NT, int PREC>
+static hipError_t launch_tile(const FwdArgs &a, bool fd, bool lama, hipStream_t s) {
+  if (!lama) return a.eqz == EQZ_MRC ? launch_direct<NT, PREC, 0>(a, fd, s) : launch_lmmse<NT, PREC>(a, fd, s);
   switch (a.lama_m) {
-    case 2: hipLaunchKernelGGL((eq_symbols_lama_kernel<UT, PREC, FD, 2>), grid, block, 0, s, a); break;
-    case 4: hipLaunchKernelGGL((eq_symbols_lama_kernel<UT, PREC, FD, 4>), grid, block, 0, s, a); break;
-    case 8: hipLaunchKernelGGL((eq_symbols_lama_kernel<UT, PREC, FD, 8>), grid, block, 0, s, a); break;
+    case 2: return launch_direct<NT, PREC, 2>(a, fd, s);
+    case 4: return launch_direct<NT, PREC, 4>(a, fd, s);
+    case 8: return launch_direct<NT, PREC, 8>(a, fd, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
-template <int UT, bool FD>
-static hipError_t launch_sym_lama_prec(const FwdArgs &a, int prec, hipStream_t s) {
-  return prec == PREC_FP32 ? launch_sym_lama_one<UT, PREC_FP32, FD>(a, s)
-                           : launch_sym_lama_one<UT, PREC_BF16X3_NR, FD>(a, s);
-}
-
-hipError_t launch_symbols_lama(const FwdArgs &a, bool fd, int prec, hipStream_t s) {
+static hipError_t launch_any(const FwdArgs &a, bool fd, int prec, bool lama, hipStream_t s) {
   if (prec != PREC_FP32 && prec != PREC_BF16X3_NR) return hipErrorInvalidValue;
-  if (a.nsym < 1 || a.nsym > symbol_tile(a.U)) return hipErrorInvalidValue;
-  const int UT = ut_for(a.U);
-  if (UT == 16) return fd ? launch_sym_lama_prec<16, true>(a, prec, s) : launch_sym_lama_prec<16, false>(a, prec, s);
-  return fd ? launch_sym_lama_prec<32, true>(a, prec, s) : launch_sym_lama_prec<32, false>(a, prec, s);
+  if (a.nsym < 1 || a.nsym > kSymTile) return hipErrorInvalidValue;
+  if (ut_for(a.U) == 16)
+    return prec == PREC_FP32 ? launch_tile<1, PREC_FP32>(a, fd, lama, s) : launch_tile<1, PREC_BF16X3_NR>(a, fd, lama, s);
+  return prec == PREC_FP32 ? launch_tile<2, PREC_FP32>(a, fd, lama, s) : launch_tile<2, PREC_BF16X3_NR>(a, fd, lama, s);
 }
 
-int symbol_tile(int U) { return ut_for(U); }
+int symbol_tile(int) { return kSymTile; }
 
-hipError_t launch_symbols(const FwdArgs &a, bool fd, int prec, hipStream_t s) {
-  if (prec != PREC_FP32 && prec != PREC_BF16X3_NR) return hipErrorInvalidValue;
-  if (a.nsym < 1 || a.nsym > symbol_tile(a.U)) return hipErrorInvalidValue;
-  const int UT = ut_for(a.U);
-  if (UT == 16) return fd ? launch_sym_prec<16, true>(a, prec, s) : launch_sym_prec<16, false>(a, prec, s);
-  return fd ? launch_sym_prec<32, true>(a, prec, s) : launch_sym_prec<32, false>(a, prec, s);
-}
+hipError_t launch_symbols_lama(const FwdArgs &a, bool fd, int prec, hipStream_t s) { return launch_any(a, fd, prec, true, s); }
+
+hipError_t launch_symbols(const FwdArgs &a, bool fd, int prec, hipStream_t s) { return launch_any(a, fd, prec, false, s); }
 
 }  // namespace dbpeq
