@@ -183,7 +183,7 @@ eq_status eq_pd_noalloc(const eq_problem *p, const eq_c32 *H, const eq_c32 *y,
    Z [W][nsym][U] likewise; sigma2 [W][U] and info ([W] for PD, [W][C] for
    FD) as for eq_pd / eq_fd, which these equal vector by vector (nsym = 1 is
    the single-vector problem).  nsym in 1..EQ_MAX_SYM; the vectors are
-   processed in tiles of 16 (U <= 16) or 32 (U > 16), and each tile reads H
+   processed in tiles of 16 (PD with U > 16: 32), and each tile reads H
    once.  Precision EQ_FP32 or EQ_BF16X3 (the refining forms return
    EQ_ENOTSUP).  Same workspace as eq_pd / eq_fd. */
 eq_status eq_pd_sym(const eq_problem *p, int32_t nsym, const eq_c32 *H,

@@ -156,7 +156,7 @@ eq_status forward(const eq_problem *p, bool fd, const eq_c32 *H, const eq_c32 *y
 }
 
 // Several receive vectors per channel matrix: Y [W][nsym][B], Z [W][nsym][U].
-// Tiles of up to symbol_tile(U) vectors per launch pair (equaliser + FP64
+// Tiles of up to symbol_tile(U, fd) vectors per launch pair (equaliser + FP64
 // re-solve); every tile re-reads H.
 eq_status forward_sym(const eq_problem *p, bool fd, int32_t nsym, const eq_c32 *H, const eq_c32 *Y,
                       const float *nu, eq_c32 *Z, float *s2, int32_t *info, void *ws, size_t ws_bytes,
@@ -182,7 +182,7 @@ eq_status forward_sym(const eq_problem *p, bool fd, int32_t nsym, const eq_c32 *
   a.fb_list = reinterpret_cast<int32_t *>(reinterpret_cast<char *>(ws) + kWsHeader);
   a.ysw = (int64_t)nsym * p->B;
   a.zsw = (int64_t)nsym * p->U;
-  const int tile = symbol_tile(p->U);
+  const int tile = symbol_tile(p->U, fd);
   const int prec = p->precision == EQ_FP32 ? PREC_FP32 : PREC_BF16X3_NR;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   for (int s0 = 0; s0 < nsym; s0 += tile) {
@@ -225,7 +225,7 @@ eq_status forward_lama(const eq_problem *p, bool fd, int32_t t_max, int32_t qam_
 }
 
 // LAMA over several receive vectors: Y [W][nsym][B], Z and sigma2
-// [W][nsym][U]; tiles of up to symbol_tile(U) vectors, each reading H once.
+// [W][nsym][U]; tiles of up to symbol_tile(U, fd) vectors, each reading H once.
 eq_status forward_lama_sym(const eq_problem *p, bool fd, int32_t nsym, int32_t t_max, int32_t qam_order,
                            const eq_c32 *H, const eq_c32 *Y, const float *nu, eq_c32 *Z, float *s2, int32_t *info,
                            void *stream) {
@@ -253,7 +253,7 @@ eq_status forward_lama_sym(const eq_problem *p, bool fd, int32_t nsym, int32_t t
   a.lama_m = qam_order == 4 ? 2 : (qam_order == 16 ? 4 : 8);
   a.ysw = (int64_t)nsym * p->B;
   a.zsw = (int64_t)nsym * p->U;
-  const int tile = symbol_tile(p->U);
+  const int tile = symbol_tile(p->U, fd);
   const int prec = p->precision == EQ_FP32 ? PREC_FP32 : PREC_BF16X3_NR;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   for (int s0 = 0; s0 < nsym; s0 += tile) {

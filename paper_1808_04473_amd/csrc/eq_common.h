@@ -68,13 +68,13 @@ hipError_t launch_forward(const FwdArgs &a, bool fd, int prec, hipStream_t s);
 hipError_t launch_fp64_resolve(const FwdArgs &a, bool fd, hipStream_t s);
 hipError_t launch_zero_i32(int32_t *p, int n, hipStream_t s);
 hipError_t launch_probe_read(const void *buf, size_t bytes, float *sink, hipStream_t s);
-// several receive vectors per channel matrix: a.nsym <= symbol_tile(a.U)
+// several receive vectors per channel matrix: a.nsym <= symbol_tile(a.U, fd)
 hipError_t launch_symbols(const FwdArgs &a, bool fd, int prec, hipStream_t s);
-int symbol_tile(int U);
+int symbol_tile(int U, bool fd);
 // MRC (no factorisation): FP32 or split-BF16 Gram
 hipError_t launch_mrc(const FwdArgs &a, bool fd, int prec, hipStream_t s);
 // LAMA (Algorithm 1): FP32 or split-BF16 Gram; one receive vector, or a tile
-// of a.nsym <= symbol_tile(a.U) vectors per channel matrix
+// of a.nsym <= symbol_tile(a.U, fd) vectors per channel matrix
 hipError_t launch_lama(const FwdArgs &a, bool fd, int prec, hipStream_t s);
 hipError_t launch_symbols_lama(const FwdArgs &a, bool fd, int prec, hipStream_t s);
 

@@ -3,13 +3,13 @@
 // The OFDM symbols of one coherence interval share the channel, so the Gram
 // matrix of a subcarrier (PD) or cluster (FD) and its factor are formed once
 // and applied to every symbol; only the matched filter is formed per symbol.
-// The matched filters of a tile of up to 16 symbols, H_c^H [y_1 .. y_S], are a
-// second MFMA product in the same pass over H, and H and the receive vectors
-// are each read from HBM once per tile.
+// The matched filters of up to 16 symbols (PD with more than 16 users: 32),
+// H_c^H [y_1 .. y_S], are a second MFMA product in the same pass over H, and H
+// and the receive vectors are each read from HBM once per launch.
 //
 // Tile layout.  Everything runs in 16 x 16 tiles: NT = 1 or 2 tiles of users
-// (U <= 16, U <= 32) and one of symbols.  Lane (g, c) = (lane / 16, lane % 16)
-// loads rows of its group for user c (and 16 + c) of H and for symbol c: the
+// (U <= 16, U <= 32) and NC = 1 or 2 of symbols.  Lane (g, c) = (lane / 16, lane % 16)
+// loads rows of its group for user c (and 16 + c) of H and symbol c (and 16 + c): the
 // A and B operands of the products over rows.  Of the Gram matrix only the
 // blocks (0, 0), (1, 0) and (1, 1) are formed (seven real FP32 products at 32
 // users where full 32 x 32 tiles take eight, and twice the symbols).  Results
@@ -35,7 +35,12 @@
 
 namespace dbpeq {
 
-constexpr int kSymTile = 16;  // symbols per launch
+// Symbol tiles per launch.  PD at 32 users reads H once for 32 symbols: two
+// launches of 16 each took 15-25% longer (MRC of 24 vectors, 1,200 subcarriers
+// of B = 1024: 228 against 185 us).  The solves bound FD, where a second
+// symbol tile in LDS would cost half the waves (two launches for 17 to 32
+// vectors take 0.4 to 0.75 of the time of the former one launch).
+constexpr int sym_tiles(int UT, bool fd) { return UT == 32 && !fd ? 2 : 1; }
 
 // ---------------------------------------------------------------- streaming
 // Rows per lane group and row block, and row e of group g within the block
@@ -53,7 +58,7 @@ __device__ __forceinline__ constexpr int tile_row(int e, int g) {
 
 struct TileSlot {
   float2 h[8];  // row e of the group: h[e], or h[2 e] and h[2 e + 1] (users c, 16 + c)
-  float2 y[8];
+  float2 y[8];  // row e: y[NC e + n] (symbol 16 n + c)
   int s;
   int nv;     // rows from the group's first to the end of the system
   bool full;  // the whole block is inside the system
@@ -63,7 +68,7 @@ struct TileSlot {
 template <int NT>
 struct TileOff {
   unsigned h, h1;  // users c and 16 + c of the group's first row, or out of range
-  unsigned y;      // the same row of symbol c < nsym, else out of range
+  unsigned y, y1;  // the same row of symbols c and 16 + c < nsym, else out of range
   int row;         // the group's first row within a block
 };
 
@@ -75,6 +80,7 @@ __device__ __forceinline__ TileOff<NT> tile_offsets(int U, int B, int nsym) {
   o.h = c < U ? (unsigned)((row * U + c) * 8) : kOutOfRange;
   o.h1 = 16 + c < U ? (unsigned)((row * U + 16 + c) * 8) : kOutOfRange;
   o.y = c < nsym ? (unsigned)(((unsigned)c * (unsigned)B + (unsigned)row) * 8u) : kOutOfRange;
+  o.y1 = 16 + c < nsym ? (unsigned)((16u + (unsigned)c) * (unsigned)B + (unsigned)row) * 8u : kOutOfRange;
   o.row = row;
   return o;
 }
@@ -87,7 +93,7 @@ __device__ __forceinline__ TileOff<NT> tile_offsets(int U, int B, int nsym) {
 // descriptor (the 16-byte loads are those of full blocks).  The loads of Y
 // use the default policy: they share cache lines (with the nontemporal one
 // the lines were fetched again, 22-28% more bytes than the algorithm reads).
-template <int NT>
+template <int NT, int NC>
 __device__ __forceinline__ void load_tile_slot(TileSlot &b, const TileOff<NT> &lo, const float2 *__restrict__ Hw,
                                                const float2 *__restrict__ Yw, int U, int B, int nsym, int rb,
                                                int r0, int r1, bool live) {
@@ -108,18 +114,21 @@ __device__ __forceinline__ void load_tile_slot(TileSlot &b, const TileOff<NT> &l
       b.h[2 * e + 1] = buf_ld2<kLoadLast>(rh, lo.h1 + rowb + tile_row<NT>(e, 0) * step);
     }
   }
-  const unsigned yb = lo.y + (unsigned)((rb - r0) * 8);
+  const unsigned yb = (unsigned)((rb - r0) * 8);
   b.full = live && rb + 4 * E <= r1;
   if (NT == 1 && b.full) {
 #pragma unroll
     for (int e = 0; e < E; e += 2) {
-      const f4 v = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(ry, yb + 8u * tile_row<NT>(e, 0), 0, kLoadKeep));
+      const f4 v = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(ry, lo.y + yb + 8u * tile_row<NT>(e, 0), 0, kLoadKeep));
       b.y[e] = make_float2(v.x, v.y);
       b.y[e + 1] = make_float2(v.z, v.w);
     }
   } else {
 #pragma unroll
-    for (int e = 0; e < E; ++e) b.y[e] = buf_ld2<kLoadKeep>(ry, yb + 8u * tile_row<NT>(e, 0));
+    for (int e = 0; e < E; ++e) {
+      b.y[NC * e] = buf_ld2<kLoadKeep>(ry, lo.y + yb + 8u * tile_row<NT>(e, 0));
+      if constexpr (NC == 2) b.y[2 * e + 1] = buf_ld2<kLoadKeep>(ry, lo.y1 + yb + 8u * tile_row<NT>(e, 0));
+    }
   }
   b.nv = r1 - (rb + lo.row);
 }
@@ -137,19 +146,21 @@ struct TileAcc {
 //   k1 = (Hr - Hi)^T Yr,  k2 = Hr^T (Yi - Yr),  k3 = Hi^T (Yr + Yi),
 //   Re M = k1 + k3,   Im M = k1 + k2;
 // the split-BF16 form accumulates Re M in k1 and Im M in k2 directly.
-template <int NT>
+template <int NT, int NC>
 struct TileMf {
-  f4 k1[NT], k2[NT], k3[NT];
+  f4 k1[NT][NC], k2[NT][NC], k3[NT][NC];
 };
 
-template <int NT>
-__device__ __forceinline__ void tile_zero(TileAcc<NT> &a, TileMf<NT> &m) {
+template <int NT, int NC>
+__device__ __forceinline__ void tile_zero(TileAcc<NT> &a, TileMf<NT, NC> &m) {
   const f4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int b = 0; b < 2 * NT - 1; ++b) a.rr[b] = a.ri[b] = a.ii[b] = z;
   a.ir = z;
 #pragma unroll
-  for (int t = 0; t < NT; ++t) m.k1[t] = m.k2[t] = m.k3[t] = z;
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int n = 0; n < NC; ++n) m.k1[t][n] = m.k2[t][n] = m.k3[t][n] = z;
 }
 
 // BF16 operands of one row block: 8 rows per lane at NT = 1 (K = 32), 4 at
@@ -174,29 +185,42 @@ __device__ __forceinline__ f4 mma_split(const Split<NT> &a, const Split<NT> &b, 
   return mma16(a.h, b.h, c);
 }
 
-template <int NT, int PREC>
-__device__ __forceinline__ void gram_mf_tile(TileSlot &sl, TileAcc<NT> &acc, TileMf<NT> &m) {
+template <int NT, int NC, int PREC>
+__device__ __forceinline__ void gram_mf_tile(TileSlot &sl, TileAcc<NT> &acc, TileMf<NT, NC> &m) {
   constexpr int E = kRows<NT>;
   if (!sl.full) {
 #pragma unroll
     for (int e = 0; e < E; ++e)
-      if (tile_row<NT>(e, 0) >= sl.nv) sl.y[e] = make_float2(0.f, 0.f);
+      if (tile_row<NT>(e, 0) >= sl.nv)
+#pragma unroll
+        for (int n = 0; n < NC; ++n) sl.y[NC * e + n] = make_float2(0.f, 0.f);
   }
   if constexpr (PREC == PREC_FP32) {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      const float2 y = sl.y[e];
-      const float ydif = y.y - y.x, ysum = y.x + y.y;
+      float yre[NC], ydif[NC], ysum[NC];
+#pragma unroll
+      for (int n = 0; n < NC; ++n) {
+        const float2 y = sl.y[NC * e + n];
+        yre[n] = y.x;
+        ydif[n] = y.y - y.x;
+        ysum[n] = y.x + y.y;
+      }
       float sum[NT];
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         const float2 h = sl.h[NT * e + t];
         sum[t] = h.x + h.y;
         acc.rr[2 * t] = mma32(sum[t], sum[t], acc.rr[2 * t]);
-        m.k1[t] = mma32(h.x - h.y, y.x, m.k1[t]);
+        m.k1[t][0] = mma32(h.x - h.y, yre[0], m.k1[t][0]);
         acc.ri[2 * t] = mma32(h.x, h.y, acc.ri[2 * t]);
-        m.k2[t] = mma32(h.x, ydif, m.k2[t]);
-        m.k3[t] = mma32(h.y, ysum, m.k3[t]);
+        m.k2[t][0] = mma32(h.x, ydif[0], m.k2[t][0]);
+        m.k3[t][0] = mma32(h.y, ysum[0], m.k3[t][0]);
+        if constexpr (NC == 2) {
+          m.k1[t][1] = mma32(h.x - h.y, yre[1], m.k1[t][1]);
+          m.k2[t][1] = mma32(h.x, ydif[1], m.k2[t][1]);
+          m.k3[t][1] = mma32(h.y, ysum[1], m.k3[t][1]);
+        }
       }
       if constexpr (NT == 2) {
         const float2 h0 = sl.h[2 * e], h1 = sl.h[2 * e + 1];
@@ -207,17 +231,20 @@ __device__ __forceinline__ void gram_mf_tile(TileSlot &sl, TileAcc<NT> &acc, Til
     }
   } else {
     static_assert(PREC == PREC_BF16X3_NR, "one-pass forms only");
-    Split<NT> hr[NT], hi[NT], yr, yi, ny;
+    Split<NT> hr[NT], hi[NT], yr[NC], yi[NC], ny[NC];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      const float2 y = sl.y[e];
-      yr.h[e] = (__bf16)y.x;
-      yr.l[e] = (__bf16)(y.x - (float)yr.h[e]);
-      yi.h[e] = (__bf16)y.y;
-      yi.l[e] = (__bf16)(y.y - (float)yi.h[e]);
-      // round-to-nearest-even is symmetric: the split of -yr is the negated split
-      ny.h[e] = -yr.h[e];
-      ny.l[e] = -yr.l[e];
+#pragma unroll
+      for (int n = 0; n < NC; ++n) {
+        const float2 y = sl.y[NC * e + n];
+        yr[n].h[e] = (__bf16)y.x;
+        yr[n].l[e] = (__bf16)(y.x - (float)yr[n].h[e]);
+        yi[n].h[e] = (__bf16)y.y;
+        yi[n].l[e] = (__bf16)(y.y - (float)yi[n].h[e]);
+        // round-to-nearest-even is symmetric: the split of -yr is the negated split
+        ny[n].h[e] = -yr[n].h[e];
+        ny[n].l[e] = -yr[n].l[e];
+      }
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         const float2 h = sl.h[NT * e + t];
@@ -230,12 +257,15 @@ __device__ __forceinline__ void gram_mf_tile(TileSlot &sl, TileAcc<NT> &acc, Til
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       acc.rr[2 * t] = mma_split<NT>(hr[t], hr[t], acc.rr[2 * t]);
-      m.k1[t] = mma_split<NT>(hr[t], yr, m.k1[t]);
       acc.ri[2 * t] = mma_split<NT>(hr[t], hi[t], acc.ri[2 * t]);
-      m.k2[t] = mma_split<NT>(hr[t], yi, m.k2[t]);
       acc.ii[2 * t] = mma_split<NT>(hi[t], hi[t], acc.ii[2 * t]);
-      m.k1[t] = mma_split<NT>(hi[t], yi, m.k1[t]);
-      m.k2[t] = mma_split<NT>(hi[t], ny, m.k2[t]);
+#pragma unroll
+      for (int n = 0; n < NC; ++n) {
+        m.k1[t][n] = mma_split<NT>(hr[t], yr[n], m.k1[t][n]);
+        m.k2[t][n] = mma_split<NT>(hr[t], yi[n], m.k2[t][n]);
+        m.k1[t][n] = mma_split<NT>(hi[t], yi[n], m.k1[t][n]);
+        m.k2[t][n] = mma_split<NT>(hi[t], ny[n], m.k2[t][n]);
+      }
     }
     if constexpr (NT == 2) {
       acc.rr[1] = mma_split<NT>(hr[1], hr[0], acc.rr[1]);
@@ -279,12 +309,13 @@ __device__ __forceinline__ void tile_gram(float *scratch, const TileAcc<NT> &a, 
   }
 }
 
-template <int NT, int PREC>
-__device__ __forceinline__ void tile_mf(const TileMf<NT> &m, Tiles<NT> &M) {
+// Matched filters of symbol tile n.
+template <int NT, int PREC, int NC>
+__device__ __forceinline__ void tile_mf(const TileMf<NT, NC> &m, int n, Tiles<NT> &M) {
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    M.re[t] = PREC == PREC_FP32 ? m.k1[t] + m.k3[t] : m.k1[t];
-    M.im[t] = PREC == PREC_FP32 ? m.k1[t] + m.k2[t] : m.k2[t];
+    M.re[t] = PREC == PREC_FP32 ? m.k1[t][n] + m.k3[t][n] : m.k1[t][n];
+    M.im[t] = PREC == PREC_FP32 ? m.k1[t][n] + m.k2[t][n] : m.k2[t][n];
   }
 }
 
@@ -294,12 +325,12 @@ __device__ __forceinline__ void tile_mf(const TileMf<NT> &m, Tiles<NT> &M) {
 // 7.5 KB): with four nothing was faster and LAMA lost a wave (104 against
 // 98 us), and one stream over all rounds of an FD wave, which loads the next
 // round's first rows during a solve, was 2-8% slower.
-template <int NT, int PREC, class Seg, class Done>
+template <int NT, int NC, int PREC, class Seg, class Done>
 __device__ __forceinline__ void gram_mf_stream(int ns, int U, int B, int nsym, Seg seg, Done done) {
   constexpr int RPB = 4 * kRows<NT>;
   TileAcc<NT> acc;
-  TileMf<NT> m;
-  tile_zero<NT>(acc, m);
+  TileMf<NT, NC> m;
+  tile_zero(acc, m);
   const TileOff<NT> lo = tile_offsets<NT>(U, B, nsym);
   SysRef cur;
   seg(0, cur.Hw, cur.yw, cur.r0, cur.r1);
@@ -309,7 +340,7 @@ __device__ __forceinline__ void gram_mf_stream(int ns, int U, int B, int nsym, S
   bool more = true;
   auto issue = [&](TileSlot &sl) -> bool {
     const bool valid = more;
-    load_tile_slot<NT>(sl, lo, cur.Hw, cur.yw, U, B, nsym, crb, cur.r0, cur.r1, valid);
+    load_tile_slot<NT, NC>(sl, lo, cur.Hw, cur.yw, U, B, nsym, crb, cur.r0, cur.r1, valid);
     sl.s = cur.s;
     sl.last = crb + RPB >= cur.r1;
     if (valid) {
@@ -326,10 +357,10 @@ __device__ __forceinline__ void gram_mf_stream(int ns, int U, int B, int nsym, S
     return valid;
   };
   auto consume = [&](TileSlot &b) {
-    gram_mf_tile<NT, PREC>(b, acc, m);
+    gram_mf_tile<NT, NC, PREC>(b, acc, m);
     if (b.last) {
       done(b.s, acc, m);
-      tile_zero<NT>(acc, m);
+      tile_zero(acc, m);
     }
   };
   TileSlot sa, sb;
@@ -462,18 +493,16 @@ __device__ __forceinline__ auto fd_seg(const FwdArgs &a, int w, Cluster cluster)
 // (accumulator layout, one 16-byte word per lane and tile part).  At 16 users
 // the matched filters of the round's four systems stay in 32 registers: 8 KB
 // of LDS instead of 16 (LDS comes in units of 1,280 bytes: 9 waves per CU).
-template <int NT, int NSLOT>
-struct SymLds;
-template <int NSLOT>
-struct SymLds<1, NSLOT> {
-  static constexpr int NS = NSLOT;
-  float2 A[NS * kSlot<16>];
-};
-template <int NSLOT>
-struct SymLds<2, NSLOT> {
+template <int NT, int NSLOT, int NC = 1>
+struct SymLds {
   static constexpr int NS = NSLOT;
   float2 A[NS * kSlot<32>];
-  f4 M[NS][4][64];
+  f4 M[NS][NC][4][64];
+};
+template <int NSLOT>
+struct SymLds<1, NSLOT, 1> {
+  static constexpr int NS = NSLOT;
+  float2 A[NS * kSlot<16>];
 };
 
 // Matched filters of the systems of a round.
@@ -482,9 +511,9 @@ struct SymMf {
   Tiles<1> m[NT == 1 ? NS : 1];
 };
 
-template <int NT, int PREC, class SM>
+template <int NT, int NC, int PREC, class SM>
 __device__ __forceinline__ void store_system(SM &sm, SymMf<NT, SM::NS> &mf, int s, const TileAcc<NT> &acc,
-                                             const TileMf<NT> &m) {
+                                             const TileMf<NT, NC> &m) {
   const int lane = lane_id();
   const int kk = lane / 16, c = lane % 16;
   float2 *As = sm.A + s * kSlot<16 * NT>;
@@ -495,17 +524,20 @@ __device__ __forceinline__ void store_system(SM &sm, SymMf<NT, SM::NS> &mf, int 
   for (int b = 0; b < 2 * NT - 1; ++b)
 #pragma unroll
     for (int r = 0; r < 4; ++r) blk_el(As, b, 4 * kk + r, c) = make_float2(G.re[b][r], G.im[b][r]);
-  Tiles<NT> M;
-  tile_mf<NT, PREC>(m, M);
-  if constexpr (NT == 1) {
-    sfor<SM::NS>([&](auto Q) {
-      if (s == Q) mf.m[Q] = M;
-    });
-  } else {
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      sm.M[s][2 * t][lane] = M.re[t];
-      sm.M[s][2 * t + 1][lane] = M.im[t];
+  for (int n = 0; n < NC; ++n) {
+    Tiles<NT> M;
+    tile_mf<NT, PREC>(m, n, M);
+    if constexpr (NT == 1) {
+      sfor<SM::NS>([&](auto Q) {
+        if (s == Q) mf.m[Q] = M;
+      });
+    } else {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        sm.M[s][n][2 * t][lane] = M.re[t];
+        sm.M[s][n][2 * t + 1][lane] = M.im[t];
+      }
     }
   }
 }
@@ -539,10 +571,10 @@ __device__ __forceinline__ void block_mul(float2 *As, int b, const f4 &mr, const
   }
 }
 
-// Z = X^H (X M) for slot q and every symbol of the tile, the whole wave on one
+// Z = X^H (X M) for slot q and every symbol of tile n, the whole wave on one
 // system.
 template <int NT, class SM>
-__device__ __forceinline__ void sym_apply(SM &sm, const Tiles<1> &m0, int q, Tiles<NT> &Z) {
+__device__ __forceinline__ void sym_apply(SM &sm, const Tiles<1> &m0, int q, int n, Tiles<NT> &Z) {
   constexpr bool GAUSS = NT == 1;
   const int lane = lane_id();
   float2 *As = sm.A + q * kSlot<16 * NT>;
@@ -555,8 +587,8 @@ __device__ __forceinline__ void sym_apply(SM &sm, const Tiles<1> &m0, int q, Til
       mr[t] = m0.re[0];
       mi[t] = m0.im[0];
     } else {
-      mr[t] = sm.M[q][2 * t][lane];
-      mi[t] = sm.M[q][2 * t + 1][lane];
+      mr[t] = sm.M[q][n][2 * t][lane];
+      mi[t] = sm.M[q][n][2 * t + 1][lane];
     }
   }
   auto out = [&](f4 &re, f4 &im) {
@@ -596,14 +628,15 @@ __device__ __forceinline__ void to_tiles(float v, int q, f4 (&o)[NT]) {
 }
 
 // PD: systems w0 .. w0+nvalid-1, one per lane group.
-template <int NT, int PREC, class SM>
+template <int NT, int NC, int PREC, class SM>
 __device__ __forceinline__ void pd_sym_task(const FwdArgs &a, int w0, int nvalid, SM &sm) {
   constexpr int UT = 16 * NT;
   const int lane = lane_id();
   const int g = lane / UT, i = lane % UT;
   SymMf<NT, SM::NS> mf;
-  gram_mf_stream<NT, PREC>(nvalid, a.U, a.B, a.nsym, pd_seg(a, w0),
-                           [&](int s, const TileAcc<NT> &acc, const TileMf<NT> &m) { store_system<NT, PREC>(sm, mf, s, acc, m); });
+  gram_mf_stream<NT, NC, PREC>(nvalid, a.U, a.B, a.nsym, pd_seg(a, w0), [&](int s, const TileAcc<NT> &acc, const TileMf<NT, NC> &m) {
+    store_system<NT, NC, PREC>(sm, mf, s, acc, m);
+  });
   wave_sync();
   LocalSolve<UT> r;
   solve_slot<UT, true, SM::NS, false>(r, sm.A, slot_of<SM>(g), i, make_float2(0.f, 0.f), a.rho, a.U);
@@ -620,18 +653,21 @@ __device__ __forceinline__ void pd_sym_task(const FwdArgs &a, int w0, int nvalid
   sfor<SM::NS>([&](auto Q) {
     constexpr int q = Q;
     if (q >= nvalid) return;
-    Tiles<NT> Z;
-    sym_apply<NT>(sm, mf.m[NT == 1 ? q : 0], q, Z);
     f4 k[NT];
     to_tiles<NT>(kz, q, k);
-    float2 *zw = a.z + (size_t)(w0 + q) * a.zsw + (size_t)c * a.U;
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+    for (int n = 0; n < NC; ++n) {
+      Tiles<NT> Z;
+      sym_apply<NT>(sm, mf.m[NT == 1 ? q : 0], q, n, Z);
+      float2 *zw = a.z + (size_t)(w0 + q) * a.zsw + (size_t)(16 * n + c) * a.U;
 #pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        const int u = 16 * t + 4 * kk + rr;
-        if (c < a.nsym && u < a.U) zw[u] = make_float2(Z.re[t][rr] * k[t][rr], Z.im[t][rr] * k[t][rr]);
-      }
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) {
+          const int u = 16 * t + 4 * kk + rr;
+          if (16 * n + c < a.nsym && u < a.U) zw[u] = make_float2(Z.re[t][rr] * k[t][rr], Z.im[t][rr] * k[t][rr]);
+        }
+    }
   });
   if (live) {
     if (i < a.U && a.s2) a.s2[(size_t)w * a.U + i] = r.bad ? nanv : a.n0 * r.d * ku;
@@ -660,8 +696,8 @@ __device__ __forceinline__ void fd_sym_task(const FwdArgs &a, int w, SM *sms, in
   for (int base = wv * NSYS; base < C; base += NW * NSYS) {
     const int nvalid = min(NSYS, C - base);
     SymMf<NT, SM::NS> mf;
-    gram_mf_stream<NT, PREC>(nvalid, a.U, a.B, a.nsym, fd_seg(a, w, [base](int s) { return base + s; }),
-                             [&](int s, const TileAcc<NT> &acc, const TileMf<NT> &m) { store_system<NT, PREC>(sm, mf, s, acc, m); });
+    gram_mf_stream<NT, 1, PREC>(nvalid, a.U, a.B, a.nsym, fd_seg(a, w, [base](int s) { return base + s; }),
+                             [&](int s, const TileAcc<NT> &acc, const TileMf<NT, 1> &m) { store_system<NT, 1, PREC>(sm, mf, s, acc, m); });
     wave_sync();
     LocalSolve<UT> r;
     solve_slot<UT, true, SM::NS, false>(r, sm.A, g, i, make_float2(0.f, 0.f), a.rho, a.U);
@@ -685,7 +721,7 @@ __device__ __forceinline__ void fd_sym_task(const FwdArgs &a, int w, SM *sms, in
       constexpr int q = Q;
       if (q >= nvalid) return;
       Tiles<NT> Z;
-      sym_apply<NT>(sm, mf.m[NT == 1 ? q : 0], q, Z);
+      sym_apply<NT>(sm, mf.m[NT == 1 ? q : 0], q, 0, Z);
       f4 wq[NT];
       to_tiles<NT>(pz, q, wq);
 #pragma unroll
@@ -876,55 +912,60 @@ struct DirectLds {
 };
 
 // One system (PD): estimates and variances to their rows.
-template <int NT, int PREC, int M>
+template <int NT, int NC, int PREC, int M>
 __device__ __forceinline__ void pd_direct_task(const FwdArgs &a, int w0, int nvalid, DirectLds<NT> &sm) {
   const int lane = lane_id();
   const int kk = lane / 16, c = lane % 16;
   const float nanv = __int_as_float(0x7fc00000);
-  gram_mf_stream<NT, PREC>(nvalid, a.U, a.B, a.nsym, pd_seg(a, w0), [&](int s, const TileAcc<NT> &acc, const TileMf<NT> &m) {
+  gram_mf_stream<NT, NC, PREC>(nvalid, a.U, a.B, a.nsym, pd_seg(a, w0), [&](int s, const TileAcc<NT> &acc, const TileMf<NT, NC> &m) {
     const int w = w0 + s;
     Tiles<2 * NT - 1> G;
-    Tiles<NT> Y, Z;
     tile_gram<NT, PREC>(sm.f, acc, G);
-    tile_mf<NT, PREC>(m, Y);
-    f4 s2[NT];
+    TileMrc<NT> o;
+    Tiles<1> T;
     int code;
-    bool out_nan;
     if constexpr (M == 0) {
-      const TileMrc<NT> o = tile_mrc<NT>(G, a.U, a.n0, a.es);
+      o = tile_mrc<NT>(G, a.U, a.n0, a.es);
       code = o.bad ? -1 : o.fail;
-      out_nan = code != 0;
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        Z.re[t] = Y.re[t] * o.inv[t];
-        Z.im[t] = Y.im[t] * o.inv[t];
-        s2[t] = o.s2[t];
-      }
     } else {
-      Tiles<1> T;
       tile_turn<NT>(sm.f, G, T);
-      out_nan = tiles_bad<2 * NT - 1>(G);
-      code = out_nan ? -1 : 0;
-      const float tau =
-          tile_lama<NT, M>(G, T, Y, a.U, a.n0, (float)a.U / (float)a.B, a.es, a.lama_t, Z);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) s2[t] = tau;
+      code = tiles_bad<2 * NT - 1>(G) ? -1 : 0;
     }
-    const size_t ob = (size_t)w * a.zsw + (size_t)c * a.U;
+    const bool out_nan = code != 0;
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+    for (int n = 0; n < NC; ++n) {
+      Tiles<NT> Y, Z;
+      tile_mf<NT, PREC>(m, n, Y);
+      f4 s2[NT];
+      if constexpr (M == 0) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int u = 16 * t + 4 * kk + r;
-        if (u < a.U) {
-          const float v = out_nan ? nanv : s2[t][r];
-          if (c < a.nsym) {
-            a.z[ob + u] = out_nan ? make_float2(nanv, nanv) : make_float2(Z.re[t][r], Z.im[t][r]);
-            if (M != 0 && a.s2) a.s2[ob + u] = v;
-          }
-          if (M == 0 && c == 0 && a.s2) a.s2[(size_t)w * a.U + u] = v;
+        for (int t = 0; t < NT; ++t) {
+          Z.re[t] = Y.re[t] * o.inv[t];
+          Z.im[t] = Y.im[t] * o.inv[t];
+          s2[t] = o.s2[t];
         }
+      } else {
+        const float tau = tile_lama<NT, M>(G, T, Y, a.U, a.n0, (float)a.U / (float)a.B, a.es, a.lama_t, Z);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) s2[t] = tau;
       }
+      const int sym = 16 * n + c;
+      const size_t ob = (size_t)w * a.zsw + (size_t)sym * a.U;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int u = 16 * t + 4 * kk + r;
+          if (u < a.U) {
+            const float v = out_nan ? nanv : s2[t][r];
+            if (sym < a.nsym) {
+              a.z[ob + u] = out_nan ? make_float2(nanv, nanv) : make_float2(Z.re[t][r], Z.im[t][r]);
+              if (M != 0 && a.s2) a.s2[ob + u] = v;
+            }
+            if (M == 0 && sym == 0 && a.s2) a.s2[(size_t)w * a.U + u] = v;
+          }
+        }
+    }
     if (lane == 0 && a.info) a.info[w] = code;
   });
 }
@@ -944,12 +985,12 @@ __device__ __forceinline__ void fd_direct_task(const FwdArgs &a, int w, DirectLd
   const int ncl = wv < C ? (C - wv + NW - 1) / NW : 0;
   auto cluster = [wv](int s) { return wv + NW * s; };
   if (ncl > 0)
-    gram_mf_stream<NT, PREC>(ncl, a.U, a.B, a.nsym, fd_seg(a, w, cluster), [&](int s, const TileAcc<NT> &acc, const TileMf<NT> &m) {
+    gram_mf_stream<NT, 1, PREC>(ncl, a.U, a.B, a.nsym, fd_seg(a, w, cluster), [&](int s, const TileAcc<NT> &acc, const TileMf<NT, 1> &m) {
       const int c = cluster(s);
       Tiles<2 * NT - 1> G;
       Tiles<NT> Y, Z;
       tile_gram<NT, PREC>(sm.f, acc, G);
-      tile_mf<NT, PREC>(m, Y);
+      tile_mf<NT, PREC>(m, 0, Y);
       f4 s2[NT];
       int code;
       if constexpr (M == 0) {
@@ -1005,11 +1046,11 @@ constexpr int sym_pd_per() {
   return NT == 1 ? 4 : 1;
 }
 
-template <int NT, int PREC>
+template <int NT, int NC, int PREC>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void eq_symbols_pd_kernel(const FwdArgs a) {
-  __shared__ SymLds<NT, sym_pd_per<NT>()> sm;
+  __shared__ SymLds<NT, sym_pd_per<NT>(), NC> sm;
   const int w0 = blockIdx.x * sym_pd_per<NT>();
-  pd_sym_task<NT, PREC>(a, w0, min(sym_pd_per<NT>(), a.W - w0), sm);
+  pd_sym_task<NT, NC, PREC>(a, w0, min(sym_pd_per<NT>(), a.W - w0), sm);
 }
 
 template <int NT, int PREC, int NW>
@@ -1018,11 +1059,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 8)))
   fd_sym_task<NT, PREC, NW>(a, blockIdx.x, sm, __builtin_amdgcn_readfirstlane(threadIdx.x / 64));
 }
 
-template <int NT, int PREC, int M>
+template <int NT, int NC, int PREC, int M>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void eq_direct_pd_kernel(const FwdArgs a) {
   __shared__ DirectLds<NT> sm;
   const int w0 = blockIdx.x * sym_pd_per<NT>();
-  pd_direct_task<NT, PREC, M>(a, w0, min(sym_pd_per<NT>(), a.W - w0), sm);
+  pd_direct_task<NT, NC, PREC, M>(a, w0, min(sym_pd_per<NT>(), a.W - w0), sm);
 }
 
 template <int NT, int PREC, int M, int NW>
@@ -1040,7 +1081,11 @@ template <int NT, int PREC>
 static hipError_t launch_lmmse(const FwdArgs &a, bool fd, hipStream_t s) {
   if (!fd) {
     constexpr int per = sym_pd_per<NT>();
-    hipLaunchKernelGGL((eq_symbols_pd_kernel<NT, PREC>), dim3((a.W + per - 1) / per), dim3(64), 0, s, a);
+    const dim3 grid((a.W + per - 1) / per);
+    if (NT == 2 && a.nsym > 16)
+      hipLaunchKernelGGL((eq_symbols_pd_kernel<NT, NT, PREC>), grid, dim3(64), 0, s, a);
+    else
+      hipLaunchKernelGGL((eq_symbols_pd_kernel<NT, 1, PREC>), grid, dim3(64), 0, s, a);
     return hipGetLastError();
   }
   // waves per subcarrier: its rounds of clusters, at most 2 (16 users) or 4.
@@ -1061,7 +1106,11 @@ template <int NT, int PREC, int M>
 static hipError_t launch_direct(const FwdArgs &a, bool fd, hipStream_t s) {
   if (!fd) {
     constexpr int per = sym_pd_per<NT>();
-    hipLaunchKernelGGL((eq_direct_pd_kernel<NT, PREC, M>), dim3((a.W + per - 1) / per), dim3(64), 0, s, a);
+    const dim3 grid((a.W + per - 1) / per);
+    if (NT == 2 && a.nsym > 16)
+      hipLaunchKernelGGL((eq_direct_pd_kernel<NT, NT, PREC, M>), grid, dim3(64), 0, s, a);
+    else
+      hipLaunchKernelGGL((eq_direct_pd_kernel<NT, 1, PREC, M>), grid, dim3(64), 0, s, a);
   } else if (a.C > 1) {
     hipLaunchKernelGGL((eq_direct_fd_kernel<NT, PREC, M, 2>), dim3(a.W), dim3(128), 0, s, a);
   } else {
@@ -1081,15 +1130,15 @@ static hipError_t launch_tile(const FwdArgs &a, bool fd, bool lama, hipStream_t 
   }
 }
 
+int symbol_tile(int U, bool fd) { return 16 * sym_tiles(ut_for(U), fd); }
+
 static hipError_t launch_any(const FwdArgs &a, bool fd, int prec, bool lama, hipStream_t s) {
   if (prec != PREC_FP32 && prec != PREC_BF16X3_NR) return hipErrorInvalidValue;
-  if (a.nsym < 1 || a.nsym > kSymTile) return hipErrorInvalidValue;
+  if (a.nsym < 1 || a.nsym > symbol_tile(a.U, fd)) return hipErrorInvalidValue;
   if (ut_for(a.U) == 16)
     return prec == PREC_FP32 ? launch_tile<1, PREC_FP32>(a, fd, lama, s) : launch_tile<1, PREC_BF16X3_NR>(a, fd, lama, s);
   return prec == PREC_FP32 ? launch_tile<2, PREC_FP32>(a, fd, lama, s) : launch_tile<2, PREC_BF16X3_NR>(a, fd, lama, s);
 }
-
-int symbol_tile(int) { return kSymTile; }
 
 hipError_t launch_symbols_lama(const FwdArgs &a, bool fd, int prec, hipStream_t s) { return launch_any(a, fd, prec, true, s); }
 
