@@ -270,9 +270,8 @@ size_t bwd_ws_bytes(const eq_problem *p) {
   int spw;
   const int nt = backward_tasks(p->W > 0 ? p->W : 1, p->U, p->C, true, &spw);
   const int nt_pd = backward_tasks(p->W > 0 ? p->W : 1, p->U, p->C, false, &spw);
-  const size_t parts = (size_t)(((nt > nt_pd ? nt : nt_pd) + 63) / 64) * 64 * sizeof(float);
-  const size_t fwd = (size_t)(p->W > 0 ? p->W : 1) * p->C * p->U * 16;
-  return parts + fwd;
+  // the workgroups' shares of the N0 gradient
+  return (size_t)(((nt > nt_pd ? nt : nt_pd) + 63) / 64) * 64 * sizeof(float);
 }
 
 eq_status backward(const eq_problem *p, bool fd, const eq_c32 *H, const eq_c32 *y, const float *nu,

@@ -12,8 +12,8 @@
 //    (16x16x4 / 32x32x2), BF16 MFMA eight (16x16x32 / 32x32x16).
 //
 //  * solve layout: lane l works on system s = l / UT, row / column
-//    i = l % UT.  The Cholesky factor is held by rows (lane i owns row i of
-//    L), the inverse factor X = L^{-1} by columns (lane u owns column u), so
+//    i = l % UT.  Lane i owns row i of the Cholesky factor L and then, in the
+//    same registers, column i of X = L^{-1} (solve_slot), so
 //    diag(A^{-1})_u = sum_j |X_ju|^2 and z = X^H (L^{-1} m) need no
 //    cross-lane reduction.  Values move between lanes of a group by
 //    broadcasting one lane: a DPP row broadcast, after a v_permlane16_swap
@@ -94,11 +94,6 @@ template <int UT, int K>
 __device__ __forceinline__ float gbcast(float v) {
   return dpp<DPP_ROW_NEWBCAST + K % 16>(bpick<K>(bsrc<UT>(v)));
 }
-template <int UT, int K>
-__device__ __forceinline__ float2 gbcast2(float2 v) {
-  return make_float2(gbcast<UT, K>(v.x), gbcast<UT, K>(v.y));
-}
-
 // acc += (NEG ? -1 : 1) * src[lane K of this lane's DPP row] * b: one VOP2
 // FMAC whose src0 comes through a DPP row broadcast (src is a BSrc half, so
 // that K = group lane % 16).  Written as inline assembly because the
@@ -166,6 +161,12 @@ __device__ __forceinline__ bool gany(bool p) {
   const int s = lane_id() / UT;
   const unsigned long long gm = (UT == 64) ? ~0ull : ((1ull << UT) - 1ull) << (s * UT);
   return (m & gm) != 0ull;
+}
+
+// Sum over the four 16-lane groups, lane by lane of a group.
+__device__ __forceinline__ float groups_sum(float v) {
+  const BSrc r = bsrc<32>(v);
+  return xor32_sum(r.lo + r.hi);
 }
 
 // Sum over the 64/UT lanes that share a column in the streaming layout.
@@ -615,35 +616,6 @@ __device__ __forceinline__ void store_gram_packed(float2 *As, const Acc<UT> &acc
 // instead of rho, so that the matrix stays positive definite when rho = 0
 // (ZF).  That block is decoupled from the users' block, whose factor and
 // solves it leaves unchanged.
-template <int UT, int PREC>
-__device__ __forceinline__ void store_gram_shift(float2 (*As)[UT], const Acc<UT> &acc, float rho, int U = UT) {
-  constexpr int NR = UT == 16 ? 4 : 16;
-  const int lane = lane_id();
-  sfor<NR>([&](auto R) {
-    constexpr int r = R;
-    int i, j;
-    acc_pos<UT>(lane, r, i, j);
-    lds_el<UT>(As, i, j) = make_float2(0.f, acc.ri[r]);
-  });
-  __syncthreads();
-  float im[NR], re[NR];
-  sfor<NR>([&](auto R) {
-    constexpr int r = R;
-    int i, j;
-    acc_pos<UT>(lane, r, i, j);
-    const float rij = lds_el<UT>(As, j, i).y;  // (Hr^T Hi)[j][i]
-    im[r] = acc.ri[r] - rij;
-    re[r] = PREC == PREC_FP32 ? acc.rr[r] - acc.ri[r] - rij : acc.rr[r] + acc.ii[r];
-  });
-  __syncthreads();
-  sfor<NR>([&](auto R) {
-    constexpr int r = R;
-    int i, j;
-    acc_pos<UT>(lane, r, i, j);
-    lds_el<UT>(As, i, j) = make_float2(re[r] + (i == j ? (i < U ? rho : 1.f) : 0.f), im[r]);
-  });
-}
-
 template <int UT>
 __device__ __forceinline__ void store_identity(float2 (*As)[UT]) {
   for (int idx = lane_id(); idx < UT * UT; idx += 64) {
@@ -652,375 +624,21 @@ __device__ __forceinline__ void store_identity(float2 (*As)[UT]) {
   }
 }
 
-// ---------------------------------------------------------------- factor / solves
+// ---------------------------------------------------------------- triangular products
 // Keeps the scheduler from hoisting the broadcasts of later pivot steps above
 // the current one (which would keep hundreds of values live at once).
 __device__ __forceinline__ void step_fence() { __builtin_amdgcn_sched_barrier(0); }
 
-// Hides a register's value from common-subexpression elimination: the
-// inverse broadcasts the same (lane, register) pairs as the factorisation,
-// and reusing those would keep every broadcast of the factorisation live.
-__device__ __forceinline__ void opaque(float2 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
-
-// The same for a lane index: each phase of the solve compares it with the
-// step number, and sharing those lane masks between phases would keep dozens
-// of 64-bit masks live in scalar registers.
-__device__ __forceinline__ int opaque_idx(int i) {
-  asm volatile("" : "+v"(i));
-  return i;
-}
-
+// Column i of a UT x UT matrix in lane i.
 template <int UT>
-struct Factor {
-  float2 a[UT];   // row i of L (entries j <= i), lane i of the group
-  float2 x[UT];   // column i of X = L^{-1}
-  float dinv;     // 1 / L_ii of this lane's row
+struct Columns {
+  float2 x[UT];
 };
-
-// Step j of the right-looking Cholesky A = L L^H of the row held by each
-// lane: column j of L, then the update of the trailing columns j < k < KEND.
-template <int UT, int J, int KEND>
-__device__ __forceinline__ void chol_step(Factor<UT> &f, int i, int &fail) {
-  constexpr int j = J;
-  const float ajj = gbcast<UT, j>(f.a[j].x);
-  if (!(ajj > 0.f) && fail == 0) fail = j + 1;
-  // hardware reciprocal square root (about 1 ulp): 1/L_jj and L_jj = a_jj / sqrt(a_jj)
-  const float inv = __builtin_amdgcn_rsqf(ajj);
-  const float ljj = ajj * inv;
-  if (i == j) f.dinv = inv;
-  float2 lij = make_float2(f.a[j].x * inv, f.a[j].y * inv);
-  if (i == j) lij = make_float2(ljj, 0.f);
-  if (i < j) lij = make_float2(0.f, 0.f);
-  f.a[j] = lij;
-  const float2 lm = (i > j) ? lij : make_float2(0.f, 0.f);
-  // a_ik -= l_ij * conj(l_kj), with l_kj broadcast from lane k: the real
-  // part of l_kj for every k, then the imaginary part, so that no
-  // instruction reads an accumulator its predecessor wrote
-  const BSrc bx = bsrc<UT>(lij.x), by = bsrc<UT>(lij.y);
-  sfor<UT>([&](auto K) {
-    constexpr int k = K;
-    if constexpr (k > j && k < KEND) {
-      fmac_rowbcast<k % 16, true, k == j + 1 ? 4 : 0>(f.a[k].x, bpick<k>(bx), lm.x);
-      fmac_rowbcast<k % 16, true, 0>(f.a[k].y, bpick<k>(bx), lm.y);
-    }
-  });
-  sfor<UT>([&](auto K) {
-    constexpr int k = K;
-    if constexpr (k > j && k < KEND) {
-      fmac_rowbcast<k % 16, true, k == j + 1 ? 4 : 0>(f.a[k].x, bpick<k>(by), lm.y);
-      fmac_rowbcast<k % 16, false, 0>(f.a[k].y, bpick<k>(by), lm.x);
-    }
-  });
-  step_fence();
-}
-
-// Right-looking Cholesky A = L L^H of the row held by each lane.
-// Returns 0, or j+1 for the first pivot j that is not positive (or NaN).
-template <int UT>
-__device__ __forceinline__ int cholesky(Factor<UT> &f, int i) {
-  i = opaque_idx(i);
-  int fail = 0;
-  sfor<UT>([&](auto J) { chol_step<UT, J, UT>(f, i, fail); });
-  return fail;
-}
-
-// Lane u computes column u of X = L^{-1}:
-//   X_ju = (delta_ju - sum_{k<j} L_jk X_ku) / L_jj,
-// right-looking: once X_ju is final, every later row i subtracts L_ij X_ju
-// (L_ij broadcast from lane i), so each step has UT - 1 - j independent
-// accumulators instead of one long chain.  inv_step is step j, with the
-// update restricted to the rows j < i < IEND.
-template <int UT, int J, int IEND>
-__device__ __forceinline__ void inv_step(Factor<UT> &f) {
-  constexpr int j = J;
-  const float invj = gbcast<UT, j>(f.dinv);
-  f.x[j] = make_float2(f.x[j].x * invj, f.x[j].y * invj);
-  // x_i -= L_ij x_j: real part of L_ij for every i, then the imaginary part
-  const BSrc bx = bsrc<UT>(f.a[j].x), by = bsrc<UT>(f.a[j].y);
-  sfor<UT>([&](auto I) {
-    constexpr int i = I;
-    if constexpr (i > j && i < IEND) {
-      fmac_rowbcast<i % 16, true, i == j + 1 ? 4 : 0>(f.x[i].x, bpick<i>(bx), f.x[j].x);
-      fmac_rowbcast<i % 16, true, 0>(f.x[i].y, bpick<i>(bx), f.x[j].y);
-    }
-  });
-  sfor<UT>([&](auto I) {
-    constexpr int i = I;
-    if constexpr (i > j && i < IEND) {
-      fmac_rowbcast<i % 16, false, i == j + 1 ? 4 : 0>(f.x[i].x, bpick<i>(by), f.x[j].y);
-      fmac_rowbcast<i % 16, true, 0>(f.x[i].y, bpick<i>(by), f.x[j].x);
-    }
-  });
-  step_fence();
-}
-
-template <int UT>
-__device__ __forceinline__ void inverse_columns(Factor<UT> &f, int u) {
-  u = opaque_idx(u);
-#pragma unroll
-  for (int j = 0; j < UT; ++j) f.x[j] = make_float2(u == j ? 1.f : 0.f, 0.f);
-  sfor<UT>([&](auto J) { inv_step<UT, J, UT>(f); });
-}
-
-// The factorisation and inverse of a system whose rows KE..UT-1 are padding
-// (users past U: identity rows of A, so identity rows of L and X): the first
-// KE steps, with the updates restricted to the first KE rows and columns.
-template <int UT, int KE>
-__device__ __forceinline__ int cholesky_pad(Factor<UT> &f, int i) {
-  i = opaque_idx(i);
-  int fail = 0;
-  sfor<KE>([&](auto J) { chol_step<UT, J, KE>(f, i, fail); });
-  if (i >= KE) f.dinv = 1.f;
-  return fail;
-}
-
-template <int UT, int KE>
-__device__ __forceinline__ void inverse_columns_pad(Factor<UT> &f, int u) {
-  u = opaque_idx(u);
-#pragma unroll
-  for (int j = 0; j < UT; ++j) f.x[j] = make_float2(u == j ? 1.f : 0.f, 0.f);
-  sfor<KE>([&](auto J) { inv_step<UT, J, KE>(f); });
-}
-
-// ---- 32 x 32: the two 16 x 16 x 16 products of the blocked forms on MFMA
-// With A = [A11 A12; A21 A22] in 16 x 16 blocks, the Cholesky factor is
-// L11 = chol(A11), L21 = A21 L11^{-H}, L22 = chol(A22 - L21 L21^H), and the
-// inverse X = L^{-1} has X11 = L11^{-1}, X22 = L22^{-1}, X21 = -X22 (L21 X11).
-// The first 16 steps of the factorisation and of the inverse run on their
-// own block only; the Schur complement A22 - L21 L21^H and -L21 X11 are
-// complex products on 16x16x4 FP32 MFMA, staged through the LDS matrix slot
-// of each system of the wave (free while the solve runs), and the last 16
-// steps are the usual ones.  This moves 2,048 of the DPP FMACs of a round
-// onto the matrix cores.  Each slot holds three 16 x 16 matrices with a row
-// stride of 17 elements (a column read touches 16 distinct bank pairs):
-// L21 at 0, A22 / S then X11 at kSplitM, -L21 X11 at kSplitY.
-constexpr int kSplitStride = 17;
-constexpr int kSplitM = 16 * kSplitStride;
-constexpr int kSplitY = 32 * kSplitStride;
-
-// C (16 x 16, MFMA D layout) += sign(A) * A B over K = 16 for complex A, B
-// given per lane as A[lr][4 kc + lg] and B[4 kc + lg][lr] (lr = lane % 16,
-// lg = lane / 16): the four real products of the complex one.
-template <class GetA, class GetB>
-__device__ __forceinline__ void cmma16(f4 &re, f4 &im, GetA ga, GetB gb, bool neg) {
-#pragma unroll
-  for (int kc = 0; kc < 4; ++kc) {
-    const float2 p = ga(kc), q = gb(kc);
-    const float s = neg ? -1.f : 1.f;
-    re = mma32(s * p.x, q.x, re);
-    re = mma32(-s * p.y, q.y, re);
-    im = mma32(s * p.x, q.y, im);
-    im = mma32(s * p.y, q.x, im);
-  }
-}
-
-// Schur complement of the 32 x 32 systems of the wave: lanes 16..31 of each
-// group (rows 16..31) hold L21 in a[0..15] and A22 in a[16..31] on entry and
-// S = A22 - L21 L21^H in a[16..31] on return.  base: the wave's LDS slots.
-__device__ __forceinline__ void schur32_mfma(Factor<32> &f, int gi, float2 *base) {
-  const int lane = lane_id();
-  float2 *W = base + (lane / 32) * 1024;
-  if (gi >= 16) {
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      W[(gi - 16) * kSplitStride + k] = f.a[k];
-      W[kSplitM + (gi - 16) * kSplitStride + k] = f.a[16 + k];
-    }
-  }
-  __syncthreads();
-  const int lr = lane % 16, lg = lane / 16;
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    float2 *Ws = base + s * 1024;
-    f4 re, im;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float2 v = Ws[kSplitM + (4 * lg + r) * kSplitStride + lr];
-      re[r] = v.x;
-      im[r] = v.y;
-    }
-    // (L21 L21^H)[i][j] = sum_k L21[i][k] conj(L21[j][k]): both operands are
-    // the element (lr, 4 kc + lg) of L21
-    auto ga = [&](int kc) { return Ws[lr * kSplitStride + 4 * kc + lg]; };
-    auto gb = [&](int kc) {
-      const float2 v = Ws[lr * kSplitStride + 4 * kc + lg];
-      return make_float2(v.x, -v.y);
-    };
-    cmma16(re, im, ga, gb, true);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) Ws[kSplitM + (4 * lg + r) * kSplitStride + lr] = make_float2(re[r], im[r]);
-  }
-  __syncthreads();
-  if (gi >= 16) {
-#pragma unroll
-    for (int k = 0; k < 16; ++k) f.a[16 + k] = W[kSplitM + (gi - 16) * kSplitStride + k];
-  }
-}
-
-__device__ __forceinline__ int cholesky32_split(Factor<32> &f, int i, float2 *base) {
-  i = opaque_idx(i);
-  int fail = 0;
-  sfor<16>([&](auto J) { chol_step<32, J, 16>(f, i, fail); });
-  schur32_mfma(f, i, base);
-  sfor<16>([&](auto J) {
-    constexpr int j = J;
-    chol_step<32, j + 16, 32>(f, i, fail);
-  });
-  return fail;
-}
-
-// X = L^{-1} by columns (lane u = column u), with rows 16..31 of the columns
-// u < 16 set to -L21 X11 on MFMA between the two halves.  L21 is still in
-// each slot from cholesky32_split.
-__device__ __forceinline__ void inverse32_split(Factor<32> &f, int u, float2 *base) {
-  u = opaque_idx(u);
-#pragma unroll
-  for (int j = 0; j < 32; ++j) f.x[j] = make_float2(u == j ? 1.f : 0.f, 0.f);
-  sfor<16>([&](auto J) { inv_step<32, J, 16>(f); });
-  const int lane = lane_id();
-  float2 *W = base + (lane / 32) * 1024;
-  if (u < 16) {
-#pragma unroll
-    for (int k = 0; k < 16; ++k) W[kSplitM + k * kSplitStride + u] = f.x[k];
-  }
-  __syncthreads();
-  const int lr = lane % 16, lg = lane / 16;
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    float2 *Ws = base + s * 1024;
-    f4 re = {0.f, 0.f, 0.f, 0.f}, im = {0.f, 0.f, 0.f, 0.f};
-    auto ga = [&](int kc) { return Ws[lr * kSplitStride + 4 * kc + lg]; };
-    auto gb = [&](int kc) { return Ws[kSplitM + (4 * kc + lg) * kSplitStride + lr]; };
-    cmma16(re, im, ga, gb, true);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) Ws[kSplitY + (4 * lg + r) * kSplitStride + lr] = make_float2(re[r], im[r]);
-  }
-  __syncthreads();
-  if (u < 16) {
-#pragma unroll
-    for (int k = 0; k < 16; ++k) f.x[16 + k] = W[kSplitY + k * kSplitStride + u];
-  }
-  sfor<16>([&](auto J) {
-    constexpr int j = J;
-    inv_step<32, j + 16, 32>(f);
-  });
-}
-
-// The same two forms in halves, for callers whose U may leave padded users
-// in a 32-lane group (the FD forms): the first 16 steps with the block
-// products, then steps 16 .. KE-1 with the updates restricted to the first KE
-// rows and columns.  For KE = 24 the rows 24..31 must be padding: users past
-// U, whose rows of A are the identity (zero Gram entries, 1 on the diagonal),
-// so their rows of L and X are the identity too and the 8 steps left out
-// would only scale them by 1.  cholesky32_split and inverse32_split keep their
-// own copies of the first halves: built from these pieces, the PD kernels
-// (which never take the short form) ran 1-2% slower.
-__device__ __forceinline__ int cholesky32_first(Factor<32> &f, int i, float2 *base) {
-  i = opaque_idx(i);
-  int fail = 0;
-  sfor<16>([&](auto J) { chol_step<32, J, 16>(f, i, fail); });
-  schur32_mfma(f, i, base);
-  return fail;
-}
-
-template <int KE>
-__device__ __forceinline__ void cholesky32_second(Factor<32> &f, int i, int &fail) {
-  i = opaque_idx(i);
-  sfor<KE - 16>([&](auto J) {
-    constexpr int j = J;
-    chol_step<32, j + 16, KE>(f, i, fail);
-  });
-  if constexpr (KE < 32) {
-    if (i >= KE) f.dinv = 1.f;
-  }
-}
-
-__device__ __forceinline__ void inverse32_first(Factor<32> &f, int u, float2 *base) {
-  u = opaque_idx(u);
-#pragma unroll
-  for (int j = 0; j < 32; ++j) f.x[j] = make_float2(u == j ? 1.f : 0.f, 0.f);
-  sfor<16>([&](auto J) { inv_step<32, J, 16>(f); });
-  const int lane = lane_id();
-  float2 *W = base + (lane / 32) * 1024;
-  if (u < 16) {
-#pragma unroll
-    for (int k = 0; k < 16; ++k) W[kSplitM + k * kSplitStride + u] = f.x[k];
-  }
-  __syncthreads();
-  const int lr = lane % 16, lg = lane / 16;
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    float2 *Ws = base + s * 1024;
-    f4 re = {0.f, 0.f, 0.f, 0.f}, im = {0.f, 0.f, 0.f, 0.f};
-    auto ga = [&](int kc) { return Ws[lr * kSplitStride + 4 * kc + lg]; };
-    auto gb = [&](int kc) { return Ws[kSplitM + (4 * kc + lg) * kSplitStride + lr]; };
-    cmma16(re, im, ga, gb, true);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) Ws[kSplitY + (4 * lg + r) * kSplitStride + lr] = make_float2(re[r], im[r]);
-  }
-  __syncthreads();
-  if (u < 16) {
-#pragma unroll
-    for (int k = 0; k < 16; ++k) f.x[16 + k] = W[kSplitY + k * kSplitStride + u];
-  }
-}
-
-template <int KE>
-__device__ __forceinline__ void inverse32_second(Factor<32> &f) {
-  sfor<KE - 16>([&](auto J) {
-    constexpr int j = J;
-    inv_step<32, j + 16, KE>(f);
-  });
-}
-
-// The same inverse with L read from LDS instead of registers: Ls holds L
-// (row i written by lane i) with 1 / L_jj on the diagonal, and every lane of
-// a group reads the same element (an LDS broadcast).  The rows of L in
-// registers are dead once they are stored, which is what the 32-lane groups
-// need: there L and L^{-1} together take 128 VGPRs.
-template <int UT>
-__device__ __forceinline__ void inverse_columns_lds(Factor<UT> &f, int u, float2 (*Ls)[UT]) {
-  u = opaque_idx(u);
-#pragma unroll
-  for (int j = 0; j < UT; ++j) f.x[j] = make_float2(u == j ? 1.f : 0.f, 0.f);
-  sfor<UT>([&](auto J) {
-    constexpr int j = J;
-    const float invj = lds_el<UT>(Ls, j, j).x;
-    f.x[j] = make_float2(f.x[j].x * invj, f.x[j].y * invj);
-    // x_i -= L_ij x_j
-    sfor<UT>([&](auto I) {
-      constexpr int i = I;
-      if constexpr (i > j) {
-        const float2 l = lds_el<UT>(Ls, i, j);
-        f.x[i].x = fmaf(-l.x, f.x[j].x, fmaf(l.y, f.x[j].y, f.x[i].x));
-        f.x[i].y = fmaf(-l.x, f.x[j].y, fmaf(-l.y, f.x[j].x, f.x[i].y));
-      }
-    });
-    step_fence();
-  });
-}
-
-// t = L^{-1} b by forward substitution; lane i holds b_i on entry, t_i on exit.
-template <int UT>
-__device__ __forceinline__ float2 fwd_subst(const Factor<UT> &f, int i, float2 b) {
-  i = opaque_idx(i);
-  float2 t = b;
-  sfor<UT>([&](auto J) {
-    constexpr int j = J;
-    if (i == j) { t.x *= f.dinv; t.y *= f.dinv; }
-    const float2 tj = gbcast2<UT, j>(t);
-    if (i > j) {
-      t.x -= f.a[j].x * tj.x - f.a[j].y * tj.y;
-      t.y -= f.a[j].x * tj.y + f.a[j].y * tj.x;
-    }
-  });
-  return t;
-}
 
 // (X^H t)_u = sum_j conj(X_ju) t_j for lane u; t_j is the DPP row broadcast
 // of lane j, fused into the FMACs (t does not change here, so one group).
 template <int UT>
-__device__ __forceinline__ float2 apply_xh(const Factor<UT> &f, float2 t) {
+__device__ __forceinline__ float2 apply_xh(const Columns<UT> &f, float2 t) {
   const BSrc bx = bsrc<UT>(t.x), by = bsrc<UT>(t.y);
   float r[4] = {0.f, 0.f, 0.f, 0.f};
   sfor<UT>([&](auto J) {
@@ -1033,115 +651,6 @@ __device__ __forceinline__ float2 apply_xh(const Factor<UT> &f, float2 t) {
     fmac_rowbcast<j % 16, true, 0>(r[p + 1], bpick<j>(bx), f.x[j].y);
   });
   return make_float2(r[0] + r[2], r[1] + r[3]);
-}
-
-// Factorises A (rows in f.a) and solves A z = m: returns z_u at lane u,
-// fills f.x (columns of L^{-1}) and sets `fail` (0 or first bad pivot + 1).
-// The forward substitution runs before the inverse so the two independent
-// chains are not interleaved by the compiler.
-//
-// Ls (optional) is the LDS matrix slot the system was loaded from: with it,
-// 32-lane groups store L there and form the inverse from LDS.
-//
-// PAD: U (wave-uniform) may leave padded users; the 32 x 32 forms (PAD & 1)
-// then leave out the last 8 steps for at most 24 users, the 16 x 16 forms
-// (PAD & 2) the last 8 for at most 8 users.
-template <int UT, int PAD = 0>
-__device__ __forceinline__ float2 factor_solve(Factor<UT> &f, int i, float2 m, int &fail,
-                                               float2 (*Ls)[UT] = nullptr, float2 *split = nullptr,
-                                               int U = UT) {
-  if constexpr (UT == 16 && (PAD & 2)) {
-    if (__builtin_amdgcn_readfirstlane(U) <= 8) {
-      fail = cholesky_pad<UT, 8>(f, i);
-      const float2 t = fwd_subst<UT>(f, i, m);
-      asm volatile("" : "+v"(f.a[0].x) : "v"(t.x), "v"(t.y));
-      inverse_columns_pad<UT, 8>(f, i);
-      return apply_xh<UT>(f, t);
-    }
-  }
-  if constexpr (UT == 32 && (PAD & 1)) {
-    if (split) {
-      const bool u24 = __builtin_amdgcn_readfirstlane(U) <= 24;
-      fail = cholesky32_first(f, i, split);
-      if (u24)
-        cholesky32_second<24>(f, i, fail);
-      else
-        cholesky32_second<32>(f, i, fail);
-      const float2 t = fwd_subst<UT>(f, i, m);
-      asm volatile("" : "+v"(f.a[0].x) : "v"(t.x), "v"(t.y));
-      inverse32_first(f, i, split);
-      if (u24)
-        inverse32_second<24>(f);
-      else
-        inverse32_second<32>(f);
-      return apply_xh<UT>(f, t);
-    }
-  }
-  if constexpr (UT == 32) {
-    if (split) {
-      // the wave's systems each own an LDS matrix slot (split: the first)
-      fail = cholesky32_split(f, i, split);
-      const float2 t = fwd_subst<UT>(f, i, m);
-      asm volatile("" : "+v"(f.a[0].x) : "v"(t.x), "v"(t.y));
-      inverse32_split(f, i, split);
-      return apply_xh<UT>(f, t);
-    }
-  }
-  fail = cholesky<UT>(f, i);
-  const float2 t = fwd_subst<UT>(f, i, m);
-  asm volatile("" : "+v"(f.a[0].x) : "v"(t.x), "v"(t.y));
-  if (UT == 32 && Ls) {
-    // row i of L, with 1 / L_ii on the diagonal
-#pragma unroll
-    for (int k = 0; k < UT; ++k) lds_el<UT>(Ls, i, k) = k == i ? make_float2(f.dinv, 0.f) : f.a[k];
-    __syncthreads();
-    inverse_columns_lds<UT>(f, i, Ls);
-  } else {
-    inverse_columns<UT>(f, i);
-  }
-  return apply_xh<UT>(f, t);
-}
-
-// Factorises A (rows in f.a) and forms the columns of X = L^{-1} in f.x,
-// for systems whose right-hand sides come later (several per factor).
-// Returns 0 or the first bad pivot + 1.  With Ls (32-lane groups) L is
-// stored there and the inverse is formed from LDS, as in factor_solve.
-template <int UT>
-__device__ __forceinline__ int factor_inverse(Factor<UT> &f, int i, float2 (*Ls)[UT] = nullptr,
-                                              float2 *split = nullptr) {
-  if constexpr (UT == 32) {
-    if (split) {
-      // the wave's systems each own an LDS matrix slot (split: the first)
-      const int fail = cholesky32_split(f, i, split);
-      inverse32_split(f, i, split);
-      return fail;
-    }
-  }
-  const int fail = cholesky<UT>(f, i);
-  if (UT == 32 && Ls) {
-#pragma unroll
-    for (int k = 0; k < UT; ++k) lds_el<UT>(Ls, i, k) = k == i ? make_float2(f.dinv, 0.f) : f.a[k];
-    __syncthreads();
-    inverse_columns_lds<UT>(f, i, Ls);
-  } else {
-    inverse_columns<UT>(f, i);
-  }
-  return fail;
-}
-
-// A^{-1} b for lane-distributed b (lane i holds b_i); result at lane u.
-template <int UT>
-__device__ __forceinline__ float2 solve(const Factor<UT> &f, int i, float2 b) {
-  return apply_xh<UT>(f, fwd_subst<UT>(f, i, b));
-}
-
-// [A^{-1}]_uu for lane u.
-template <int UT>
-__device__ __forceinline__ float inv_diag(const Factor<UT> &f) {
-  float d = 0.f;
-#pragma unroll
-  for (int j = 0; j < UT; ++j) d += f.x[j].x * f.x[j].x + f.x[j].y * f.x[j].y;
-  return d;
 }
 
 __device__ __forceinline__ bool finite2(float2 v) { return isfinite(v.x) && isfinite(v.y); }
@@ -1265,7 +774,7 @@ __device__ __forceinline__ void elim_step(float2 (&v)[16], Elim &e, float rho, i
   if (me) s = make_float2(inv, 0.f);
   float d = e.d;
   if (me) d = 0.f;
-  e.d = fmaf(s.x, s.x, fmaf(s.y, s.y, d));
+  e.d = d + fmaf(s.x, s.x, s.y * s.y);  // one rounding of the running sum a step
   const BSrc bx = bsrc<UT>(s.x), by = bsrc<UT>(s.y);
   if constexpr (RHS) {
     const BSrc tx = bsrc<UT>(e.acc.x * inv), ty = bsrc<UT>(e.acc.y * inv);

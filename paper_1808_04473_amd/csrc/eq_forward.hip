@@ -98,18 +98,6 @@ __device__ __forceinline__ void pd_task(const FwdArgs &a, int w0, int nvalid, SM
   }
 }
 
-// Sum over the gw lane groups that share a subcarrier (gw = 1, 2, 4 groups,
-// consecutive and aligned); every lane of them receives it.
-template <int UT>
-__device__ __forceinline__ float group_sum(float v, int gw) {
-  if (UT == 16 && gw > 1) {
-    const BSrc r = bsrc<32>(v);
-    v = r.lo + r.hi;
-  }
-  if (gw > (UT == 16 ? 2 : 1)) v = xor32_sum(v);
-  return v;
-}
-
 // All clusters of subcarriers w0 .. w0+nsub-1, NSYS clusters per round.  The
 // nw waves of the workgroup take the rounds in turn (nsub = 1 if nw > 1);
 // sms: the LDS of all of them.

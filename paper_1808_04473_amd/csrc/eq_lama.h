@@ -38,7 +38,7 @@ __device__ __forceinline__ void pam_posterior(float x, float inv_tau, float lvl,
 // coordinate and energy es.  Returns z of the last iteration in z and its
 // variance N0 + beta phi in tau.
 template <int UT, int M>
-__device__ __forceinline__ void lama_iterate(const Factor<UT> &f, float2 m, int i, int U, float n0, float beta,
+__device__ __forceinline__ void lama_iterate(const Columns<UT> &f, float2 m, int i, int U, float n0, float beta,
                                              float es, int t_max, float2 &z, float &tau) {
   const float lvl = sqrtf(3.0f * es / (2.0f * (float)(M * M - 1)));
   const float inv_u = 1.0f / (float)U;

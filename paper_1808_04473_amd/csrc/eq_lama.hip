@@ -28,7 +28,7 @@ struct LamaOut {
 template <int UT, int M, class SM>
 __device__ __forceinline__ LamaOut lama_local(SM &sm, int slot, int i, int U, float scale, float n0, float beta,
                                               float es, int t_max) {
-  Factor<UT> f;  // f.x[k] = conj(G_ik) * scale
+  Columns<UT> f;  // f.x[k] = conj(G_ik) * scale
   bool bad = false;
 #pragma unroll
   for (int k = 0; k < UT; ++k) {

@@ -28,42 +28,6 @@ __device__ __forceinline__ int slot_of(int g) {
   return g < SM::NS ? g : SM::NS - 1;
 }
 
-// Loads row i of system `sme` from LDS and factorises / solves it.
-template <int UT>
-struct FactorSolve {
-  Factor<UT> f;
-  float2 z;
-  float d;
-  float norm1;
-  int fail;
-  bool bad;
-};
-
-// PAD (factor_solve): leave out the steps of the factorisation and inverse
-// that only touch padded users, for at most 24 users in a 32-lane group
-// (PAD & 1) or 8 in a 16-lane group (PAD & 2); the FD forms, which solve one
-// system per cluster, use it (PD measured no faster).
-template <int UT, int PAD = 0, class SM>
-__device__ __forceinline__ void factor_local(FactorSolve<UT> &r, SM &sm, int sme, int i, int U) {
-  float rowsum = 0.f;
-#pragma unroll
-  for (int k = 0; k < UT; ++k) {
-    r.f.a[k] = lds_el<UT>(sm.A[sme], i, k);
-    rowsum = abs_row_acc(rowsum, r.f.a[k]);
-  }
-  const float2 m = sm.M[sme][i];
-  r.bad = gany<UT>(!isfinite(abs_row_acc(rowsum, m)));
-  r.norm1 = gmax<UT>(i < U ? rowsum * (1.f / kRowScale) : 0.f);
-  // with fewer slots than groups (PD items of one 32-lane system) the freed
-  // registers raise occupancy, so the inverse reads L from LDS there
-  // with a slot per system, the 32 x 32 forms run their two block products
-  // on MFMA through the slots (read above, free until the solve ends)
-  float2 *split = nullptr;
-  if constexpr (UT == 32 && SM::NS == SM::NSYS) split = &sm.A[0][0][0];
-  r.z = factor_solve<UT, PAD>(r.f, i, m, r.fail, SM::NS < SM::NSYS ? sm.A[sme] : nullptr, split, U);
-  r.d = inv_diag<UT>(r.f);
-}
-
 // LDS of one wave of the local solves: NSLOT packed matrix slots (one per
 // system of a round by default; fewer when the work items hold fewer systems
 // than there are lane groups) and, per system, every lane's share of the
@@ -102,6 +66,18 @@ __device__ __forceinline__ void local_solve(LocalSolve<UT> &r, SM &sm, int sme, 
   solve_slot<UT, KEEP, SM::NS>(r, sm.A, sme, i, m, rho, U);
 }
 
+// Sum over the gw lane groups that share a subcarrier (gw = 1, 2, 4 groups,
+// consecutive and aligned); every lane of them receives it.
+template <int UT>
+__device__ __forceinline__ float group_sum(float v, int gw) {
+  if (UT == 16 && gw > 1) {
+    const BSrc r = bsrc<32>(v);
+    v = r.lo + r.hi;
+  }
+  if (gw > (UT == 16 ? 2 : 1)) v = xor32_sum(v);
+  return v;
+}
+
 // One refinement step for the systems of a round: every group's z goes to
 // LDS, the residual pass streams the systems' rows again and each group
 // solves A dz = H^H (y - H z) - rho z as dz = X^H (X r) with X = L^{-1}
@@ -137,7 +113,7 @@ __device__ __forceinline__ void refine_round(LocalSolve<UT> &r, SM &sm, int nval
 #pragma unroll
     for (int u = 0; u < 16; ++u) add(blk_el(As, 2, u, ii), sm.R[sme][16 + u]);
   }
-  Factor<UT> f;
+  Columns<UT> f;
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
     float2 x = blk_el(As, 0, ii, k);

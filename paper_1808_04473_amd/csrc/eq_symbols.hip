@@ -377,12 +377,6 @@ __device__ __forceinline__ void gram_mf_stream(int ns, int U, int B, int nsym, S
   }
 }
 
-// Sum over the four lane groups, lane by lane of a group.
-__device__ __forceinline__ float groups_sum(float v) {
-  const BSrc r = bsrc<32>(v);
-  return xor32_sum(r.lo + r.hi);
-}
-
 // ---------------------------------------------------------------- outputs
 // FD sums in accumulator layout: weighted estimates, and weights (optimal:
 // the fused variance is 1 / tk) or nu^2 sigma2_c (given weights: the fused
