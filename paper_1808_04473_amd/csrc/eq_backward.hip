@@ -426,8 +426,7 @@ __device__ __forceinline__ float fd_backward_task(const BwdArgs &a, int w0, int 
       const size_t w = (size_t)(w0 + wl);
       Hw = a.H + w * HB;
       yw = a.y + w * a.B;
-      r0 = a.off[c];
-      r1 = a.off[c + 1];
+      cluster_rows<BwdArgs>(c, r0, r1);
     };
   };
   auto accumulate = [&](int base) {

@@ -42,7 +42,8 @@ struct FwdArgs {
   int32_t eqz;          // Eqz; ZF runs the L-MMSE kernels with rho = 0
   int32_t lama_t;       // LAMA: iterations T_max
   int32_t lama_m;       // LAMA: levels per coordinate of the square QAM (2, 4, 8)
-  uint16_t off[EQ_MAX_C + 1];
+  // cluster c owns rows off[c] .. off[c+1]-1; read in words (cluster_rows)
+  alignas(4) uint16_t off[EQ_MAX_C + 2];
 };
 
 // Backward launch arguments.
@@ -60,7 +61,8 @@ struct BwdArgs {
   int32_t W, B, U, C;
   float n0, rho, es;
   int32_t spw;
-  uint16_t off[EQ_MAX_C + 1];
+  // cluster c owns rows off[c] .. off[c+1]-1; read in words (cluster_rows)
+  alignas(4) uint16_t off[EQ_MAX_C + 2];
 };
 
 // Host launchers (defined in the .hip files).

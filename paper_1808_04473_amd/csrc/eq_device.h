@@ -19,6 +19,8 @@
 //    broadcasting one lane: a DPP row broadcast, after a v_permlane16_swap
 //    for 32-lane groups, fused into the FMAC that consumes it.
 #pragma once
+#include <stddef.h>
+
 #include <utility>
 
 #include "eq_common.h"
@@ -212,6 +214,33 @@ __device__ __forceinline__ void acc_zero(Acc<UT> &a) {
   constexpr int NR = UT == 16 ? 4 : 16;
 #pragma unroll
   for (int r = 0; r < NR; ++r) { a.rr[r] = 0.f; a.ri[r] = 0.f; a.ii[r] = 0.f; }
+}
+
+// ---------------------------------------------------------------- wave-uniform tables
+// Word p[k] of a table that no kernel writes, for wave-uniform k, as a scalar
+// load.  Without the constant address space the compiler reads tables through
+// the vector memory path, whose results arrive in order: waiting for one
+// entry waits for every load of the stream in flight.
+template <class T>
+__device__ __forceinline__ T table(const T *p, int k) {
+  typedef const T __attribute__((address_space(4))) *cp;
+  return ((cp)(uintptr_t)p)[__builtin_amdgcn_readfirstlane(k)];
+}
+
+// Rows [r0, r1) of cluster c (wave-uniform) from the 16-bit offsets in the
+// launch arguments Args, the kernel's first parameter.  There is no 16-bit
+// scalar load, and the address of a by-value argument would put a copy of all
+// of them in scratch, so by words of the kernel-argument segment.
+template <class Args>
+__device__ __forceinline__ void cluster_rows(int c, int &r0, int &r1) {
+  typedef const char __attribute__((address_space(4))) *bp;
+  typedef const uint32_t __attribute__((address_space(4))) *wp;
+  const wp w = (wp)((bp)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(Args, off));
+  c = __builtin_amdgcn_readfirstlane(c);
+  const uint32_t a = w[c >> 1], b = w[(c + 1) >> 1];
+  const bool odd = c & 1;
+  r0 = odd ? a >> 16 : a & 0xffffu;
+  r1 = odd ? b & 0xffffu : b >> 16;
 }
 
 // ---------------------------------------------------------------- row-block streaming
@@ -717,7 +746,7 @@ __device__ __forceinline__ void elim_cols(float2 *v, float bx, float by, float2 
   constexpr int m0 = (int)(le | lanes_ge<UT>(K0)), m1 = (int)(le | lanes_ge<UT>(K0 + 1));
   constexpr int m2 = (int)(le | lanes_ge<UT>(K0 + 2)), m3 = (int)(le | lanes_ge<UT>(K0 + 3));
   constexpr int k0 = K0 % 16;
-  if constexpr (NOP) asm volatile("s_nop 4");
+  if constexpr (NOP) asm volatile("s_nop 2");  // and the two scalar moves
   if constexpr (N == 4) {
     asm volatile(EQ_COL_EXEC("%12") EQ_COL_FMAC("%0", "%1", "%8", "%9", "%10", "%11", "%16")
                      EQ_COL_EXEC("%13") EQ_COL_FMAC("%2", "%3", "%8", "%9", "%10", "%11", "%17")
@@ -783,7 +812,7 @@ __device__ __forceinline__ void elim_step(float2 (&v)[16], Elim &e, float rho, i
     // sum is rounded once a step: 5% less error in z than four FMACs on it).
     // The s_nop also covers the columns that follow.
     float px, py;
-    asm volatile("s_nop 4\n\t"
+    asm volatile("s_nop 1\n\t"
                  "v_mul_f32_dpp %0, %2, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
                  "v_mul_f32_dpp %1, %2, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
                  "v_fmac_f32_dpp %0, -%3, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
@@ -794,7 +823,7 @@ __device__ __forceinline__ void elim_step(float2 (&v)[16], Elim &e, float rho, i
     e.acc.x -= px;
     e.acc.y -= py;
   } else {
-    asm volatile("s_nop 4" : : "v"(bpick<J>(bx)), "v"(bpick<J>(by)));
+    asm volatile("s_nop 1" : : "v"(bpick<J>(bx)), "v"(bpick<J>(by)));
   }
   sfor<4>([&](auto G) {
     constexpr int g = G;

@@ -130,8 +130,7 @@ __device__ __forceinline__ void fd_task(const FwdArgs &a, int w0, int nsub, SM *
       const size_t w = (size_t)(w0 + wl);
       Hw = a.H + w * HB;
       yw = a.y + w * a.B;
-      r0 = a.off[c];
-      r1 = a.off[c + 1];
+      cluster_rows<FwdArgs>(c, r0, r1);
     };
     // ---- local Gram + MRC of the clusters of this round
     gram_stream<UT, PREC, refines(PREC) ? kLoadKeep : kLoadLast>(nvalid, a.U, seg, [&](int s, const Acc<UT> &acc, float2 mf) {

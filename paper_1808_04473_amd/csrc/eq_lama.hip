@@ -95,8 +95,7 @@ __device__ __forceinline__ void lama_fd_task(const FwdArgs &a, int w, Smem<UT> &
     auto seg = [&](int s, const float2 *&Hw, const float2 *&yw, int &r0, int &r1) {
       Hw = a.H + (size_t)w * HB;
       yw = a.y + (size_t)w * a.B;
-      r0 = a.off[base + s];
-      r1 = a.off[base + s + 1];
+      cluster_rows<FwdArgs>(base + s, r0, r1);
     };
     gram_stream<UT, PREC, kLoadLast>(nvalid, a.U, seg, [&](int s, const Acc<UT> &acc, float2 mf) {
       store_gram<UT, PREC>(sm.A[s], acc);

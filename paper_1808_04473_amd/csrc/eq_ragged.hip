@@ -48,6 +48,12 @@ __device__ __forceinline__ T ld_dev(const T *p) {
 // arrival increment that publishes them.
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// Descriptor of system k (wave-uniform), through scalar loads.
+typedef const RSys __attribute__((address_space(4))) SysDesc;
+__device__ __forceinline__ SysDesc &sys_desc(const RaggedArgs &a, int k) {
+  return ((SysDesc *)(uintptr_t)a.sys)[__builtin_amdgcn_readfirstlane(k)];
+}
+
 // Solve and outputs of a PD round whose n systems (sysk(s), s < n) have their
 // G + rho I and matched filters in sm.A / sm.M; seg re-streams them for the
 // refinement step.
@@ -91,7 +97,7 @@ __device__ __forceinline__ void pd_group(const RaggedArgs &a, const RTask &task,
   const int U = task.U;
   auto sysk = [&](int s) { return a.order[task.first + s]; };
   auto seg = [&](int s, const float2 *&Hw, const float2 *&yw, int &r0, int &r1) {
-    const RSys &d = a.sys[sysk(s)];
+    SysDesc &d = sys_desc(a, table(a.order, task.first + s));
     Hw = a.Hpool + d.h_off;
     yw = a.ypool + d.y_off;
     r0 = 0;
@@ -111,7 +117,7 @@ __device__ __forceinline__ void pd_piece(const RaggedArgs &a, const RTask &task,
   const int lane = lane_id();
   const int k = task.first;
   const int U = task.U;
-  const RSys &d = a.sys[k];
+  SysDesc &d = sys_desc(a, k);
   const int np = d.npieces;
   float *slot = a.part + (size_t)(d.slot0 + task.piece) * kPartStride;
   auto seg_piece = [&](int, const float2 *&Hw, const float2 *&yw, int &r0, int &r1) {
@@ -174,13 +180,13 @@ __device__ __forceinline__ void fd_round(const RaggedArgs &a, const RTask &task,
   auto gcl = [&](int s) { return a.order[task.first + s]; };
   auto sysk = [&](int s) { return a.cl_sys[gcl(s)]; };
   auto seg = [&](int s, const float2 *&Hw, const float2 *&yw, int &r0, int &r1) {
-    const int gc = gcl(s);
-    const RSys &d = a.sys[a.cl_sys[gc]];
+    const int gc = table(a.order, task.first + s);
+    SysDesc &d = sys_desc(a, table(a.cl_sys, gc));
     const int c = gc - d.cl0;
     Hw = a.Hpool + d.h_off;
     yw = a.ypool + d.y_off;
-    r0 = a.offs[d.off_first + c];
-    r1 = a.offs[d.off_first + c + 1];
+    r0 = table(a.offs, d.off_first + c);
+    r1 = table(a.offs, d.off_first + c + 1);
   };
   gram_stream<UT, PREC, refines(PREC) ? kLoadKeep : kLoadLast>(n, U, seg, [&](int s, const Acc<UT> &acc, float2 mf) {
     store_gram_packed<UT, PREC>(sm.A + s * kSlot<UT>, acc);
@@ -275,7 +281,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void
     if (lane == 0) t = atomicAdd(head, 1);
     t = q + kQueues * __shfl(t, 0);
     if (t >= a.ntasks) break;
-    const RTask task = a.tasks[t];
+    // the items are read through scalar loads, like every table of the plan
+    RTask task;
+    int32_t *tw = &task.kind;
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(RTask) / 4); ++k) tw[k] = table(&a.tasks->kind, t * (int)(sizeof(RTask) / 4) + k);
     if constexpr (FD) {
       if (task.ut == 16)
         fd_round<16, PREC>(a, task, sm.s16);

@@ -477,8 +477,7 @@ __device__ __forceinline__ auto fd_seg(const FwdArgs &a, int w, Cluster cluster)
   return [&a, w, cluster](int s, const float2 *&Hw, const float2 *&Yw, int &r0, int &r1) {
     Hw = a.H + (size_t)w * ((size_t)a.B * a.U);
     Yw = a.y + (size_t)w * (size_t)a.ysw;
-    r0 = a.off[cluster(s)];
-    r1 = a.off[cluster(s) + 1];
+    cluster_rows<FwdArgs>(cluster(s), r0, r1);
   };
 }
 
@@ -997,7 +996,9 @@ __device__ __forceinline__ void fd_direct_task(const FwdArgs &a, int w, DirectLd
           s2[t] = o.s2[t];
         }
       } else {
-        const float iw = 1.0f / ((float)(a.off[c + 1] - a.off[c]) / (float)a.B);
+        int r0, r1;
+        cluster_rows<FwdArgs>(c, r0, r1);
+        const float iw = 1.0f / ((float)(r1 - r0) / (float)a.B);
 #pragma unroll
         for (int b = 0; b < 2 * NT - 1; ++b) {
           G.re[b] *= iw;
