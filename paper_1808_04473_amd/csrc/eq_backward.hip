@@ -365,8 +365,9 @@ __device__ __forceinline__ float round_grads(const BwdArgs &a, BwdLds<UT> &sm, c
 template <int UT, class Seg>
 __device__ __forceinline__ void round_solve(const BwdArgs &a, BwdLds<UT> &sm, LocalSolve<UT> &r, int nvalid, Seg seg) {
   const int lane = lane_id();
+  const GramAddr<UT> ga = gram_addr<UT>();
   gram_stream<UT, PREC_FP32, kLoadKeep>(nvalid, a.U, seg, [&](int s, const Acc<UT> &acc, float2 mf) {
-    store_gram_packed<UT, PREC_FP32>(sm.A + s * kSlot<UT>, acc);
+    store_gram_packed<UT, PREC_FP32>(ga, sm.A + s * kSlot<UT>, acc);
     sm.M[s][lane] = mf;
   });
   wave_sync();
@@ -536,7 +537,7 @@ constexpr int kBwdWaves = 8;
 template <int UT, bool QUAD, bool ONCE>
 __global__ __launch_bounds__(64 * kBwdWaves) __attribute__((amdgpu_waves_per_eu(UT == 16 ? 4 : 2, 8))) void eq_backward_fd_kernel(
     const BwdArgs a) {
-  extern __shared__ float2 bwd_lds[];
+  extern __shared__ __align__(128) float2 bwd_lds[];
   BwdLds<UT> *sm = reinterpret_cast<BwdLds<UT> *>(bwd_lds);
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), nw = blockDim.x / 64;
   const int w0 = blockIdx.x * a.spw;

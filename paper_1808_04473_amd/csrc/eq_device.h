@@ -329,10 +329,10 @@ __device__ __forceinline__ void load_slot(Slot &b, const LaneOff<UT> &lo, const 
       __builtin_amdgcn_make_buffer_rsrc((void *)(Hw + (size_t)r0 * U), (short)0, nrow * U * 8, kBufFlags);
   const __amdgpu_buffer_rsrc_t ry =
       __builtin_amdgcn_make_buffer_rsrc((void *)(yw + r0), (short)0, nrow * 8, kBufFlags);
-  const unsigned rowb = (unsigned)((rb - r0) * U * 8);
+  const unsigned h0 = lo.h + (unsigned)((rb - r0) * U * 8);
   const unsigned step = (unsigned)(U * 8);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) b.h[e] = buf_ld2<AUX>(rh, lo.h + rowb + e * step);
+  for (int e = 0; e < 8; ++e) b.h[e] = buf_ld2<AUX>(rh, h0 + e * step);
   b.yl = buf_ld2<AUX>(ry, lo.y + (unsigned)((rb - r0) * 8));
   b.g = lo.g;
   b.Hw = Hw;
@@ -575,23 +575,55 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// Re G, Im G at the accumulator positions; the transposed ri comes through
-// UT x UT floats of LDS at `scratch` (swizzled like lds_el).
-template <int UT, int PREC, int NR>
-__device__ __forceinline__ void gram_values(float *scratch, const Acc<UT> &acc, float (&re)[NR], float (&im)[NR]) {
+// LDS accesses by byte address.
+typedef __attribute__((address_space(3))) float lds_f32;
+typedef float f2v __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) f2v lds_f64;
+__device__ __forceinline__ uint32_t lds_addr(const void *p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
+}
+__device__ __forceinline__ lds_f32 &lds_f(uint32_t addr) { return *(lds_f32 *)addr; }
+__device__ __forceinline__ void lds_put(uint32_t addr, float x, float y) { *(lds_f64 *)addr = f2v{x, y}; }
+
+// Byte offsets, within a packed slot, of the accumulator positions: register
+// r holds row i0 + q(r) (i0 from the lane, no bits in common with q) of
+// column j, so every swizzled address is one of these with the constant q
+// xor-ed into its column bits and added, as an instruction offset, to its row
+// bits.  Kept in registers over a stream: formed anew at each system they
+// were a tenth of the VALU work of an FD round.
+template <int UT>
+struct GramAddr {
+  uint32_t w, t;  // [i][j] and [j][i] of UT x UT floats
+  uint32_t p0;    // element (i, j) of the packed blocks, rows 0..15
+  uint32_t p1;    // the same for the rows 16..31 (UT = 32)
+  static constexpr int q(int r) { return UT == 16 ? r : 8 * (r >> 2) + (r & 3); }
+};
+template <int UT>
+__device__ __forceinline__ GramAddr<UT> gram_addr() {
   const int lane = lane_id();
+  const uint32_t i0 = UT == 16 ? 4 * (lane >> 4) : 4 * (lane >> 5), j = lane % UT;
+  GramAddr<UT> o;
+  o.w = 4 * (UT * i0 + (j ^ i0));
+  o.t = 4 * (UT * j + (j ^ i0));
+  o.p0 = 8 * (16 * i0 + ((j & 15) ^ i0));
+  o.p1 = o.p0 + 2048 * (1 + (j >> 4));
+  return o;
+}
+
+// Re G, Im G at the accumulator positions; the transposed ri comes through
+// UT x UT floats of LDS at byte address `slot` (aligned to them).
+template <int UT, int PREC, int NR>
+__device__ __forceinline__ void gram_values(const GramAddr<UT> &ga, uint32_t slot, const Acc<UT> &acc, float (&re)[NR],
+                                            float (&im)[NR]) {
+  const uint32_t w = slot + ga.w, t = slot + ga.t;
   sfor<NR>([&](auto R) {
-    constexpr int r = R;
-    int i, j;
-    acc_pos<UT>(lane, r, i, j);
-    scratch[UT * i + (j ^ i)] = acc.ri[r];
+    constexpr int r = R, q = GramAddr<UT>::q(r);
+    lds_f((w ^ (4 * q)) + 4 * UT * q) = acc.ri[r];
   });
   wave_sync();
   sfor<NR>([&](auto R) {
-    constexpr int r = R;
-    int i, j;
-    acc_pos<UT>(lane, r, i, j);
-    const float rij = scratch[UT * j + (i ^ j)];  // (Hr^T Hi)[j][i]
+    constexpr int r = R, q = GramAddr<UT>::q(r);
+    const float rij = lds_f(t ^ (4 * q));  // (Hr^T Hi)[j][i]
     im[r] = acc.ri[r] - rij;
     re[r] = PREC == PREC_FP32 ? acc.rr[r] - acc.ri[r] - rij : acc.rr[r] + acc.ii[r];
   });
@@ -608,7 +640,7 @@ __device__ __forceinline__ void store_gram(float2 (*As)[UT], const Acc<UT> &acc)
   constexpr int NR = UT == 16 ? 4 : 16;
   const int lane = lane_id();
   float im[NR], re[NR];
-  gram_values<UT, PREC>(&lds_el<UT>(As, 0, 0).x, acc, re, im);
+  gram_values<UT, PREC>(gram_addr<UT>(), lds_addr(As), acc, re, im);
   sfor<NR>([&](auto R) {
     constexpr int r = R;
     int i, j;
@@ -619,32 +651,24 @@ __device__ __forceinline__ void store_gram(float2 (*As)[UT], const Acc<UT> &acc)
 
 // The same into the packed slot of the local solves.
 template <int UT, int PREC>
-__device__ __forceinline__ void store_gram_packed(float2 *As, const Acc<UT> &acc) {
+__device__ __forceinline__ void store_gram_packed(const GramAddr<UT> &ga, float2 *As, const Acc<UT> &acc) {
   constexpr int NR = UT == 16 ? 4 : 16;
-  const int lane = lane_id();
   float im[NR], re[NR];
-  gram_values<UT, PREC>(&As[0].x, acc, re, im);
+  const uint32_t slot = lds_addr(As);
+  gram_values<UT, PREC>(ga, slot, acc, re, im);
+  const uint32_t p0 = slot + ga.p0, p1 = slot + ga.p1;
+  const bool low = UT == 16 || lane_id() % 32 < 16;
   sfor<NR>([&](auto R) {
-    constexpr int r = R;
-    int i, j;
-    acc_pos<UT>(lane, r, i, j);
-    if constexpr (UT == 16) {
-      blk_el(As, 0, i, j) = make_float2(re[r], im[r]);
+    constexpr int r = R, q = GramAddr<UT>::q(r) & 15;
+    if constexpr (UT == 16 || r < 8) {
+      // of the rows 0..15 only the block (0, 0) is kept
+      if (low) lds_put((p0 ^ (8 * q)) + 128 * q, re[r], im[r]);
     } else {
-      // rows 0..15 are registers 0..7: of those only the block (0, 0) is kept
-      if (r >= 8 || j < 16) blk_el(As, r < 8 ? 0 : 1 + (j >> 4), i & 15, j & 15) = make_float2(re[r], im[r]);
+      lds_put((p1 ^ (8 * q)) + 128 * q, re[r], im[r]);
     }
   });
 }
 
-// Writes G + rho I of one system from the MFMA accumulators into LDS
-// (full Hermitian matrix, swizzled rows):
-//   Re G = Hr^T Hr + Hi^T Hi,   Im G[i][j] = (Hr^T Hi)[i][j] - (Hr^T Hi)[j][i],
-// with Re G = P - ri - ri^T for the FP32 accumulators (see gram_blk).
-// Rows and columns of padded users (i >= U) are zero; their diagonal gets 1
-// instead of rho, so that the matrix stays positive definite when rho = 0
-// (ZF).  That block is decoupled from the users' block, whose factor and
-// solves it leaves unchanged.
 template <int UT>
 __device__ __forceinline__ void store_identity(float2 (*As)[UT]) {
   for (int idx = lane_id(); idx < UT * UT; idx += 64) {

@@ -69,7 +69,7 @@ __device__ __forceinline__ void pd_task(const FwdArgs &a, int w0, int nvalid, SM
   // ---- Gram + matched filter of the round's subcarriers (all clusters
   //      accumulate into one G and one y^MRC: the adder tree of eq. (fullMRC))
   gram_stream<UT, PREC, refines(PREC) ? kLoadKeep : kLoadLast>(nvalid, a.U, seg, [&](int s, const Acc<UT> &acc, float2 mf) {
-    store_gram_packed<UT, PREC>(sm.A + s * kSlot<UT>, acc);
+    store_gram_packed<UT, PREC>(gram_addr<UT>(), sm.A + s * kSlot<UT>, acc);
     sm.M[s][lane] = mf;
   });
   wave_sync();
@@ -122,6 +122,7 @@ __device__ __forceinline__ void fd_task(const FwdArgs &a, int w0, int nsub, SM *
   float sw = 0.f, szx = 0.f, szy = 0.f;
   unsigned long long routedm = 0;
 
+  const GramAddr<UT> ga = gram_addr<UT>();
   for (int base = wv * NSYS; base < ntot; base += nw * NSYS) {
     const int nvalid = min(NSYS, ntot - base);
     auto seg = [&](int s, const float2 *&Hw, const float2 *&yw, int &r0, int &r1) {
@@ -134,7 +135,7 @@ __device__ __forceinline__ void fd_task(const FwdArgs &a, int w0, int nsub, SM *
     };
     // ---- local Gram + MRC of the clusters of this round
     gram_stream<UT, PREC, refines(PREC) ? kLoadKeep : kLoadLast>(nvalid, a.U, seg, [&](int s, const Acc<UT> &acc, float2 mf) {
-      store_gram_packed<UT, PREC>(sm.A + s * kSlot<UT>, acc);
+      store_gram_packed<UT, PREC>(ga, sm.A + s * kSlot<UT>, acc);
       sm.M[s][lane] = mf;
     });
     wave_sync();
@@ -222,7 +223,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(waves_target
 constexpr int kFdWaves = 4;
 template <int UT, int PREC>
 __global__ __launch_bounds__(64 * kFdWaves) __attribute__((amdgpu_waves_per_eu(waves_target<UT, PREC, true>(), 8))) void eq_forward_fd_kernel(const FwdArgs a) {
-  extern __shared__ float2 fd_lds[];
+  extern __shared__ __align__(128) float2 fd_lds[];
   using SM = SolveSmem<UT, refines(PREC)>;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), nw = blockDim.x / 64;
   const int w0 = blockIdx.x * a.spw;

@@ -103,8 +103,9 @@ __device__ __forceinline__ void pd_group(const RaggedArgs &a, const RTask &task,
     r0 = 0;
     r1 = d.B;
   };
+  const GramAddr<UT> ga = gram_addr<UT>();
   gram_stream<UT, PREC, refines(PREC) ? kLoadKeep : kLoadLast>(n, U, seg, [&](int s, const Acc<UT> &acc, float2 mf) {
-    store_gram_packed<UT, PREC>(sm.A + s * kSlot<UT>, acc);
+    store_gram_packed<UT, PREC>(ga, sm.A + s * kSlot<UT>, acc);
     sm.M[s][lane] = mf;
   });
   pd_solve_round<UT, PREC>(a, sm, n, U, sysk, seg);
@@ -158,7 +159,7 @@ __device__ __forceinline__ void pd_piece(const RaggedArgs &a, const RTask &task,
     mf.x += ld_dev(q + 3 * R * 64 + lane);
     mf.y += ld_dev(q + (3 * R + 1) * 64 + lane);
   }
-  store_gram_packed<UT, PREC>(sm.A, acc);
+  store_gram_packed<UT, PREC>(gram_addr<UT>(), sm.A, acc);
   sm.M[0][lane] = mf;
   auto seg_whole = [&](int, const float2 *&Hw, const float2 *&yw, int &r0, int &r1) {
     Hw = a.Hpool + d.h_off;
@@ -188,8 +189,9 @@ __device__ __forceinline__ void fd_round(const RaggedArgs &a, const RTask &task,
     r0 = table(a.offs, d.off_first + c);
     r1 = table(a.offs, d.off_first + c + 1);
   };
+  const GramAddr<UT> ga = gram_addr<UT>();
   gram_stream<UT, PREC, refines(PREC) ? kLoadKeep : kLoadLast>(n, U, seg, [&](int s, const Acc<UT> &acc, float2 mf) {
-    store_gram_packed<UT, PREC>(sm.A + s * kSlot<UT>, acc);
+    store_gram_packed<UT, PREC>(ga, sm.A + s * kSlot<UT>, acc);
     sm.M[s][lane] = mf;
   });
   wave_sync();

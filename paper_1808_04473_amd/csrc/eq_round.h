@@ -15,7 +15,7 @@ template <int UT, int NSLOT = 64 / UT>
 struct Smem {
   static constexpr int NSYS = 64 / UT;
   static constexpr int NS = NSLOT;
-  float2 A[NS][UT][UT];  // swizzled rows (lds_el)
+  alignas(128) float2 A[NS][UT][UT];  // swizzled rows (lds_el)
   float2 M[NS][UT];
   float4 F[NS][UT];
   int routed[NSYS];
@@ -41,7 +41,7 @@ struct NoRefineRhs {};
 template <int UT, bool REFINE, int NSLOT = 64 / UT>
 struct SolveSmem : std::conditional_t<REFINE, RefineRhs<UT, NSLOT>, NoRefineRhs> {
   static constexpr int NS = NSLOT;
-  float2 A[NS * kSlot<UT>];
+  alignas(128) float2 A[NS * kSlot<UT>];  // GramAddr flips address bits below 128
   float2 M[NS][64];
 };
 

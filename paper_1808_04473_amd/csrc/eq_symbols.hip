@@ -283,25 +283,38 @@ struct Tiles {
   f4 re[N], im[N];
 };
 
-// The Gram blocks; the transposes of the diagonal ones go through 256 floats
-// of LDS.
-template <int NT, int PREC>
-__device__ __forceinline__ void tile_gram(float *scratch, const TileAcc<NT> &a, Tiles<2 * NT - 1> &G) {
+// Byte offsets of the accumulator positions in 16 x 16 tiles of LDS, the row 4
+// kk + r of register r swizzled and added as in GramAddr: [4 kk][c] and its
+// transpose of floats, element (4 kk, c) of a packed block.
+struct TileAddr {
+  uint32_t w, t, p;
+};
+__device__ __forceinline__ TileAddr tile_addr() {
   const int lane = lane_id();
-  const int kk = lane / 16, c = lane % 16;
+  const uint32_t i0 = 4 * (lane / 16), c = lane % 16;
+  return {4 * (16 * i0 + (c ^ i0)), 4 * (16 * c + (c ^ i0)), 8 * (16 * i0 + (c ^ i0))};
+}
+
+// The Gram blocks; the transposes of the diagonal ones go through 256 floats
+// of LDS at byte address `scratch`.
+template <int NT, int PREC>
+__device__ __forceinline__ void tile_gram(const TileAddr &ta, uint32_t scratch, const TileAcc<NT> &a, Tiles<2 * NT - 1> &G) {
+  const uint32_t w = scratch + ta.w, tr = scratch + ta.t;
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     const int b = 2 * t;
     wave_sync();
-#pragma unroll
-    for (int r = 0; r < 4; ++r) scratch[16 * (4 * kk + r) + (c ^ (4 * kk + r))] = a.ri[b][r];
+    sfor<4>([&](auto R) {
+      constexpr int r = R;
+      lds_f((w ^ (4 * r)) + 64 * r) = a.ri[b][r];
+    });
     wave_sync();
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float rij = scratch[16 * c + ((4 * kk + r) ^ c)];
+    sfor<4>([&](auto R) {
+      constexpr int r = R;
+      const float rij = lds_f(tr ^ (4 * r));
       G.im[b][r] = a.ri[b][r] - rij;
       G.re[b][r] = PREC == PREC_FP32 ? a.rr[b][r] - a.ri[b][r] - rij : a.rr[b][r] + a.ii[b][r];
-    }
+    });
   }
   if constexpr (NT == 2) {
     G.im[1] = a.ri[1] - a.ir;
@@ -489,13 +502,13 @@ __device__ __forceinline__ auto fd_seg(const FwdArgs &a, int w, Cluster cluster)
 template <int NT, int NSLOT, int NC = 1>
 struct SymLds {
   static constexpr int NS = NSLOT;
-  float2 A[NS * kSlot<32>];
+  alignas(128) float2 A[NS * kSlot<32>];  // TileAddr flips address bits below 128
   f4 M[NS][NC][4][64];
 };
 template <int NSLOT>
 struct SymLds<1, NSLOT, 1> {
   static constexpr int NS = NSLOT;
-  float2 A[NS * kSlot<16>];
+  alignas(128) float2 A[NS * kSlot<16>];
 };
 
 // Matched filters of the systems of a round.
@@ -505,18 +518,21 @@ struct SymMf {
 };
 
 template <int NT, int NC, int PREC, class SM>
-__device__ __forceinline__ void store_system(SM &sm, SymMf<NT, SM::NS> &mf, int s, const TileAcc<NT> &acc,
+__device__ __forceinline__ void store_system(SM &sm, const TileAddr &ta, SymMf<NT, SM::NS> &mf, int s, const TileAcc<NT> &acc,
                                              const TileMf<NT, NC> &m) {
   const int lane = lane_id();
-  const int kk = lane / 16, c = lane % 16;
-  float2 *As = sm.A + s * kSlot<16 * NT>;
+  const uint32_t slot = lds_addr(sm.A) + s * (8 * kSlot<16 * NT>);
   Tiles<2 * NT - 1> G;
-  tile_gram<NT, PREC>(&As[0].x, acc, G);
+  tile_gram<NT, PREC>(ta, slot, acc, G);
   wave_sync();
-#pragma unroll
-  for (int b = 0; b < 2 * NT - 1; ++b)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) blk_el(As, b, 4 * kk + r, c) = make_float2(G.re[b][r], G.im[b][r]);
+  const uint32_t p = slot + ta.p;
+  sfor<2 * NT - 1>([&](auto Bk) {
+    constexpr int b = Bk;
+    sfor<4>([&](auto R) {
+      constexpr int r = R;
+      lds_put((p ^ (8 * r)) + 2048 * b + 128 * r, G.re[b][r], G.im[b][r]);
+    });
+  });
 #pragma unroll
   for (int n = 0; n < NC; ++n) {
     Tiles<NT> M;
@@ -627,8 +643,9 @@ __device__ __forceinline__ void pd_sym_task(const FwdArgs &a, int w0, int nvalid
   const int lane = lane_id();
   const int g = lane / UT, i = lane % UT;
   SymMf<NT, SM::NS> mf;
+  const TileAddr ta = tile_addr();
   gram_mf_stream<NT, NC, PREC>(nvalid, a.U, a.B, a.nsym, pd_seg(a, w0), [&](int s, const TileAcc<NT> &acc, const TileMf<NT, NC> &m) {
-    store_system<NT, NC, PREC>(sm, mf, s, acc, m);
+    store_system<NT, NC, PREC>(sm, ta, mf, s, acc, m);
   });
   wave_sync();
   LocalSolve<UT> r;
@@ -686,11 +703,12 @@ __device__ __forceinline__ void fd_sym_task(const FwdArgs &a, int w, SM *sms, in
   float tk = 0.f;  // the weights' sum of user i, clusters of this lane's group
   bool any = false;
   const int g = lane / UT, i = lane % UT;
+  const TileAddr ta = tile_addr();
   for (int base = wv * NSYS; base < C; base += NW * NSYS) {
     const int nvalid = min(NSYS, C - base);
     SymMf<NT, SM::NS> mf;
     gram_mf_stream<NT, 1, PREC>(nvalid, a.U, a.B, a.nsym, fd_seg(a, w, [base](int s) { return base + s; }),
-                             [&](int s, const TileAcc<NT> &acc, const TileMf<NT, 1> &m) { store_system<NT, 1, PREC>(sm, mf, s, acc, m); });
+                             [&](int s, const TileAcc<NT> &acc, const TileMf<NT, 1> &m) { store_system<NT, 1, PREC>(sm, ta, mf, s, acc, m); });
     wave_sync();
     LocalSolve<UT> r;
     solve_slot<UT, true, SM::NS, false>(r, sm.A, g, i, make_float2(0.f, 0.f), a.rho, a.U);
@@ -901,7 +919,7 @@ __device__ __forceinline__ void tile_turn(float *scratch, const Tiles<2 * NT - 1
 // transposes' scratch and, at the end, the wave's fusion sums.
 template <int NT>
 struct DirectLds {
-  float f[12 * NT * 64];
+  alignas(128) float f[12 * NT * 64];
 };
 
 // One system (PD): estimates and variances to their rows.
@@ -913,7 +931,7 @@ __device__ __forceinline__ void pd_direct_task(const FwdArgs &a, int w0, int nva
   gram_mf_stream<NT, NC, PREC>(nvalid, a.U, a.B, a.nsym, pd_seg(a, w0), [&](int s, const TileAcc<NT> &acc, const TileMf<NT, NC> &m) {
     const int w = w0 + s;
     Tiles<2 * NT - 1> G;
-    tile_gram<NT, PREC>(sm.f, acc, G);
+    tile_gram<NT, PREC>(tile_addr(), lds_addr(sm.f), acc, G);
     TileMrc<NT> o;
     Tiles<1> T;
     int code;
@@ -982,7 +1000,7 @@ __device__ __forceinline__ void fd_direct_task(const FwdArgs &a, int w, DirectLd
       const int c = cluster(s);
       Tiles<2 * NT - 1> G;
       Tiles<NT> Y, Z;
-      tile_gram<NT, PREC>(sm.f, acc, G);
+      tile_gram<NT, PREC>(tile_addr(), lds_addr(sm.f), acc, G);
       tile_mf<NT, PREC>(m, 0, Y);
       f4 s2[NT];
       int code;
