@@ -282,7 +282,7 @@ typedef struct eq_plan eq_plan;
    rounds of up to 64/UT clusters of equal U (each cluster's fusion terms go
    to a slot; the last cluster of a system fuses them in cluster order).
    Results do not depend on the launch shape beyond the rounding of those
-   sums.  The launch shape (waves per CU; piece rows per class) comes from
+   sums.  The launch shape (workgroups per CU; piece rows per class) comes from
    the autotune cache (`tune_cache_path`, NULL = the DBPEQ_TUNE_CACHE
    environment variable, else no cache), whose entries are keyed by device,
    mode, precision and, for the piece rows, tile class, so that any batch of
@@ -310,7 +310,7 @@ eq_status eq_plan_execute(eq_plan *plan, const eq_c32 *Hpool, const eq_c32 *ypoo
    padded user count 16, 32), in out_shape[5k .. 5k+4] (out_shape holds
    5 * EQ_PLAN_CLASSES entries, may be NULL): systems of the class, work
    items, PD row pieces (FD: clusters), PD piece rows (0 = systems are not
-   cut; always 0 for FD and the refining forms), persistent waves of the
+   cut; always 0 for FD and the refining forms), persistent workgroups of the
    launch.  *out_tasks (may be NULL) = work items of all classes. */
 #define EQ_PLAN_CLASSES 2
 eq_status eq_plan_describe(const eq_plan *plan, int32_t *out_shape, int32_t *out_tasks);

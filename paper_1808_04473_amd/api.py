@@ -520,7 +520,7 @@ class Plan:
     def describe(self):
         """Launch shape per tile class (padded users 16 / 32): systems, work
         items, PD row pieces (FD: clusters) and PD piece rows (0 = systems
-        are not cut); the persistent waves of the launch and the total number
+        are not cut); the persistent workgroups of the launch and the total number
         of work items."""
         shape = (c_int32 * (5 * PLAN_CLASSES))()
         nt = c_int32()

@@ -32,7 +32,7 @@ struct eq_plan {
   std::vector<RSys> sys;
   std::vector<int32_t> offs;
   std::vector<int32_t> cl_sys;  // system of each global cluster
-  // launch shape: waves per CU of the persistent grid, and per tile class
+  // launch shape: workgroups per CU of the persistent grid, and per tile class
   // the row count above which a PD system is cut into pieces (0 = never)
   int wpc = kDefaultWpc;
   int piece_rows[kClasses] = {kDefaultRows, kDefaultRows};
@@ -292,8 +292,8 @@ RaggedArgs make_args(const eq_plan *p, const eq_c32 *H, const eq_c32 *y, eq_c32 
   return a;
 }
 
-// Persistent waves: CUs x waves per CU, at most one per item, and at least one
-// per queue that holds items (queue q holds the items t with t % kQueues == q).
+// Persistent workgroups: CUs x workgroups per CU, at most one per item, and at
+// least one per queue that holds items (queue q holds the items t with t % kQueues == q).
 int grid_of(const eq_plan *p, int wpc) {
   const int g = std::min(p->cus * wpc, p->ntasks);
   return std::max(1, std::max(g, std::min(kQueues, p->ntasks)));
@@ -327,7 +327,7 @@ hipError_t make_streams(eq_plan *p) {
 }
 
 // Times the launch on the real pools for each candidate of whatever the
-// cache did not hold: first the waves per CU (with the current piece rows),
+// cache did not hold: first the workgroups per CU (with the current piece rows),
 // then, for PD outside the refining forms, the piece rows of each tile class
 // that has systems.  Keeps the fastest of each.
 eq_status autotune(eq_plan *p, const eq_c32 *H, const eq_c32 *y, eq_c32 *z, float *s2, int32_t *info,
@@ -357,9 +357,10 @@ eq_status autotune(eq_plan *p, const eq_c32 *H, const eq_c32 *y, eq_c32 *z, floa
   };
   auto m = read_cache(p->cache_path);
   if (!p->tuned_launch) {
-    // the kernel's registers (2 waves per SIMD) hold 8 waves per CU, and its
-    // LDS (17.9 KB per one-wave workgroup) would not hold more than 9; larger
-    // grids only queue workgroups that find the queues empty
+    // one-wave workgroups: the kernels' registers (2 to 3 waves per SIMD) and
+    // LDS (13.3 KB a wave) hold 8 to 11 on a CU; FD workgroups of two waves
+    // (launch_ragged): 6.  Larger grids only queue workgroups that find the
+    // queues empty.
     const int wpcs[] = {4, 6, 8};
     float tbest = 1e30f;
     for (int w : wpcs) {

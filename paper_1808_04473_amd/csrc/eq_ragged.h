@@ -35,6 +35,10 @@ struct RTask {
 constexpr int kQueues = 8;
 constexpr int kQueueStride = 32;
 
+// Waves per workgroup of the persistent FD launch when there are more items
+// than workgroups.
+constexpr int kRaggedWaves = 2;
+
 // Floats per PD partial slot: the three accumulator arrays and the matched
 // filter, per lane, for the widest tile (UT = 32: 16 accumulator registers).
 constexpr int kPartRegs = 3 * 16 + 2;

@@ -268,13 +268,17 @@ __device__ __forceinline__ void fd_round(const RaggedArgs &a, const RTask &task,
   }
 }
 
+// LDS of one wave.
+template <int PREC>
+union RaggedSmem {
+  SolveSmem<16, refines(PREC)> s16;
+  SolveSmem<32, refines(PREC)> s32;
+};
+
+// One wave: takes items from its queue until that is empty.  The waves of a
+// workgroup share nothing but their launch.
 template <int PREC, bool FD>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void eq_ragged_kernel(
-    const RaggedArgs a) {
-  __shared__ union {
-    SolveSmem<16, refines(PREC)> s16;
-    SolveSmem<32, refines(PREC)> s32;
-  } sm;
+__device__ __forceinline__ void ragged_wave(const RaggedArgs &a, RaggedSmem<PREC> &sm) {
   const int lane = lane_id();
   const int q = (int)(blockIdx.x % kQueues);
   int32_t *head = a.counter + q * kQueueStride;
@@ -308,16 +312,34 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void
   }
 }
 
+template <int PREC>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void eq_ragged_pd_kernel(const RaggedArgs a) {
+  __shared__ RaggedSmem<PREC> sm;
+  ragged_wave<PREC, false>(a, sm);
+}
+template <int PREC>
+__global__ __launch_bounds__(64 * kRaggedWaves) __attribute__((amdgpu_waves_per_eu(2, 8))) void eq_ragged_fd_kernel(
+    const RaggedArgs a) {
+  extern __shared__ __align__(128) char lds[];
+  ragged_wave<PREC, true>(a, ((RaggedSmem<PREC> *)lds)[__builtin_amdgcn_readfirstlane(threadIdx.x / 64)]);
+}
+
 hipError_t launch_ragged(const RaggedArgs &a, bool fd, int prec, int grid, hipStream_t s) {
-  const dim3 g(grid), b(64);
-#define EQ_RAGGED_LAUNCH(P)                                                \
-  if (fd) hipLaunchKernelGGL((eq_ragged_kernel<P, true>), g, b, 0, s, a); \
-  else hipLaunchKernelGGL((eq_ragged_kernel<P, false>), g, b, 0, s, a);
+  // Two waves per workgroup put 12 on a CU (LDS) where one put 8.  FD, with
+  // more items than workgroups: 4096 systems 172 -> 154 us (13,889 items), 768
+  // systems 55 -> 55 (2,568); the items are short, and a wave's loads did not
+  // cover its solves.  PD items are few and long, so that more waves only
+  // spread them worse: 4096 systems 81 -> 90 us, 16,384 systems 250 -> 247.
+  const int nw = fd && a.ntasks > grid ? kRaggedWaves : 1;
+  const dim3 g(grid), b(64 * nw);
+#define EQ_RAGGED_LAUNCH(P)                                                                         \
+  if (fd) hipLaunchKernelGGL(eq_ragged_fd_kernel<P>, g, b, nw * sizeof(RaggedSmem<P>), s, a); \
+  else hipLaunchKernelGGL(eq_ragged_pd_kernel<P>, g, b, 0, s, a);
   switch (prec) {
     case PREC_FP32: EQ_RAGGED_LAUNCH(PREC_FP32) break;
     case PREC_BF16:  // PD only (the plan refuses FD with the single-BF16 Gram)
       if (fd) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((eq_ragged_kernel<PREC_BF16, false>), g, b, 0, s, a);
+      hipLaunchKernelGGL(eq_ragged_pd_kernel<PREC_BF16>, g, b, 0, s, a);
       break;
     case PREC_BF16X3: EQ_RAGGED_LAUNCH(PREC_BF16X3) break;
     default: EQ_RAGGED_LAUNCH(PREC_BF16X3_NR) break;
