@@ -43,14 +43,18 @@ namespace dbpeq {
 constexpr int sym_tiles(int UT, bool fd) { return UT == 32 && !fd ? 2 : 1; }
 
 // ---------------------------------------------------------------- streaming
-// Rows per lane group and row block, and row e of group g within the block
-// (the products sum over rows: any order will do that H and Y share).  At 16
-// users the rows go to the groups in pairs: a 16-byte load of Y then covers
-// two rows, and the four groups 64 consecutive bytes of a vector (14 vectors,
-// PD 38,400 / 4 subcarriers of B = 256, U = 16: 113 against 121 us with eight
-// rows per group; at 32 users, with half the rows, it was 5% slower).
-template <int NT>
-constexpr int kRows = 8 / NT;
+// Rows per lane group and row block.  At 16 users two blocks of eight rows
+// take 64 registers, of four 32: FD, whose solves bound it, runs a wave more
+// per SIMD with four (14 vectors, 9,600 subcarriers of B = 256, U = 16, C = 8:
+// 166 -> 159 us; C = 16: 311 -> 235).  PD streams, and wants the bytes in
+// flight (300 subcarriers: 54 us with eight rows, 58 with four).
+constexpr int sym_rows(int NT, bool fd) { return NT == 1 && !fd ? 8 : 4; }
+// Row e of lane group g within the block (the products sum over rows: any
+// order will do that H and Y share).  At 16 users the rows go to the groups in
+// pairs: a 16-byte load of Y then covers two rows, and the four groups 64
+// consecutive bytes of a vector (14 vectors, PD 38,400 / 4 subcarriers of B =
+// 256, U = 16: 113 against 121 us with eight rows per group; at 32 users, with
+// half the rows, it was 5% slower).
 template <int NT>
 __device__ __forceinline__ constexpr int tile_row(int e, int g) {
   return NT == 1 ? 8 * (e / 2) + 2 * g + e % 2 : 4 * g + e;
@@ -93,11 +97,10 @@ __device__ __forceinline__ TileOff<NT> tile_offsets(int U, int B, int nsym) {
 // descriptor (the 16-byte loads are those of full blocks).  The loads of Y
 // use the default policy: they share cache lines (with the nontemporal one
 // the lines were fetched again, 22-28% more bytes than the algorithm reads).
-template <int NT, int NC>
+template <int NT, int NC, int E>
 __device__ __forceinline__ void load_tile_slot(TileSlot &b, const TileOff<NT> &lo, const float2 *__restrict__ Hw,
                                                const float2 *__restrict__ Yw, int U, int B, int nsym, int rb,
                                                int r0, int r1, bool live) {
-  constexpr int E = kRows<NT>;
   const int nrow = live ? r1 - r0 : 0;
   const int ylen = live ? ((nsym - 1) * B + (r1 - r0)) * 8 : 0;
   const __amdgpu_buffer_rsrc_t rh =
@@ -163,31 +166,29 @@ __device__ __forceinline__ void tile_zero(TileAcc<NT> &a, TileMf<NT, NC> &m) {
     for (int n = 0; n < NC; ++n) m.k1[t][n] = m.k2[t][n] = m.k3[t][n] = z;
 }
 
-// BF16 operands of one row block: 8 rows per lane at NT = 1 (K = 32), 4 at
-// NT = 2 (K = 16).
+// BF16 operands of one row block of E rows per lane: 8 (K = 32) or 4 (K = 16).
 typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
 typedef short s4 __attribute__((ext_vector_type(4)));
-template <int NT>
-using BfVec = std::conditional_t<NT == 1, bf8, bf4>;
+template <int E>
+using BfVec = std::conditional_t<E == 8, bf8, bf4>;
 __device__ __forceinline__ f4 mma16(bf4 a, bf4 b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s4, a), __builtin_bit_cast(s4, b), c, 0, 0, 0);
 }
 
-template <int NT>
+template <int E>
 struct Split {
-  BfVec<NT> h, l;
+  BfVec<E> h, l;
 };
 // acc += a b with both operands split: hi lo + lo hi + hi hi
-template <int NT>
-__device__ __forceinline__ f4 mma_split(const Split<NT> &a, const Split<NT> &b, f4 c) {
+template <int E>
+__device__ __forceinline__ f4 mma_split(const Split<E> &a, const Split<E> &b, f4 c) {
   c = mma16(a.h, b.l, c);
   c = mma16(a.l, b.h, c);
   return mma16(a.h, b.h, c);
 }
 
-template <int NT, int NC, int PREC>
+template <int NT, int NC, int PREC, int E>
 __device__ __forceinline__ void gram_mf_tile(TileSlot &sl, TileAcc<NT> &acc, TileMf<NT, NC> &m) {
-  constexpr int E = kRows<NT>;
   if (!sl.full) {
 #pragma unroll
     for (int e = 0; e < E; ++e)
@@ -231,7 +232,7 @@ __device__ __forceinline__ void gram_mf_tile(TileSlot &sl, TileAcc<NT> &acc, Til
     }
   } else {
     static_assert(PREC == PREC_BF16X3_NR, "one-pass forms only");
-    Split<NT> hr[NT], hi[NT], yr[NC], yi[NC], ny[NC];
+    Split<E> hr[NT], hi[NT], yr[NC], yi[NC], ny[NC];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
 #pragma unroll
@@ -256,22 +257,22 @@ __device__ __forceinline__ void gram_mf_tile(TileSlot &sl, TileAcc<NT> &acc, Til
     }
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      acc.rr[2 * t] = mma_split<NT>(hr[t], hr[t], acc.rr[2 * t]);
-      acc.ri[2 * t] = mma_split<NT>(hr[t], hi[t], acc.ri[2 * t]);
-      acc.ii[2 * t] = mma_split<NT>(hi[t], hi[t], acc.ii[2 * t]);
+      acc.rr[2 * t] = mma_split<E>(hr[t], hr[t], acc.rr[2 * t]);
+      acc.ri[2 * t] = mma_split<E>(hr[t], hi[t], acc.ri[2 * t]);
+      acc.ii[2 * t] = mma_split<E>(hi[t], hi[t], acc.ii[2 * t]);
 #pragma unroll
       for (int n = 0; n < NC; ++n) {
-        m.k1[t][n] = mma_split<NT>(hr[t], yr[n], m.k1[t][n]);
-        m.k2[t][n] = mma_split<NT>(hr[t], yi[n], m.k2[t][n]);
-        m.k1[t][n] = mma_split<NT>(hi[t], yi[n], m.k1[t][n]);
-        m.k2[t][n] = mma_split<NT>(hi[t], ny[n], m.k2[t][n]);
+        m.k1[t][n] = mma_split<E>(hr[t], yr[n], m.k1[t][n]);
+        m.k2[t][n] = mma_split<E>(hr[t], yi[n], m.k2[t][n]);
+        m.k1[t][n] = mma_split<E>(hi[t], yi[n], m.k1[t][n]);
+        m.k2[t][n] = mma_split<E>(hi[t], ny[n], m.k2[t][n]);
       }
     }
     if constexpr (NT == 2) {
-      acc.rr[1] = mma_split<NT>(hr[1], hr[0], acc.rr[1]);
-      acc.ri[1] = mma_split<NT>(hr[1], hi[0], acc.ri[1]);
-      acc.ii[1] = mma_split<NT>(hi[1], hi[0], acc.ii[1]);
-      acc.ir = mma_split<NT>(hi[1], hr[0], acc.ir);
+      acc.rr[1] = mma_split<E>(hr[1], hr[0], acc.rr[1]);
+      acc.ri[1] = mma_split<E>(hr[1], hi[0], acc.ri[1]);
+      acc.ii[1] = mma_split<E>(hi[1], hi[0], acc.ii[1]);
+      acc.ir = mma_split<E>(hi[1], hr[0], acc.ir);
     }
   }
 }
@@ -338,9 +339,9 @@ __device__ __forceinline__ void tile_mf(const TileMf<NT, NC> &m, int n, Tiles<NT
 // 7.5 KB): with four nothing was faster and LAMA lost a wave (104 against
 // 98 us), and one stream over all rounds of an FD wave, which loads the next
 // round's first rows during a solve, was 2-8% slower.
-template <int NT, int NC, int PREC, class Seg, class Done>
+template <int NT, int NC, int PREC, int E, class Seg, class Done>
 __device__ __forceinline__ void gram_mf_stream(int ns, int U, int B, int nsym, Seg seg, Done done) {
-  constexpr int RPB = 4 * kRows<NT>;
+  constexpr int RPB = 4 * E;
   TileAcc<NT> acc;
   TileMf<NT, NC> m;
   tile_zero(acc, m);
@@ -353,7 +354,7 @@ __device__ __forceinline__ void gram_mf_stream(int ns, int U, int B, int nsym, S
   bool more = true;
   auto issue = [&](TileSlot &sl) -> bool {
     const bool valid = more;
-    load_tile_slot<NT, NC>(sl, lo, cur.Hw, cur.yw, U, B, nsym, crb, cur.r0, cur.r1, valid);
+    load_tile_slot<NT, NC, E>(sl, lo, cur.Hw, cur.yw, U, B, nsym, crb, cur.r0, cur.r1, valid);
     sl.s = cur.s;
     sl.last = crb + RPB >= cur.r1;
     if (valid) {
@@ -370,7 +371,7 @@ __device__ __forceinline__ void gram_mf_stream(int ns, int U, int B, int nsym, S
     return valid;
   };
   auto consume = [&](TileSlot &b) {
-    gram_mf_tile<NT, NC, PREC>(b, acc, m);
+    gram_mf_tile<NT, NC, PREC, E>(b, acc, m);
     if (b.last) {
       done(b.s, acc, m);
       tile_zero(acc, m);
@@ -644,7 +645,7 @@ __device__ __forceinline__ void pd_sym_task(const FwdArgs &a, int w0, int nvalid
   const int g = lane / UT, i = lane % UT;
   SymMf<NT, SM::NS> mf;
   const TileAddr ta = tile_addr();
-  gram_mf_stream<NT, NC, PREC>(nvalid, a.U, a.B, a.nsym, pd_seg(a, w0), [&](int s, const TileAcc<NT> &acc, const TileMf<NT, NC> &m) {
+  gram_mf_stream<NT, NC, PREC, sym_rows(NT, false)>(nvalid, a.U, a.B, a.nsym, pd_seg(a, w0), [&](int s, const TileAcc<NT> &acc, const TileMf<NT, NC> &m) {
     store_system<NT, NC, PREC>(sm, ta, mf, s, acc, m);
   });
   wave_sync();
@@ -707,7 +708,7 @@ __device__ __forceinline__ void fd_sym_task(const FwdArgs &a, int w, SM *sms, in
   for (int base = wv * NSYS; base < C; base += NW * NSYS) {
     const int nvalid = min(NSYS, C - base);
     SymMf<NT, SM::NS> mf;
-    gram_mf_stream<NT, 1, PREC>(nvalid, a.U, a.B, a.nsym, fd_seg(a, w, [base](int s) { return base + s; }),
+    gram_mf_stream<NT, 1, PREC, sym_rows(NT, true)>(nvalid, a.U, a.B, a.nsym, fd_seg(a, w, [base](int s) { return base + s; }),
                              [&](int s, const TileAcc<NT> &acc, const TileMf<NT, 1> &m) { store_system<NT, 1, PREC>(sm, ta, mf, s, acc, m); });
     wave_sync();
     LocalSolve<UT> r;
@@ -928,7 +929,7 @@ __device__ __forceinline__ void pd_direct_task(const FwdArgs &a, int w0, int nva
   const int lane = lane_id();
   const int kk = lane / 16, c = lane % 16;
   const float nanv = __int_as_float(0x7fc00000);
-  gram_mf_stream<NT, NC, PREC>(nvalid, a.U, a.B, a.nsym, pd_seg(a, w0), [&](int s, const TileAcc<NT> &acc, const TileMf<NT, NC> &m) {
+  gram_mf_stream<NT, NC, PREC, sym_rows(NT, false)>(nvalid, a.U, a.B, a.nsym, pd_seg(a, w0), [&](int s, const TileAcc<NT> &acc, const TileMf<NT, NC> &m) {
     const int w = w0 + s;
     Tiles<2 * NT - 1> G;
     tile_gram<NT, PREC>(tile_addr(), lds_addr(sm.f), acc, G);
@@ -996,7 +997,7 @@ __device__ __forceinline__ void fd_direct_task(const FwdArgs &a, int w, DirectLd
   const int ncl = wv < C ? (C - wv + NW - 1) / NW : 0;
   auto cluster = [wv](int s) { return wv + NW * s; };
   if (ncl > 0)
-    gram_mf_stream<NT, 1, PREC>(ncl, a.U, a.B, a.nsym, fd_seg(a, w, cluster), [&](int s, const TileAcc<NT> &acc, const TileMf<NT, 1> &m) {
+    gram_mf_stream<NT, 1, PREC, sym_rows(NT, true)>(ncl, a.U, a.B, a.nsym, fd_seg(a, w, cluster), [&](int s, const TileAcc<NT> &acc, const TileMf<NT, 1> &m) {
       const int c = cluster(s);
       Tiles<2 * NT - 1> G;
       Tiles<NT> Y, Z;
@@ -1060,14 +1061,14 @@ constexpr int sym_pd_per() {
 }
 
 template <int NT, int NC, int PREC>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void eq_symbols_pd_kernel(const FwdArgs a) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 3 : 2, 8))) void eq_symbols_pd_kernel(const FwdArgs a) {
   __shared__ SymLds<NT, sym_pd_per<NT>(), NC> sm;
   const int w0 = blockIdx.x * sym_pd_per<NT>();
   pd_sym_task<NT, NC, PREC>(a, w0, min(sym_pd_per<NT>(), a.W - w0), sm);
 }
 
 template <int NT, int PREC, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 8))) void eq_symbols_fd_kernel(const FwdArgs a) {
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1 && PREC == PREC_FP32 ? 4 : NT == 1 ? 3 : 2, 8))) void eq_symbols_fd_kernel(const FwdArgs a) {
   __shared__ SymLds<NT, 4 / NT> sm[NW];
   fd_sym_task<NT, PREC, NW>(a, blockIdx.x, sm, __builtin_amdgcn_readfirstlane(threadIdx.x / 64));
 }
