@@ -32,7 +32,7 @@ struct FwdArgs {
   float n0, rho, es;
   float ub;             // 1/E_s for the unbiased L-MMSE, else 0: the outputs are
                         // divided by the gain 1 - sigma2 * ub (exactly 1 at ub = 0)
-  int32_t spw;          // FD: subcarriers per wave
+  int32_t spw;          // FD: subcarriers per wave; PD: systems per work item
   // receive vectors: nsym per channel matrix in this launch (1 for the
   // single-vector entry points), y + w*ysw is the first of subcarrier w,
   // z + w*zsw its first estimate; vectors of one subcarrier are B (y) and
@@ -64,6 +64,17 @@ struct BwdArgs {
   // cluster c owns rows off[c] .. off[c+1]-1; read in words (cluster_rows)
   alignas(4) uint16_t off[EQ_MAX_C + 2];
 };
+
+// Systems per PD work item of at most `most` lane groups: fewer where W would
+// leave the chip short of waves (two per SIMD).  A wave streams its systems one
+// after the other, and its solve takes as long for one as for four.  MRC of 14
+// vectors at U = 16 took, with four each / one each, 56 / 26 us for 2,048
+// subcarriers of B = 256, 184 / 51 us for 512 of B = 1024.
+constexpr int kPdItems = 2048;
+inline int pd_share(int W, int most) {
+  const int n = (W + kPdItems - 1) / kPdItems;
+  return n < 1 ? 1 : n < most ? n : most;
+}
 
 // Host launchers (defined in the .hip files).
 hipError_t launch_forward(const FwdArgs &a, bool fd, int prec, hipStream_t s);

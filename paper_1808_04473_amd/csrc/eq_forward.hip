@@ -32,7 +32,7 @@ __device__ __forceinline__ void enqueue_fp64(const FwdArgs &a, int w) {
   if (pos >= 0 && pos < a.W) a.fb_list[pos] = w;  // capacity W
 }
 
-// PD systems per work item.  A 32-lane group streams 32 KiB..1 MiB per
+// Most PD systems per work item.  A 32-lane group streams 32 KiB..1 MiB per
 // system, so one system per item keeps the work items short enough to fill
 // the device several times over (two per item left most of it idle during
 // the last generation of workgroups).
@@ -209,14 +209,14 @@ __device__ __forceinline__ void fd_task(const FwdArgs &a, int w0, int nsub, SM *
   }
 }
 
-// PD: one wave per workgroup; workgroup b takes systems b per .. of W.
+// PD: one wave per workgroup; workgroup b takes systems b spw .. of W.
 template <int UT, int PREC>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(waves_target<UT, PREC, false>(), 8))) void eq_forward_pd_kernel(const FwdArgs a) {
   constexpr int per = pd_per<UT, PREC>();
   // work items of fewer systems than lane groups need fewer matrix slots
   __shared__ SolveSmem<UT, refines(PREC), (per < 64 / UT ? per : 64 / UT)> sm;
-  const int w0 = blockIdx.x * per;
-  pd_task<UT, PREC>(a, w0, min(per, a.W - w0), sm);
+  const int w0 = blockIdx.x * a.spw;
+  pd_task<UT, PREC>(a, w0, min(a.spw, a.W - w0), sm);
 }
 
 // FD: blockDim / 64 waves per workgroup (fd_waves), `spw` subcarriers.
@@ -261,8 +261,9 @@ static hipError_t launch_one(const FwdArgs &a, hipStream_t s) {
     hipLaunchKernelGGL((eq_forward_fd_kernel<UT, PREC>), dim3((a.W + a.spw - 1) / a.spw), dim3(64 * nw),
                        nw * sizeof(SolveSmem<UT, refines(PREC)>), s, a);
   } else {
-    constexpr int per = pd_per<UT, PREC>();
-    hipLaunchKernelGGL((eq_forward_pd_kernel<UT, PREC>), dim3((a.W + per - 1) / per), dim3(64), 0, s, a);
+    FwdArgs b = a;
+    b.spw = pd_share(a.W, pd_per<UT, PREC>());
+    hipLaunchKernelGGL((eq_forward_pd_kernel<UT, PREC>), dim3((a.W + b.spw - 1) / b.spw), dim3(64), 0, s, b);
   }
   return hipGetLastError();
 }

@@ -74,7 +74,7 @@ __device__ __forceinline__ void lama_pd_task(const FwdArgs &a, int w0, int nvali
   const float nanv = __int_as_float(0x7fc00000);
   if (i < a.U) {
     a.z[(size_t)w * a.U + i] = o.bad ? make_float2(nanv, nanv) : o.z;
-    if (a.s2) a.s2[(size_t)w * a.U + i] = o.bad ? nanv : o.s2;
+    if (a.s2) a.s2[(size_t)w * a.zsw + i] = o.bad ? nanv : o.s2;
   }
   if (i == 0 && a.info) a.info[w] = o.bad ? -1 : 0;
 }
@@ -148,7 +148,7 @@ __device__ __forceinline__ void lama_fd_task(const FwdArgs &a, int w, Smem<UT> &
       so = inv;
     }
     a.z[(size_t)w * a.U + i] = zo;
-    if (a.s2) a.s2[(size_t)w * a.U + i] = so;
+    if (a.s2) a.s2[(size_t)w * a.zsw + i] = so;
   }
 }
 
@@ -161,16 +161,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(UT == 16 ? 3
   if constexpr (FD) {
     lama_fd_task<UT, PREC, M>(a, blockIdx.x, sm);
   } else {
-    const int w0 = blockIdx.x * (64 / UT);
-    lama_pd_task<UT, PREC, M>(a, w0, min(64 / UT, a.W - w0), sm);
+    const int w0 = blockIdx.x * a.spw;
+    lama_pd_task<UT, PREC, M>(a, w0, min(a.spw, a.W - w0), sm);
   }
 }
 
 template <int UT, int PREC, bool FD, int M>
 static hipError_t launch_lama_one(const FwdArgs &a, hipStream_t s) {
-  const int per = FD ? 1 : 64 / UT;
-  const int grid = (a.W + per - 1) / per;
-  hipLaunchKernelGGL((eq_lama_kernel<UT, PREC, FD, M>), dim3(grid), dim3(64), 0, s, a);
+  FwdArgs b = a;
+  b.spw = FD ? 1 : pd_share(a.W, 64 / UT);
+  hipLaunchKernelGGL((eq_lama_kernel<UT, PREC, FD, M>), dim3((a.W + b.spw - 1) / b.spw), dim3(64), 0, s, b);
   return hipGetLastError();
 }
 

@@ -152,16 +152,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(UT == 16 ? 4
   if constexpr (FD) {
     mrc_fd_task<UT, PREC>(a, blockIdx.x, sm);
   } else {
-    const int w0 = blockIdx.x * (64 / UT);
-    mrc_pd_task<UT, PREC>(a, w0, min(64 / UT, a.W - w0), sm);
+    const int w0 = blockIdx.x * a.spw;
+    mrc_pd_task<UT, PREC>(a, w0, min(a.spw, a.W - w0), sm);
   }
 }
 
 template <int UT, int PREC, bool FD>
 static hipError_t launch_mrc_one(const FwdArgs &a, hipStream_t s) {
-  const int per = FD ? 1 : 64 / UT;
-  const int grid = (a.W + per - 1) / per;
-  hipLaunchKernelGGL((eq_mrc_kernel<UT, PREC, FD>), dim3(grid), dim3(64), 0, s, a);
+  FwdArgs b = a;
+  b.spw = FD ? 1 : pd_share(a.W, 64 / UT);
+  hipLaunchKernelGGL((eq_mrc_kernel<UT, PREC, FD>), dim3((a.W + b.spw - 1) / b.spw), dim3(64), 0, s, b);
   return hipGetLastError();
 }
 

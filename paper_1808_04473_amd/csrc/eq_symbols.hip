@@ -1054,7 +1054,7 @@ __device__ __forceinline__ void fd_direct_task(const FwdArgs &a, int w, DirectLd
 }
 
 // ---------------------------------------------------------------- kernels
-// PD systems per work item: a round of lane groups.
+// Most PD systems per work item: a round of lane groups.
 template <int NT>
 constexpr int sym_pd_per() {
   return NT == 1 ? 4 : 1;
@@ -1063,8 +1063,8 @@ constexpr int sym_pd_per() {
 template <int NT, int NC, int PREC>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 3 : 2, 8))) void eq_symbols_pd_kernel(const FwdArgs a) {
   __shared__ SymLds<NT, sym_pd_per<NT>(), NC> sm;
-  const int w0 = blockIdx.x * sym_pd_per<NT>();
-  pd_sym_task<NT, NC, PREC>(a, w0, min(sym_pd_per<NT>(), a.W - w0), sm);
+  const int w0 = blockIdx.x * a.spw;
+  pd_sym_task<NT, NC, PREC>(a, w0, min(a.spw, a.W - w0), sm);
 }
 
 template <int NT, int PREC, int NW>
@@ -1076,8 +1076,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
 template <int NT, int NC, int PREC, int M>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void eq_direct_pd_kernel(const FwdArgs a) {
   __shared__ DirectLds<NT> sm;
-  const int w0 = blockIdx.x * sym_pd_per<NT>();
-  pd_direct_task<NT, NC, PREC, M>(a, w0, min(sym_pd_per<NT>(), a.W - w0), sm);
+  const int w0 = blockIdx.x * a.spw;
+  pd_direct_task<NT, NC, PREC, M>(a, w0, min(a.spw, a.W - w0), sm);
 }
 
 template <int NT, int PREC, int M, int NW>
@@ -1094,12 +1094,13 @@ static void launch_fd(const FwdArgs &a, hipStream_t s) {
 template <int NT, int PREC>
 static hipError_t launch_lmmse(const FwdArgs &a, bool fd, hipStream_t s) {
   if (!fd) {
-    constexpr int per = sym_pd_per<NT>();
-    const dim3 grid((a.W + per - 1) / per);
+    FwdArgs b = a;
+    b.spw = pd_share(a.W, sym_pd_per<NT>());
+    const dim3 grid((a.W + b.spw - 1) / b.spw);
     if (NT == 2 && a.nsym > 16)
-      hipLaunchKernelGGL((eq_symbols_pd_kernel<NT, NT, PREC>), grid, dim3(64), 0, s, a);
+      hipLaunchKernelGGL((eq_symbols_pd_kernel<NT, NT, PREC>), grid, dim3(64), 0, s, b);
     else
-      hipLaunchKernelGGL((eq_symbols_pd_kernel<NT, 1, PREC>), grid, dim3(64), 0, s, a);
+      hipLaunchKernelGGL((eq_symbols_pd_kernel<NT, 1, PREC>), grid, dim3(64), 0, s, b);
     return hipGetLastError();
   }
   // waves per subcarrier: its rounds of clusters, at most 2 (16 users) or 4.
@@ -1119,12 +1120,16 @@ static hipError_t launch_lmmse(const FwdArgs &a, bool fd, hipStream_t s) {
 template <int NT, int PREC, int M>
 static hipError_t launch_direct(const FwdArgs &a, bool fd, hipStream_t s) {
   if (!fd) {
-    constexpr int per = sym_pd_per<NT>();
-    const dim3 grid((a.W + per - 1) / per);
+    // the systems of an item share nothing but the start of a stream, which
+    // short ones notice (32,768 of B = 64: 100 us with four each, 105 with
+    // one; 16,384 of B = 256: 220 and 197)
+    FwdArgs b = a;
+    b.spw = a.B >= 256 ? 1 : pd_share(a.W, sym_pd_per<NT>());
+    const dim3 grid((a.W + b.spw - 1) / b.spw);
     if (NT == 2 && a.nsym > 16)
-      hipLaunchKernelGGL((eq_direct_pd_kernel<NT, NT, PREC, M>), grid, dim3(64), 0, s, a);
+      hipLaunchKernelGGL((eq_direct_pd_kernel<NT, NT, PREC, M>), grid, dim3(64), 0, s, b);
     else
-      hipLaunchKernelGGL((eq_direct_pd_kernel<NT, 1, PREC, M>), grid, dim3(64), 0, s, a);
+      hipLaunchKernelGGL((eq_direct_pd_kernel<NT, 1, PREC, M>), grid, dim3(64), 0, s, b);
   } else if (a.C > 1) {
     hipLaunchKernelGGL((eq_direct_fd_kernel<NT, PREC, M, 2>), dim3(a.W), dim3(128), 0, s, a);
   } else {
