@@ -24,10 +24,12 @@ struct LamaOut {
 };
 
 // Algorithm 1 for the system in `slot` (lane i: row i of G, y^MRC_i), with
-// the statistics scaled by `scale`, noise n0 and system ratio beta.
+// the statistics scaled by `scale`, noise n0 and system ratio beta.  A
+// non-finite y^MRC marks the system bad where it is the only vector; of
+// several it is left to give NaN for its own.
 template <int UT, int M, class SM>
 __device__ __forceinline__ LamaOut lama_local(SM &sm, int slot, int i, int U, float scale, float n0, float beta,
-                                              float es, int t_max) {
+                                              float es, int t_max, bool one) {
   Columns<UT> f;  // f.x[k] = conj(G_ik) * scale
   bool bad = false;
 #pragma unroll
@@ -37,7 +39,7 @@ __device__ __forceinline__ LamaOut lama_local(SM &sm, int slot, int i, int U, fl
     f.x[k] = make_float2(g.x * scale, -g.y * scale);
   }
   float2 m = sm.M[slot][i];
-  bad |= !finite2(m);
+  if (one) bad |= !finite2(m);
   m = make_float2(m.x * scale, m.y * scale);
   LamaOut o;
   o.bad = gany<UT>(bad);
@@ -53,7 +55,7 @@ __device__ __forceinline__ void lama_pd_task(const FwdArgs &a, int w0, int nvali
   auto seg = [&](int s, const float2 *&Hw, const float2 *&yw, int &r0, int &r1) {
     const size_t w = (size_t)w0 + s;
     Hw = a.H + w * HB;
-    yw = a.y + w * a.B;
+    yw = a.y + w * (size_t)a.ysw + (size_t)blockIdx.y * a.B;
     r0 = 0;
     r1 = a.B;
   };
@@ -68,13 +70,13 @@ __device__ __forceinline__ void lama_pd_task(const FwdArgs &a, int w0, int nvali
   }
   __syncthreads();
   const float beta = (float)a.U / (float)a.B;
-  const LamaOut o = lama_local<UT, M>(sm, g, i, a.U, 1.0f, a.n0, beta, a.es, a.lama_t);
+  const LamaOut o = lama_local<UT, M>(sm, g, i, a.U, 1.0f, a.n0, beta, a.es, a.lama_t, a.nsym == 1);
   if (g >= nvalid) return;
   const int w = w0 + g;
   const float nanv = __int_as_float(0x7fc00000);
   if (i < a.U) {
-    a.z[(size_t)w * a.U + i] = o.bad ? make_float2(nanv, nanv) : o.z;
-    if (a.s2) a.s2[(size_t)w * a.zsw + i] = o.bad ? nanv : o.s2;
+    a.z[(size_t)w * a.zsw + blockIdx.y * a.U + i] = o.bad ? make_float2(nanv, nanv) : o.z;
+    if (a.s2) a.s2[(size_t)w * a.zsw + blockIdx.y * a.U + i] = o.bad ? nanv : o.s2;
   }
   if (i == 0 && a.info) a.info[w] = o.bad ? -1 : 0;
 }
@@ -94,7 +96,7 @@ __device__ __forceinline__ void lama_fd_task(const FwdArgs &a, int w, Smem<UT> &
     const int nvalid = min(NSYS, C - base);
     auto seg = [&](int s, const float2 *&Hw, const float2 *&yw, int &r0, int &r1) {
       Hw = a.H + (size_t)w * HB;
-      yw = a.y + (size_t)w * a.B;
+      yw = a.y + (size_t)w * a.ysw + (size_t)blockIdx.y * a.B;
       cluster_rows<FwdArgs>(base + s, r0, r1);
     };
     gram_stream<UT, PREC, kLoadLast>(nvalid, a.U, seg, [&](int s, const Acc<UT> &acc, float2 mf) {
@@ -112,7 +114,7 @@ __device__ __forceinline__ void lama_fd_task(const FwdArgs &a, int w, Smem<UT> &
     // w_c of this lane group's cluster (1 for groups past the round)
     const float wc = live ? (float)(a.off[c + 1] - a.off[c]) / (float)a.B : 1.0f;
     const float iw = 1.0f / wc;
-    const LamaOut o = lama_local<UT, M>(sm, g, i, a.U, iw, a.n0 * iw, beta * iw, a.es, a.lama_t);
+    const LamaOut o = lama_local<UT, M>(sm, g, i, a.U, iw, a.n0 * iw, beta * iw, a.es, a.lama_t, a.nsym == 1);
     if (live && i == 0 && a.info) a.info[(size_t)w * C + c] = o.bad ? -1 : 0;
     sm.F[g][i] = live ? (o.bad ? make_float4(nanv, nanv, nanv, 1.f) : make_float4(o.z.x, o.z.y, o.s2, 1.f))
                       : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -147,14 +149,15 @@ __device__ __forceinline__ void lama_fd_task(const FwdArgs &a, int w, Smem<UT> &
       zo = make_float2(szx * inv, szy * inv);
       so = inv;
     }
-    a.z[(size_t)w * a.U + i] = zo;
-    if (a.s2) a.s2[(size_t)w * a.zsw + i] = so;
+    a.z[(size_t)w * a.zsw + blockIdx.y * a.U + i] = zo;
+    if (a.s2) a.s2[(size_t)w * a.zsw + blockIdx.y * a.U + i] = so;
   }
 }
 
 // One wave per workgroup: NSYS subcarriers per work item (PD) or one
 // subcarrier with all its clusters (FD).  3 waves per SIMD at UT = 16: the
 // row of G, the iterates and the denoiser's level terms spill at 4.
+// Block row y of the grid takes receive vector y.
 template <int UT, int PREC, bool FD, int M>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(UT == 16 ? 3 : 2, 8))) void eq_lama_kernel(const FwdArgs a) {
   __shared__ Smem<UT> sm;
@@ -170,7 +173,7 @@ template <int UT, int PREC, bool FD, int M>
 static hipError_t launch_lama_one(const FwdArgs &a, hipStream_t s) {
   FwdArgs b = a;
   b.spw = FD ? 1 : pd_share(a.W, 64 / UT);
-  hipLaunchKernelGGL((eq_lama_kernel<UT, PREC, FD, M>), dim3((a.W + b.spw - 1) / b.spw), dim3(64), 0, s, b);
+  hipLaunchKernelGGL((eq_lama_kernel<UT, PREC, FD, M>), dim3((a.W + b.spw - 1) / b.spw, a.nsym), dim3(64), 0, s, b);
   return hipGetLastError();
 }
 

@@ -170,3 +170,30 @@ def test_lama_symbols_non_finite_vector(mode):
     keep = np.ones(z.shape[:2], bool)
     keep[2, 3] = False
     assert np.isfinite(z[keep]).all()
+
+
+@pytest.mark.parametrize("mode", ["pd", "fd"])
+@pytest.mark.parametrize("prec", ["fp32", "bf16x3"])
+@pytest.mark.parametrize("shape,t_max", [
+    ((7, 40, 8, [0, 13, 25, 40], 2), 2), ((7, 40, 8, [0, 13, 25, 40], 2), 3),
+    ((5, 67, 16, [0, 17, 33, 50, 67], 3), 4), ((5, 67, 16, [0, 17, 33, 50, 67], 4), 4),
+    ((4, 96, 17, 2, 2), 4), ((4, 96, 17, 2, 2), 5), ((3, 100, 32, [0, 34, 66, 100], 3), 7)])
+def test_lama_symbols_few_vectors(mode, prec, shape, t_max):
+    """Vector and iteration counts on both sides of the line between a kernel
+    run per vector and the 16-vector tiles."""
+    _check_sym(mode, _sym_batch(shape, 16, seed=61), t_max, 16, prec)
+
+
+@pytest.mark.parametrize("mode", ["pd", "fd"])
+def test_lama_symbols_few_vectors_non_finite(mode):
+    """As for the tiles: NaN for that vector only, and no system code."""
+    from paper_1808_04473_amd import api
+    b = _sym_batch((6, 64, 8, 2, 2), 16, seed=62)
+    b.Y[2, 1, 17] = np.complex64(complex(np.nan, 0.0))
+    fn = api.eq_pd_lama_sym if mode == "pd" else api.eq_fd_lama_sym
+    z, s2, info = fn(dev(b.H), dev(b.Y), b.n0, b.cluster_off, t_max=3, qam=16, return_info=True)
+    torch.cuda.synchronize()
+    z = host(z)
+    assert np.isnan(z[2, 1]).all() and (host(info) == 0).all()
+    z[2, 1] = 0
+    assert np.isfinite(z).all()
