@@ -227,3 +227,29 @@ def test_config5_user_weights_directional_fp64_finite_difference():
     print(f"directional (user nu): fd64 {num:.6e} gpu {ana:.6e} (nu part {nu_part:.3e})", flush=True)
     assert abs(nu_part) > 0.05 * abs(ana)  # the nu direction carries weight in the check
     assert abs(num - ana) <= TOL * abs(num)
+
+
+EDGES = [
+    # W, B, U, offsets: U of 4 k and not, one to eight rounds of clusters and more
+    (3, 9, 1, [0, 9]),
+    (7, 41, 5, [0, 11, 30, 41]),
+    (4, 72, 8, list(range(0, 73, 9))),
+    (3, 320, 8, list(range(0, 321, 10))),     # 32 clusters: 8 rounds at 16 users
+    (3, 330, 8, list(range(0, 331, 10))),     # 33: 9 rounds
+    (3, 297, 7, list(range(0, 298, 9))),
+    (3, 160, 15, list(range(0, 161, 32))),
+    (2, 320, 20, list(range(0, 321, 20))),    # 16 clusters: 8 rounds at 32 users
+    (2, 374, 17, list(range(0, 375, 22))),    # 17: 9 rounds
+    (2, 70, 31, [0, 34, 70]),
+]
+
+
+@pytest.mark.parametrize("case", EDGES, ids=lambda c: f"W{c[0]}B{c[1]}U{c[2]}C{len(c[3]) - 1}")
+def test_pd_backward_edges(case):
+    test_pd_backward_vs_oracle(case, True)
+
+
+@pytest.mark.parametrize("case", EDGES, ids=lambda c: f"W{c[0]}B{c[1]}U{c[2]}C{len(c[3]) - 1}")
+@pytest.mark.parametrize("user_nu", [False, True])
+def test_fd_backward_edges(case, user_nu):
+    test_fd_backward_vs_oracle(case, user_nu)

@@ -261,3 +261,44 @@ def test_kernel_timer_times_each_forward_launch():
     with api.KernelTimer(4) as kt2:
         pass
     assert kt2.count == 0
+
+
+# ------------------------------------------------------------------ edges of the solve, waves per subcarrier
+@pytest.mark.parametrize("U", [1, 2, 4, 5, 8, 9, 15, 16, 17, 20, 24, 31, 32])
+@pytest.mark.parametrize("C", [1, 2, 3, 5, 9])
+@pytest.mark.parametrize("mode", ["pd", "fd"])
+@pytest.mark.parametrize("prec", PRECS)
+def test_elimination_edges(U, C, mode, prec):
+    """User counts around the column groups and blocks of the elimination;
+    cluster counts that leave one to four waves of a subcarrier full, partial
+    or with a round of one system."""
+    Bc = U + 9
+    off = [c * Bc + (c % 2) for c in range(C)] + [C * Bc + 1]
+    b = synth.make_batch(5, C * Bc + 1, U, 1, 12.0, "16qam", seed=31 * U + C, cluster_off=[0] + off[1:])
+    check(mode, b, prec)
+
+
+@pytest.mark.parametrize("U", [3, 16])
+@pytest.mark.parametrize("W", [2049, 4099, 6145])
+@pytest.mark.parametrize("op", ["pd", "mrc", "pd_sym", "mrc_sym", "lama", "lama_sym"])
+def test_pd_systems_per_item(op, U, W):
+    """Two to four systems per PD work item: each system's results are those
+    of a batch small enough to give every system its own."""
+    from paper_1808_04473_amd import api
+    B, S, off = 19, 3, [0, 19]
+    g = torch.Generator(device="cuda").manual_seed(W + U)
+    H = torch.randn(W, B, U, generator=g, device="cuda", dtype=torch.complex64)
+    Y = torch.randn(W, S, B, generator=g, device="cuda", dtype=torch.complex64)
+    y = Y[:, 0].contiguous()
+    run_op = {
+        "pd": lambda s: api.eq_pd(H[s], y[s], 0.1, off),
+        "mrc": lambda s: api.eq_pd(H[s], y[s], 0.1, off, equalizer="mrc"),
+        "pd_sym": lambda s: api.eq_pd_sym(H[s], Y[s], 0.1, off),
+        "mrc_sym": lambda s: api.eq_pd_sym(H[s], Y[s], 0.1, off, equalizer="mrc"),
+        "lama": lambda s: api.eq_pd_lama(H[s], y[s], 0.1, off),
+        "lama_sym": lambda s: api.eq_pd_lama_sym(H[s], Y[s], 0.1, off, t_max=1),
+    }[op]
+    z, s2 = run_op(slice(0, W))[:2]
+    for lo in (0, W - 1500):
+        zp, sp = run_op(slice(lo, lo + 1500))[:2]
+        assert torch.equal(z[lo:lo + 1500], zp) and torch.equal(s2[lo:lo + 1500], sp)

@@ -206,3 +206,18 @@ def test_mrc_symbols_user_without_channel():
     z, info = host(z), host(info)
     assert info[2] == 5 and np.isnan(z[2]).all()
     assert (info[np.arange(5) != 2] == 0).all() and np.isfinite(z[np.arange(5) != 2]).all()
+
+
+@pytest.mark.parametrize("mode", ["pd", "fd"])
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("S", [1, 2, 15, 16, 17, 32, 33])
+@pytest.mark.parametrize("shape", [(5, 33, 3, 2), (4, 63, 16, 5), (3, 77, 17, 2), (3, 160, 32, 5)],
+                         ids=lambda s: f"B{s[1]}U{s[2]}C{s[3]}")
+def test_symbol_tile_edges(mode, prec, S, shape):
+    """Vector counts at the edges of the 16-vector tiles, row blocks that end
+    inside a block of 16 or 32 rows, full and partial user tiles, and cluster
+    counts that leave a wave of a subcarrier a partial round."""
+    W, B, U, C = shape
+    cuts = [c * (B // C) + (c % 2 if 0 < c < C else 0) for c in range(C)] + [B]
+    b = synth.make_symbol_batch(W, B, U, C, S, 10.0, "16qam", seed=B + 7 * S, cluster_off=cuts)
+    check(mode, b, prec)
