@@ -775,7 +775,7 @@ def _gpu_main(args, cpu):
         "roofline": {"bound": "hbm", "achieved": head["kernel_alg_GBps"], "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": head["kernel_hbm_frac"],
                      "traffic": traffic,
-                     "kernel": "eq_forward_kernel<16, FP32, PD>",
+                     "kernel": "eq_forward_pd_kernel<16, FP32>",
                      "kernel_us_mean": head["kernel_ms_mean"] * 1e3,
                      "timing": f"kernel-timer HIP events on its stream, {head['kernel_launches_timed']} "
                                f"launches (second pass)",
