@@ -156,10 +156,13 @@ __device__ __forceinline__ void lama_fd_task(const FwdArgs &a, int w, Smem<UT> &
 
 // One wave per workgroup: NSYS subcarriers per work item (PD) or one
 // subcarrier with all its clusters (FD).  3 waves per SIMD at UT = 16: the
-// row of G, the iterates and the denoiser's level terms spill at 4.
+// row of G, the iterates and the denoiser's level terms spill at 4.  UT = 32: 2,
+// and FD no more than 2 even where the registers would hold 3: the LDS holds 8
+// waves a CU, and with room for a third on each SIMD they spread unevenly
+// (2,500 subcarriers of B = 512, U = 20, C = 8: 122 us against 103).
 // Block row y of the grid takes receive vector y.
 template <int UT, int PREC, bool FD, int M>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(UT == 16 ? 3 : 2, 8))) void eq_lama_kernel(const FwdArgs a) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(UT == 16 ? 3 : 2, UT == 32 && FD ? 2 : 8))) void eq_lama_kernel(const FwdArgs a) {
   __shared__ Smem<UT> sm;
   if constexpr (FD) {
     lama_fd_task<UT, PREC, M>(a, blockIdx.x, sm);

@@ -3,6 +3,7 @@ planted hazards in small listings are found, safe listings pass, and the
 assembly of the current build (when present) is clean."""
 import glob
 import os
+import re
 
 import pytest
 
@@ -82,3 +83,17 @@ def test_built_device_assembly_is_clean():
     # the factorisation's fused broadcasts are present in the forward kernels
     fwd = [f for f in files if "eq_forward" in f]
     assert fwd and "v_fmac_f32_dpp" in open(fwd[0]).read()
+
+
+def test_lama_fd_waves_per_simd():
+    """FD LAMA above 16 users allots registers for two waves per SIMD: with
+    room for a third the eight that LDS holds on a CU spread unevenly."""
+    f = build.device_asm("eq_lama.hip")
+    if not os.path.exists(f):
+        pytest.skip("no device assembly in the build folder (run python -m paper_1808_04473_amd.build)")
+    text = open(f).read()
+    found = 0
+    for m in re.finditer(r"\.amdhsa_kernel (\S*eq_lama_kernelILi32ELi\dELb1\S*)\n.*?\.amdhsa_next_free_vgpr (\d+)", text, re.S):
+        found += 1
+        assert 168 < int(m.group(2)) <= 256, m.group(1)  # 512 per SIMD, in units of 8
+    assert found
