@@ -225,7 +225,7 @@ eq_status forward_lama(const eq_problem *p, bool fd, int32_t t_max, int32_t qam_
 }
 
 // LAMA over several receive vectors: Y [W][nsym][B], Z and sigma2
-// [W][nsym][U]; tiles of up to symbol_tile(U, fd) vectors, each reading H once.
+// [W][nsym][U]; passes of up to symbol_tile(U, fd) vectors, each reading H once.
 eq_status forward_lama_sym(const eq_problem *p, bool fd, int32_t nsym, int32_t t_max, int32_t qam_order,
                            const eq_c32 *H, const eq_c32 *Y, const float *nu, eq_c32 *Z, float *s2, int32_t *info,
                            void *stream) {
@@ -251,18 +251,10 @@ eq_status forward_lama_sym(const eq_problem *p, bool fd, int32_t nsym, int32_t t
   a.info = info;
   a.lama_t = t_max;
   a.lama_m = qam_order == 4 ? 2 : (qam_order == 16 ? 4 : 8);
+  a.lama_sym = 1;
   a.ysw = (int64_t)nsym * p->B;
   a.zsw = (int64_t)nsym * p->U;
-  // A tile of 16 vectors costs the same for any number of them, and its
-  // iterations bound it; the single-vector kernel, once per vector in one
-  // launch, reads H again, but its iterations are nearly free.  FD, t_max = 3,
-  // B = 111, C = 12, U = 9, tile / single: 3,586 subcarriers, 2 vectors of
-  // QPSK 104 / 73 us (in launches of their own, 12,000 subcarriers, 2 vectors
-  // of 64-QAM 516 / 275, 3 vectors 515 / 412; QPSK 315 / 358); t_max = 1, 2
-  // vectors: 108 / 211.  U = 32, B = 512, C = 8: 2 vectors at t_max = 3
-  // 251 / 271, QPSK 187 / 256.
-  const bool single = nsym > 1 && nsym <= (t_max - 1) / (p->U > 16 ? 2 : 1);
-  const int tile = single ? nsym : symbol_tile(p->U, fd);
+  const int tile = symbol_tile(p->U, fd);
   const int prec = p->precision == EQ_FP32 ? PREC_FP32 : PREC_BF16X3_NR;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   for (int s0 = 0; s0 < nsym; s0 += tile) {
@@ -270,7 +262,8 @@ eq_status forward_lama_sym(const eq_problem *p, bool fd, int32_t nsym, int32_t t
     a.y = reinterpret_cast<const float2 *>(Y) + (size_t)s0 * p->B;
     a.z = reinterpret_cast<float2 *>(Z) + (size_t)s0 * p->U;
     a.s2 = s2 ? s2 + (size_t)s0 * p->U : nullptr;
-    if ((single ? launch_lama(a, fd, prec, s) : launch_symbols_lama(a, fd, prec, s)) != hipSuccess) return EQ_EHIP;
+    const hipError_t e = lama_by_vector(a, fd) ? launch_lama(a, fd, prec, s) : launch_symbols_lama(a, fd, prec, s);
+    if (e != hipSuccess) return EQ_EHIP;
   }
   return EQ_OK;
 }

@@ -42,6 +42,7 @@ struct FwdArgs {
   int32_t eqz;          // Eqz; ZF runs the L-MMSE kernels with rho = 0
   int32_t lama_t;       // LAMA: iterations T_max
   int32_t lama_m;       // LAMA: levels per coordinate of the square QAM (2, 4, 8)
+  int32_t lama_sym;     // LAMA: 1 in the several-vector calls, whose info tells of G alone
   // cluster c owns rows off[c] .. off[c+1]-1; read in words (cluster_rows)
   alignas(4) uint16_t off[EQ_MAX_C + 2];
 };
@@ -71,8 +72,8 @@ struct BwdArgs {
 // vectors at U = 16 took, with four each / one each, 56 / 26 us for 2,048
 // subcarriers of B = 256, 184 / 51 us for 512 of B = 1024.
 constexpr int kPdItems = 2048;
-inline int pd_share(int W, int most) {
-  const int n = (W + kPdItems - 1) / kPdItems;
+inline int pd_share(int W, int most, int items = kPdItems) {
+  const int n = (W + items - 1) / items;
   return n < 1 ? 1 : n < most ? n : most;
 }
 
@@ -86,8 +87,11 @@ hipError_t launch_symbols(const FwdArgs &a, bool fd, int prec, hipStream_t s);
 int symbol_tile(int U, bool fd);
 // MRC (no factorisation): FP32 or split-BF16 Gram
 hipError_t launch_mrc(const FwdArgs &a, bool fd, int prec, hipStream_t s);
-// LAMA (Algorithm 1): FP32 or split-BF16 Gram; one receive vector, or a tile
-// of a.nsym <= symbol_tile(a.U, fd) vectors per channel matrix
+// LAMA (Algorithm 1): FP32 or split-BF16 Gram; a.nsym receive vectors per
+// channel matrix, one after the other in the lane groups (lama_by_vector: which
+// of the two is faster; at most 16), or a tile of a.nsym <= symbol_tile(a.U, fd)
+// at once
+bool lama_by_vector(const FwdArgs &a, bool fd);
 hipError_t launch_lama(const FwdArgs &a, bool fd, int prec, hipStream_t s);
 hipError_t launch_symbols_lama(const FwdArgs &a, bool fd, int prec, hipStream_t s);
 

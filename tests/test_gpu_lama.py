@@ -197,3 +197,70 @@ def test_lama_symbols_few_vectors_non_finite(mode):
     assert np.isnan(z[2, 1]).all() and (host(info) == 0).all()
     z[2, 1] = 0
     assert np.isfinite(z).all()
+
+
+@pytest.mark.parametrize("mode", ["pd", "fd"])
+@pytest.mark.parametrize("prec", ["fp32", "bf16x3"])
+@pytest.mark.parametrize("S", [1, 2, 3, 4, 5, 8, 9, 10, 11])
+@pytest.mark.parametrize("shape", [(5, 80, 5, [0, 20, 41, 60, 80]), (3, 260, 16, [0, 64, 129, 193, 260]), (3, 150, 17, 2),
+                                   (3, 260, 32, [0, 130, 260])], ids=lambda s: f"B{s[1]}U{s[2]}")
+def test_lama_symbols_many_iterations(mode, prec, S, shape):
+    """Vector after vector in the lane groups, at the vector counts where its
+    stream changes form, and the tiles on the other side of the line."""
+    _check_sym(mode, _sym_batch(shape + (S,), 4, seed=63 + S), 12, 4, prec)
+
+
+@pytest.mark.parametrize("S,t_max", [(2, 6), (3, 6), (5, 8)])
+def test_lama_symbols_systems_per_wave(S, t_max):
+    """As many PD systems as fill the lane groups of a wave."""
+    _check_sym("pd", _sym_batch((6200, 24, 5, 1, S), 4, seed=64), t_max, 4, "fp32")
+
+
+def test_lama_symbols_many_iterations_given_weights():
+    b = _sym_batch((7, 120, 8, 3, 6), 4, seed=65)
+    nu = np.random.default_rng(7).uniform(0.1, 1.0, size=(7, 3, 8))
+    _check_sym("fd", b, 16, 4, "fp32", nu=nu)
+
+
+@pytest.mark.parametrize("mode", ["pd", "fd"])
+@pytest.mark.parametrize("U", [8, 32])
+def test_lama_symbols_of_an_interval_share_one_pass(mode, U):
+    """14 vectors are equalised from one Gram whatever the iteration count: in
+    the tile, where a vector's result does not depend on the others'."""
+    from paper_1808_04473_amd import api
+    fn = api.eq_pd_lama_sym if mode == "pd" else api.eq_fd_lama_sym
+    b = _sym_batch((6, 4 * U, U, 2, 16), 4, seed=66)
+    H, Y = dev(b.H), dev(b.Y)
+    for t_max in (16, 40):
+        z, s2 = fn(H, Y, b.n0, b.cluster_off, t_max=t_max, qam=4)
+        z14, s14 = fn(H, Y[:, :14].contiguous(), b.n0, b.cluster_off, t_max=t_max, qam=4)
+        assert torch.equal(z14, z[:, :14]) and torch.equal(s14, s2[:, :14])
+
+
+@pytest.mark.parametrize("mode", ["pd", "fd"])
+@pytest.mark.parametrize("U", [5, 16, 20])
+@pytest.mark.parametrize("t_max", [1, 3])
+def test_lama_symbols_of_one_vector_is_the_single_call(mode, U, t_max):
+    from paper_1808_04473_amd import api
+    b = _sym_batch((9, 3 * U + 6, U, 3 if mode == "fd" else 1, 1), 16, seed=67)
+    args = (b.n0, b.cluster_off, t_max, 16)
+    one, sym = (api.eq_pd_lama, api.eq_pd_lama_sym) if mode == "pd" else (api.eq_fd_lama, api.eq_fd_lama_sym)
+    z, s2 = one(dev(b.H), dev(b.Y[:, 0]), *args)
+    zs, ss = sym(dev(b.H), dev(b.Y), *args)
+    assert torch.equal(zs[:, 0], z) and torch.equal(ss[:, 0], s2)
+
+
+@pytest.mark.parametrize("mode", ["pd", "fd"])
+@pytest.mark.parametrize("S", [1, 3, 6])
+def test_lama_symbols_non_finite_vector_by_vector(mode, S):
+    """As for the tiles: NaN for that vector only, and no system code."""
+    from paper_1808_04473_amd import api
+    b = _sym_batch((6, 64, 8, 4, S), 4, seed=68)
+    b.Y[2, S - 1, 17] = np.complex64(complex(np.nan, 0.0))
+    fn = api.eq_pd_lama_sym if mode == "pd" else api.eq_fd_lama_sym
+    z, s2, info = fn(dev(b.H), dev(b.Y), b.n0, b.cluster_off, t_max=30, qam=4, return_info=True)
+    torch.cuda.synchronize()
+    z = host(z)
+    assert np.isnan(z[2, S - 1]).all() and (host(info) == 0).all()
+    z[2, S - 1] = 0
+    assert np.isfinite(z).all()
