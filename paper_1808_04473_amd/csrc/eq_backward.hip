@@ -147,6 +147,46 @@ __device__ __forceinline__ void ainv_blocks(float2 *As, Blocks<NT> &I) {
 template <int UT>
 using BwdLds = SolveSmem<UT, false>;
 
+// The second pass in the streaming layout, for gs = 0 and hence Q = 0: grad_H =
+// (y - H z) lambda^H - (H lambda) z^H (stream_rows says where).
+template <int UT, class Seg>
+__device__ __forceinline__ void rank1_rows(const BwdArgs &a, BwdLds<UT> &sm, int nvalid, Seg seg) {
+  const int lane = lane_id();
+  const int col = lane % UT, g = lane / UT;
+  const int U = a.U;
+  float2 zc = sm.M[0][col], lc = sm.M[0][UT + col];
+  stream_blocks<UT, kLoadLast>(
+      nvalid, U, seg,
+      [&](const Slot &b) {
+        float2 *gHw = a.gH ? a.gH + (b.Hw - a.H) : nullptr;
+        float2 *gyw = a.gy ? a.gy + (b.yw - a.y) : nullptr;
+        sfor<8>([&](auto E) {
+          constexpr int e = E;
+          const float2 h = slot_h<UT>(b, e, U);
+          const float hzx = gsum<UT>(h.x * zc.x - h.y * zc.y);
+          const float hzy = gsum<UT>(h.x * zc.y + h.y * zc.x);
+          const float hlx = gsum<UT>(h.x * lc.x - h.y * lc.y);
+          const float hly = gsum<UT>(h.x * lc.y + h.y * lc.x);
+          const float2 yv = slot_y<UT, e>(b);
+          const float rx = yv.x - hzx, ry = yv.y - hzy;
+          const int row = b.rb + slot_row(e, g);
+          if (row < b.r1) {
+            if (gHw && col < U)
+              gHw[(size_t)row * U + col] = make_float2(rx * lc.x + ry * lc.y - (hlx * zc.x + hly * zc.y),
+                                                       ry * lc.x - rx * lc.y - (hly * zc.x - hlx * zc.y));
+            if (gyw && col == 0) gyw[row] = make_float2(hlx, hly);
+          }
+        });
+      },
+      [&](int s) {
+        if (s + 1 < nvalid) {
+          zc = sm.M[s + 1][col];
+          lc = sm.M[s + 1][UT + col];
+        }
+      });
+  wave_sync();
+}
+
 // Gradients of one round of systems, X in the slots of sm.  Lane (sme, i)
 // holds the solve r and the upstream gradients gzc, gsc of user i of system
 // sme.  Returns this lane's share of grad_N0.
@@ -231,6 +271,10 @@ __device__ __forceinline__ float round_grads(const BwdArgs &a, BwdLds<UT> &sm, c
   }
 
   // ---- the rows again: grad_H and grad_y
+  if (!use_q && a.stream_rows) {
+    rank1_rows<UT>(a, sm, nvalid, seg);
+    return gn0;
+  }
   const RowOff<NT> off = row_offsets<NT, QUAD>(U);
   SysRef cur;
   int next = 0;
@@ -276,25 +320,22 @@ __device__ __forceinline__ float round_grads(const BwdArgs &a, BwdLds<UT> &sm, c
         zt[k] = sm.M[b.s][u];
         lt[k] = sm.M[b.s][UT + u];
       }
-      const float n2 = 2.f * a.n0;
+      if (use_q) {
+        const float n2 = 2.f * a.n0;
 #pragma unroll
-      for (int e = 0; e < NT; ++e) {
-        const float2 zc = sm.M[b.s][16 * e + c];
+        for (int e = 0; e < NT; ++e) {
+          const float2 zc = sm.M[b.s][16 * e + c];
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+          for (int t = 0; t < NT; ++t)
 #pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const float2 l = lt[4 * t + k];
-            float kr = l.x * zc.x + l.y * zc.y, ki = l.y * zc.x - l.x * zc.y;
-            if (use_q) {
-              // block (0, 1) is the conjugate transpose of (1, 0)
+            for (int k = 0; k < 4; ++k) {
+              const float2 l = lt[4 * t + k];
+              // block (0, 1) of Q is the conjugate transpose of (1, 0)
               const float2 qv = t >= e ? blk_el(As, t + e, 4 * kk + k, c) : blk_el(As, 1, c, 4 * kk + k);
-              kr = fmaf(n2, qv.x, kr);
-              ki = fmaf(t >= e ? n2 : -n2, qv.y, ki);
+              K.re[t][e][k] = fmaf(n2, qv.x, l.x * zc.x + l.y * zc.y);
+              K.im[t][e][k] = fmaf(t >= e ? n2 : -n2, qv.y, l.y * zc.x - l.x * zc.y);
             }
-            K.re[t][e][k] = kr;
-            K.im[t][e][k] = ki;
-          }
+        }
       }
     }
     // (H z), (H lambda) of row c
@@ -319,18 +360,27 @@ __device__ __forceinline__ float round_grads(const BwdArgs &a, BwdLds<UT> &sm, c
           (void *)(a.gH + (b.Hw - a.H) + (size_t)b.r0 * U), (short)0, nrow * U * 8, kBufFlags);
 #pragma unroll
       for (int e = 0; e < NT; ++e) {
-        // (H K)_{row c, 16 e + 4 kk + k}
+        // (H K)_{row c, 16 e + 4 kk + k}; without Q it is (H lambda) z^H
         f4 pr = {0.f, 0.f, 0.f, 0.f}, pi = pr;
+        if (use_q) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+          for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              const float2 h = b.h[4 * t + k];
+              pr = mma32(K.re[t][e][k], h.x, pr);
+              pi = mma32(K.re[t][e][k], h.y, pi);
+              pr = mma32(-K.im[t][e][k], h.y, pr);
+              pi = mma32(K.im[t][e][k], h.x, pi);
+            }
+        } else {
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
-            const float2 h = b.h[4 * t + k];
-            pr = mma32(K.re[t][e][k], h.x, pr);
-            pi = mma32(K.re[t][e][k], h.y, pi);
-            pr = mma32(-K.im[t][e][k], h.y, pr);
-            pi = mma32(K.im[t][e][k], h.x, pi);
+            const float2 z = zt[4 * e + k];
+            pr[k] = hlx * z.x + hly * z.y;
+            pi[k] = hly * z.x - hlx * z.y;
           }
+        }
         float2 g[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -568,14 +618,25 @@ int backward_tasks(int W, int U, int C, bool fd, int *spw) {
   return fd ? (W + *spw - 1) / *spw : (W + nsys - 1) / nsys;
 }
 
+// Layout of the second pass where gs is zero.  The MFMA layout needs fewer
+// instructions, but its lanes take 16 bytes (8 where U is not a multiple of 4)
+// of 16 rows at a time, and where the launch fills the chip those accesses
+// bound it: then rows of 128 bytes (U = 16) and of odd lengths take the
+// streaming layout.  MFMA / streaming, us, PD: 9,600 subcarriers of B = 256, U
+// = 8: 127 / 150, U = 12: 180 / 198, U = 16: 232 / 213, U = 15: 276 / 237, U =
+// 32: 408 / 425, U = 31: 684 / 422; 1,200 of them (300 waves), U = 16: 56 / 76.
+static bool stream_rows(int U, int waves) { return (U % 4 != 0 || U == 16) && waves > 512; }
+
 template <int UT, bool QUAD>
-static void launch_bwd(const BwdArgs &a, bool fd, int ntasks, hipStream_t s) {
+static void launch_bwd(BwdArgs a, bool fd, int ntasks, hipStream_t s) {
   if (!fd) {
+    a.stream_rows = stream_rows(a.U, ntasks);
     hipLaunchKernelGGL((eq_backward_pd_kernel<UT, QUAD>), dim3(ntasks), dim3(64), 0, s, a);
     return;
   }
   const int rounds = a.spw > 1 ? 1 : (a.C * UT + 63) / 64;
   const int nw = rounds < kBwdWaves ? rounds : kBwdWaves;
+  a.stream_rows = stream_rows(a.U, ntasks > 512 ? ntasks : ntasks * nw);
   const dim3 grid(ntasks), block(64 * nw);
   const size_t lds = nw * sizeof(BwdLds<UT>);
   if (rounds <= kBwdWaves)

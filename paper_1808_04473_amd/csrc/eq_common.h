@@ -62,6 +62,7 @@ struct BwdArgs {
   int32_t W, B, U, C;
   float n0, rho, es;
   int32_t spw;
+  int32_t stream_rows;  // second pass without Q in the streaming layout
   // cluster c owns rows off[c] .. off[c+1]-1; read in words (cluster_rows)
   alignas(4) uint16_t off[EQ_MAX_C + 2];
 };

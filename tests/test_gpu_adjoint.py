@@ -253,3 +253,52 @@ def test_pd_backward_edges(case):
 @pytest.mark.parametrize("user_nu", [False, True])
 def test_fd_backward_edges(case, user_nu):
     test_fd_backward_vs_oracle(case, user_nu)
+
+
+# W on both sides of 512 waves, U a multiple of 4, of 128-byte rows and neither
+@pytest.mark.parametrize("W", [5, 2100])
+@pytest.mark.parametrize("U", [1, 7, 8, 15, 16, 20, 31, 32])
+def test_backward_of_the_estimates_alone(W, U):
+    from paper_1808_04473_amd import api
+    off = [0, U + 3, 2 * U + 5, 3 * U + 6]
+    B = off[-1]
+    b = synth.make_batch(W, B, U, 1, 10.0, "16qam", seed=W + U, cluster_off=off)
+    gz, _ = _upstream(W, U, 11, False)
+    nu = np.random.default_rng(3).uniform(0.1, 0.9, size=(W, 3, U)).astype(np.float32)
+    H, y, g = dev(b.H), dev(b.y), dev(gz)
+    gH, gy, gn0 = api.eq_pd_backward(H, y, b.n0, off, gz=g)
+    rH, ry, rn0 = oracle.pd_backward(b.H, b.y, b.n0, off, gz, None)
+    assert nrel(host(gH), rH) <= TOL and nrel(host(gy), ry) <= TOL and abs(float(gn0) - rn0) <= TOL * abs(rn0)
+    gH, gy, gn0, gnu = api.eq_fd_backward(H, y, b.n0, off, gz=g, nu=dev(nu))
+    rH, ry, rn0, rnu = oracle.fd_backward(b.H, b.y, b.n0, off, gz, np.zeros((W, U)), nu=nu)
+    assert nrel(host(gH), rH) <= TOL and nrel(host(gy), ry) <= TOL and abs(float(gn0) - rn0) <= TOL * abs(rn0)
+    assert nrel(host(gnu), rnu) <= TOL
+
+
+def test_backward_of_the_estimates_alone_skips_the_products():
+    """Without a gradient of sigma2 there is no H K to form (and U = 31 streams
+    its rows): about 0.6 of the time, where forming it anyway takes 1.0."""
+    from paper_1808_04473_amd import api
+    W, B, U = 2000, 1023, 31
+    g = torch.Generator(device="cuda").manual_seed(1)
+    H = torch.randn(W, B, U, generator=g, device="cuda", dtype=torch.complex64) / 32
+    y = torch.randn(W, B, generator=g, device="cuda", dtype=torch.complex64)
+    gz = torch.randn(W, U, generator=g, device="cuda", dtype=torch.complex64)
+    gs = torch.randn(W, U, generator=g, device="cuda")
+
+    def ms(gs):
+        best = 1e9
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                api.eq_pd_backward(H, y, 0.1, [0, B], gz=gz, gs=gs)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) / 10)
+        return best
+
+    ms(gs)
+    alone, both = ms(None), ms(gs)
+    print(f"adjoint of z {alone:.3f} ms, of z and sigma2 {both:.3f} ms", flush=True)
+    assert alone <= 0.85 * both
