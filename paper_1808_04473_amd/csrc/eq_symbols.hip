@@ -116,6 +116,7 @@ __device__ __forceinline__ void fuse_write(const FwdArgs &a, int w, const FuseSu
 }
 
 __device__ __forceinline__ void enqueue_fp64_sym(const FwdArgs &a, int w) {
+  if (!a.fb_count) return;
   const int pos = atomicAdd(a.fb_count, 1);
   if (pos >= 0 && pos < a.W) a.fb_list[pos] = w;  // capacity W
 }
@@ -685,11 +686,32 @@ constexpr int sym_pd_per() {
   return NT == 1 ? 4 : 1;
 }
 
+// The launch arguments of block row y of the grid: its 16 vectors.  The others
+// of a subcarrier leave what does not depend on the vector to row 0.
+template <bool PERSYM>
+__device__ __forceinline__ FwdArgs tile_args(const FwdArgs &a) {
+  FwdArgs b = a;
+  const int s0 = 16 * blockIdx.y;
+  b.nsym = min(16, a.nsym - s0);
+  b.y += (size_t)s0 * a.B;
+  b.z += (size_t)s0 * a.U;
+  if (PERSYM && a.s2) b.s2 += (size_t)s0 * a.U;
+  if (s0) {
+    if (!PERSYM) b.s2 = nullptr;
+    b.info = nullptr;
+    b.fb_count = nullptr;
+  }
+  return b;
+}
+
 template <int NT, int NC, int PREC>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 3 : 2, 8))) void eq_symbols_pd_kernel(const FwdArgs a) {
   __shared__ SymLds<NT, sym_pd_per<NT>(), NC> sm;
   const int w0 = blockIdx.x * a.spw;
-  pd_sym_task<NT, NC, PREC>(a, w0, min(a.spw, a.W - w0), sm);
+  if constexpr (NT == 2 && NC == 1)
+    pd_sym_task<NT, NC, PREC>(tile_args<false>(a), w0, min(a.spw, a.W - w0), sm);
+  else
+    pd_sym_task<NT, NC, PREC>(a, w0, min(a.spw, a.W - w0), sm);
 }
 
 template <int NT, int PREC, int NW>
@@ -702,7 +724,10 @@ template <int NT, int NC, int PREC, int M>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void eq_direct_pd_kernel(const FwdArgs a) {
   __shared__ DirectLds<NT> sm;
   const int w0 = blockIdx.x * a.spw;
-  pd_direct_task<NT, NC, PREC, M>(a, w0, min(a.spw, a.W - w0), sm);
+  if constexpr (NT == 2 && NC == 1)
+    pd_direct_task<NT, NC, PREC, M>(tile_args<M != 0>(a), w0, min(a.spw, a.W - w0), sm);
+  else
+    pd_direct_task<NT, NC, PREC, M>(a, w0, min(a.spw, a.W - w0), sm);
 }
 
 template <int NT, int PREC, int M, int NW>
@@ -716,14 +741,20 @@ static void launch_fd(const FwdArgs &a, hipStream_t s) {
   hipLaunchKernelGGL((eq_symbols_fd_kernel<NT, PREC, NW>), dim3(a.W), dim3(64 * NW), 0, s, a);
 }
 
+// PD above 16 users, 17 to 32 vectors: a wave for each 16 while the chip has a
+// SIMD for both, which then take as long as one (MRC, split BF16, 24 vectors,
+// one wave / two, us: 512 subcarriers of B = 1024, U = 32: 59 / 54; 100 of B =
+// 4096: 212 / 185; 600 of B = 1024, U = 24: 59 / 77).
+static bool split_tiles(int W) { return W <= 512; }
+
 template <int NT, int PREC>
 static hipError_t launch_lmmse(const FwdArgs &a, bool fd, hipStream_t s) {
   if (!fd) {
     FwdArgs b = a;
     b.spw = pd_share(a.W, sym_pd_per<NT>());
-    const dim3 grid((a.W + b.spw - 1) / b.spw);
-    if (NT == 2 && a.nsym > 16)
-      hipLaunchKernelGGL((eq_symbols_pd_kernel<NT, NT, PREC>), grid, dim3(64), 0, s, b);
+    const dim3 grid((a.W + b.spw - 1) / b.spw, (a.nsym + 15) / 16);
+    if (NT == 2 && a.nsym > 16 && !split_tiles(a.W))
+      hipLaunchKernelGGL((eq_symbols_pd_kernel<NT, NT, PREC>), dim3(grid.x), dim3(64), 0, s, b);
     else
       hipLaunchKernelGGL((eq_symbols_pd_kernel<NT, 1, PREC>), grid, dim3(64), 0, s, b);
     return hipGetLastError();
@@ -750,9 +781,9 @@ static hipError_t launch_direct(const FwdArgs &a, bool fd, hipStream_t s) {
     // one; 16,384 of B = 256: 220 and 197)
     FwdArgs b = a;
     b.spw = a.B >= 256 ? 1 : pd_share(a.W, sym_pd_per<NT>());
-    const dim3 grid((a.W + b.spw - 1) / b.spw);
-    if (NT == 2 && a.nsym > 16)
-      hipLaunchKernelGGL((eq_direct_pd_kernel<NT, NT, PREC, M>), grid, dim3(64), 0, s, b);
+    const dim3 grid((a.W + b.spw - 1) / b.spw, (a.nsym + 15) / 16);
+    if (NT == 2 && a.nsym > 16 && !split_tiles(a.W))
+      hipLaunchKernelGGL((eq_direct_pd_kernel<NT, NT, PREC, M>), dim3(grid.x), dim3(64), 0, s, b);
     else
       hipLaunchKernelGGL((eq_direct_pd_kernel<NT, 1, PREC, M>), grid, dim3(64), 0, s, b);
   } else if (a.C > 1) {

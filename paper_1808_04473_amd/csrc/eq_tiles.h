@@ -203,6 +203,59 @@ __device__ __forceinline__ void gram_mf_tile(TileSlot &sl, TileAcc<NT> &acc, Til
         acc.ir = mma32(h1.y, h0.x, acc.ir);
       }
     }
+  } else if constexpr (NC == 2) {
+    static_assert(PREC == PREC_BF16X3_NR && E == 4, "one-pass forms only");
+    // Four rows are half of the k = 32 of a product, and k = 16 ones run at half
+    // the rate, which bounds this form.  Real and imaginary part side by side
+    // fill it where their products are summed: Re G, Re M = [Hr Hi]^T [Yr; Yi],
+    // Im M = [Hr Hi]^T [Yi; -Yr].  The sum is in rr, ii stays zero.  (With one
+    // symbol tile FD lost a wave per SIMD to the registers that it takes.)  MRC
+    // of 24 vectors, PD, 600 subcarriers of B = 1024, U = 24: 67 and 59 us.
+    Split<8> h[NT], y[NC], w[NC];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const float2 v = sl.h[NT * e + t];
+        h[t].h[e] = (__bf16)v.x;
+        h[t].l[e] = (__bf16)(v.x - (float)h[t].h[e]);
+        h[t].h[4 + e] = (__bf16)v.y;
+        h[t].l[4 + e] = (__bf16)(v.y - (float)h[t].h[4 + e]);
+      }
+#pragma unroll
+      for (int n = 0; n < NC; ++n) {
+        const float2 v = sl.y[NC * e + n];
+        y[n].h[e] = w[n].h[4 + e] = (__bf16)v.x;
+        y[n].l[e] = w[n].l[4 + e] = (__bf16)(v.x - (float)y[n].h[e]);
+        y[n].h[4 + e] = w[n].h[e] = (__bf16)v.y;
+        y[n].l[4 + e] = w[n].l[e] = (__bf16)(v.y - (float)y[n].h[4 + e]);
+        // round-to-nearest-even is symmetric: the split of -yr is the negated split
+        w[n].h[4 + e] = -w[n].h[4 + e];
+        w[n].l[4 + e] = -w[n].l[4 + e];
+      }
+    }
+    auto part = [](const Split<8> &v, auto Im) {
+      constexpr int k = 4 * decltype(Im)::value;
+      return Split<4>{__builtin_shufflevector(v.h, v.h, k, k + 1, k + 2, k + 3),
+                      __builtin_shufflevector(v.l, v.l, k, k + 1, k + 2, k + 3)};
+    };
+    constexpr std::integral_constant<int, 0> Re{};
+    constexpr std::integral_constant<int, 1> Im{};
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      acc.rr[2 * t] = mma_split<8>(h[t], h[t], acc.rr[2 * t]);
+      acc.ri[2 * t] = mma_split<4>(part(h[t], Re), part(h[t], Im), acc.ri[2 * t]);
+#pragma unroll
+      for (int n = 0; n < NC; ++n) {
+        m.k1[t][n] = mma_split<8>(h[t], y[n], m.k1[t][n]);
+        m.k2[t][n] = mma_split<8>(h[t], w[n], m.k2[t][n]);
+      }
+    }
+    if constexpr (NT == 2) {
+      acc.rr[1] = mma_split<8>(h[1], h[0], acc.rr[1]);
+      acc.ri[1] = mma_split<4>(part(h[1], Re), part(h[0], Im), acc.ri[1]);
+      acc.ir = mma_split<4>(part(h[1], Im), part(h[0], Re), acc.ir);
+    }
   } else {
     static_assert(PREC == PREC_BF16X3_NR, "one-pass forms only");
     Split<E> hr[NT], hi[NT], yr[NC], yi[NC], ny[NC];

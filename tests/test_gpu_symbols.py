@@ -221,3 +221,70 @@ def test_symbol_tile_edges(mode, prec, S, shape):
     cuts = [c * (B // C) + (c % 2 if 0 < c < C else 0) for c in range(C)] + [B]
     b = synth.make_symbol_batch(W, B, U, C, S, 10.0, "16qam", seed=B + 7 * S, cluster_off=cuts)
     check(mode, b, prec)
+
+
+@pytest.mark.parametrize("W", [512, 513])
+@pytest.mark.parametrize("S", [17, 31, 32, 33])
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("eqz", ["lmmse", "mrc", "lama"])
+def test_pd_symbols_above_16_vectors(W, S, prec, eqz):
+    """Either side of the batch size up to which every 16 vectors of a
+    subcarrier have a wave; some of the systems routed to FP64."""
+    from paper_1808_04473_amd import api
+    B, U = 40, 18
+    b = synth.make_symbol_batch(W, B, U, 1, S, 10.0, "16qam", seed=S)
+    H = b.H.copy()
+    ill = [3, W - 1]
+    if eqz == "lmmse":
+        rng = np.random.default_rng(14)
+        H[ill, :, 1] = H[ill, :, 0] + 1e-4 * (rng.standard_normal((2, B)) + 1j * rng.standard_normal((2, B)))
+        b.Y = np.matmul(b.x.astype(np.complex128), np.swapaxes(H.astype(np.complex128), 1, 2)).astype(np.complex64)
+        b.n0 = float(np.float32(1e-9))
+    some = np.array([0, 3, 4, W // 2, W - 2, W - 1])
+    args = (b.n0, b.cluster_off)
+    for rep in range(2):  # the FP64 queue starts empty each time
+        if eqz == "lama":
+            z, s2, info = api.eq_pd_lama_sym(dev(H), dev(b.Y), *args, t_max=2, qam=16, precision=prec, return_info=True)
+        else:
+            z, s2, info = api.eq_pd_sym(dev(H), dev(b.Y), *args, precision=prec, equalizer=eqz, return_info=True)
+        z, s2, info = host(z)[some], host(s2)[some], host(info)
+        for s in range(S):
+            y = b.Y[some][:, s]
+            if eqz == "lama":
+                zr, sr = oracle.eq_pd_lama(H[some], y, *args, 2, 16)
+            elif eqz == "mrc":
+                zr, sr = oracle.eq_pd_linear(H[some], y, *args, "mrc")
+            else:
+                zr, sr = oracle.eq_pd(H[some], y, *args)
+            assert max_rel_err(z[:, s], zr) <= TOL_Z[prec], s
+            assert max_db_err(s2[:, s] if eqz == "lama" else s2, sr) <= TOL_DB
+        flags = (info & (1 << 30)) != 0
+        assert flags[ill].all() if eqz == "lmmse" else not info.any()
+
+
+def test_pd_symbols_of_two_tiles_side_by_side():
+    """24 vectors of a batch that leaves SIMDs idle take about as long as 14
+    (1.0 of it, 1.3 with both tiles in one wave)."""
+    from paper_1808_04473_amd import api
+    W, B, U = 256, 2048, 32
+    g = torch.Generator(device="cuda").manual_seed(1)
+    H = torch.randn(W, B, U, generator=g, device="cuda", dtype=torch.complex64) / 32
+    Y = torch.randn(W, 24, B, generator=g, device="cuda", dtype=torch.complex64)
+
+    def ms(Y):
+        best = 1e9
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                api.eq_pd_sym(H, Y, 0.1, [0, B], precision="bf16x3", equalizer="mrc")
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) / 20)
+        return best
+
+    Y14 = Y[:, :14].contiguous()
+    ms(Y)
+    t14, t24 = ms(Y14), ms(Y)
+    print(f"MRC of 14 vectors {t14:.3f} ms, of 24 {t24:.3f} ms", flush=True)
+    assert t24 <= 1.15 * t14
