@@ -42,6 +42,7 @@ struct FwdArgs {
   int32_t eqz;          // Eqz; ZF runs the L-MMSE kernels with rho = 0
   int32_t lama_t;       // LAMA: iterations T_max
   int32_t lama_m;       // LAMA: levels per coordinate of the square QAM (2, 4, 8)
+  int32_t lama_per;     // LAMA vector by vector: vectors per wave
   int32_t lama_sym;     // LAMA: 1 in the several-vector calls, whose info tells of G alone
   // cluster c owns rows off[c] .. off[c+1]-1; read in words (cluster_rows)
   alignas(4) uint16_t off[EQ_MAX_C + 2];

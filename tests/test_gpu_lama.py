@@ -264,3 +264,42 @@ def test_lama_symbols_non_finite_vector_by_vector(mode, S):
     assert np.isnan(z[2, S - 1]).all() and (host(info) == 0).all()
     z[2, S - 1] = 0
     assert np.isfinite(z).all()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16x3"])
+@pytest.mark.parametrize("mode,shape", [
+    ("pd", (8300, 16, 3, 1, 4)), ("pd", (8300, 16, 3, 1, 5)), ("pd", (2500, 48, 20, 1, 2)), ("pd", (2500, 48, 20, 1, 5)),
+    ("fd", (1100, 105, 5, 5, 2)), ("fd", (1100, 105, 5, 7, 4)), ("fd", (700, 104, 5, 13, 5)), ("fd", (700, 120, 20, 3, 2)),
+    ("fd", (700, 160, 20, 4, 5)), ("fd", (300, 245, 17, 7, 8)), ("fd", (20, 104, 5, 13, 3)), ("fd", (20, 245, 17, 7, 3)),
+], ids=lambda v: v if isinstance(v, str) else f"W{v[0]}U{v[2]}C{v[3]}S{v[4]}")
+def test_lama_symbols_waves_and_vectors(mode, shape, prec):
+    """Vector after vector: each number of vectors per wave, and of waves per
+    FD subcarrier, whose rounds do not divide among them.  Up to 4 vectors (2
+    above 16 users) the sums are the single call's, bit for bit; more come from
+    the tiles.  Among thousands of systems of 3 users the iterations amplify
+    rounding by up to 1e4, in the single call too: each system's bound is
+    scaled by what the oracle makes of a relative change of H and y by 1e-6."""
+    from paper_1808_04473_amd import api
+    b = _sym_batch(shape, 4, seed=69)
+    args = (b.n0, b.cluster_off, 4, 4)
+    one, sym = (api.eq_pd_lama, api.eq_pd_lama_sym) if mode == "pd" else (api.eq_fd_lama, api.eq_fd_lama_sym)
+    rf = oracle.eq_pd_lama if mode == "pd" else oracle.eq_fd_lama
+    z, s2 = sym(dev(b.H), dev(b.Y), *args, precision=prec)
+    H, Y = b.H.astype(np.complex128), b.Y.astype(np.complex128)
+    rng = np.random.default_rng(70)
+    pert = [[x * (1 + 1e-6 * rng.standard_normal(x.shape)) for x in (H, Y)] for _ in range(2)]
+    for s in range(b.Y.shape[1]):
+        if shape[4] <= (4 if shape[2] <= 16 else 2) or shape[0] == 20:
+            z1, s21 = one(dev(b.H), dev(b.Y[:, s]), *args, precision=prec)
+            assert torch.equal(z[:, s], z1) and torch.equal(s2[:, s], s21)
+        zr, sr = rf(H, Y[:, s], *args)
+        ref = np.abs(zr).max(1)
+        err = np.abs(host(z[:, s]) - zr).max(1) / ref
+        db = np.abs(10 * np.log10(host(s2[:, s]) / sr)).max(1)
+        kz, ks = np.ones(len(zr)), np.ones(len(zr))
+        for Hp, Yp in pert:
+            zp, sp = rf(Hp, Yp[:, s], *args)
+            kz = np.maximum(kz, np.abs(zp - zr).max(1) / ref / 1e-6)
+            ks = np.maximum(ks, np.abs(np.log(sp / sr)).max(1) / 1e-6)
+        assert (err <= TOL_Z[prec] * kz).all(), (s, (err / kz).max())
+        assert (db <= TOL_DB * ks).all(), (s, (db / ks).max())
