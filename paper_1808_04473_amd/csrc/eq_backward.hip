@@ -621,11 +621,15 @@ int backward_tasks(int W, int U, int C, bool fd, int *spw) {
 // Layout of the second pass where gs is zero.  The MFMA layout needs fewer
 // instructions, but its lanes take 16 bytes (8 where U is not a multiple of 4)
 // of 16 rows at a time, and where the launch fills the chip those accesses
-// bound it: then rows of 128 bytes (U = 16) and of odd lengths take the
-// streaming layout.  MFMA / streaming, us, PD: 9,600 subcarriers of B = 256, U
-// = 8: 127 / 150, U = 12: 180 / 198, U = 16: 232 / 213, U = 15: 276 / 237, U =
-// 32: 408 / 425, U = 31: 684 / 422; 1,200 of them (300 waves), U = 16: 56 / 76.
-static bool stream_rows(int U, int waves) { return (U % 4 != 0 || U == 16) && waves > 512; }
+// bound it: then rows of 128 bytes (U = 16) and those of odd lengths above 8
+// users take the streaming layout, but for 17 and 18 users, where its second
+// half row is nearly empty.  MFMA / streaming, us, PD: 9,600 subcarriers of B =
+// 256, U = 7: 138 / 146, U = 8: 127 / 150, U = 12: 180 / 198, U = 15: 276 / 237, U
+// = 16: 232 / 213, U = 17: 316 / 317, U = 31: 684 / 422, U = 32: 408 / 425; 1,200 of
+// them (300 waves), U = 16: 56 / 76.  60,000 of B = 16, U = 1: 72 / 90.
+static bool stream_rows(int U, int waves) {
+  return U > 8 && (U % 4 != 0 ? U % 16 > 2 : U == 16) && waves > 512;
+}
 
 template <int UT, bool QUAD>
 static void launch_bwd(BwdArgs a, bool fd, int ntasks, hipStream_t s) {
