@@ -639,11 +639,11 @@ static void launch_bwd(BwdArgs a, bool fd, int ntasks, hipStream_t s) {
     return;
   }
   const int rounds = a.spw > 1 ? 1 : (a.C * UT + 63) / 64;
-  const int nw = rounds < kBwdWaves ? rounds : kBwdWaves;
+  const int nw = waves_in_launch(ntasks, rounds < kBwdWaves ? rounds : kBwdWaves);
   a.stream_rows = stream_rows(a.U, ntasks > 512 ? ntasks : ntasks * nw);
   const dim3 grid(ntasks), block(64 * nw);
   const size_t lds = nw * sizeof(BwdLds<UT>);
-  if (rounds <= kBwdWaves)
+  if (rounds <= nw)
     hipLaunchKernelGGL((eq_backward_fd_kernel<UT, QUAD, true>), grid, block, lds, s, a);
   else
     hipLaunchKernelGGL((eq_backward_fd_kernel<UT, QUAD, false>), grid, block, lds, s, a);

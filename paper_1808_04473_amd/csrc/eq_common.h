@@ -79,6 +79,10 @@ inline int pd_share(int W, int most, int items = kPdItems) {
   return n < 1 ? 1 : n < most ? n : most;
 }
 
+// A launch takes fewer than 2^32 work-items along x: the waves of each of `n`
+// workgroups, all of them or one.
+inline int waves_in_launch(int n, int waves) { return (int64_t)n * waves < (1 << 26) ? waves : 1; }
+
 // Host launchers (defined in the .hip files).
 hipError_t launch_forward(const FwdArgs &a, bool fd, int prec, hipStream_t s);
 hipError_t launch_fp64_resolve(const FwdArgs &a, bool fd, hipStream_t s);

@@ -257,7 +257,7 @@ static hipError_t launch_one(const FwdArgs &a, hipStream_t s) {
   // at once (a one-generation grid with equal shares per workgroup measured
   // slower: its partial rounds add solves)
   if constexpr (FD) {
-    const int nw = a.spw > 1 ? 1 : fd_waves(UT, a.C);
+    const int nw = a.spw > 1 ? 1 : waves_in_launch(a.W, fd_waves(UT, a.C));
     hipLaunchKernelGGL((eq_forward_fd_kernel<UT, PREC>), dim3((a.W + a.spw - 1) / a.spw), dim3(64 * nw),
                        nw * sizeof(SolveSmem<UT, refines(PREC)>), s, a);
   } else {

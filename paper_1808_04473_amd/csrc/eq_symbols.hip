@@ -764,9 +764,10 @@ static hipError_t launch_lmmse(const FwdArgs &a, bool fd, hipStream_t s) {
   // with one wave each, 230 with two, 191 with four (4,800 of them 716, 709,
   // 684); of 9,600 of B = 256, C = 8, U = 16, 196, 182 and 182
   const int rounds = (a.C * NT + 3) / 4;
-  if (rounds == 1)
+  const int nw = waves_in_launch(a.W, rounds == 1 ? 1 : NT == 1 || rounds <= 3 ? 2 : 4);
+  if (nw == 1)
     launch_fd<NT, PREC, 1>(a, s);
-  else if (NT == 1 || rounds <= 3)
+  else if (nw == 2)
     launch_fd<NT, PREC, 2>(a, s);
   else
     launch_fd<NT, PREC, NT == 1 ? 2 : 4>(a, s);
@@ -780,13 +781,13 @@ static hipError_t launch_direct(const FwdArgs &a, bool fd, hipStream_t s) {
     // short ones notice (32,768 of B = 64: 100 us with four each, 105 with
     // one; 16,384 of B = 256: 220 and 197)
     FwdArgs b = a;
-    b.spw = a.B >= 256 ? 1 : pd_share(a.W, sym_pd_per<NT>());
+    b.spw = a.B >= 256 && a.W < (1 << 26) ? 1 : pd_share(a.W, sym_pd_per<NT>());
     const dim3 grid((a.W + b.spw - 1) / b.spw, (a.nsym + 15) / 16);
     if (NT == 2 && a.nsym > 16 && !split_tiles(a.W))
       hipLaunchKernelGGL((eq_direct_pd_kernel<NT, NT, PREC, M>), dim3(grid.x), dim3(64), 0, s, b);
     else
       hipLaunchKernelGGL((eq_direct_pd_kernel<NT, 1, PREC, M>), grid, dim3(64), 0, s, b);
-  } else if (a.C > 1) {
+  } else if (a.C > 1 && waves_in_launch(a.W, 2) == 2) {
     hipLaunchKernelGGL((eq_direct_fd_kernel<NT, PREC, M, 2>), dim3(a.W), dim3(128), 0, s, a);
   } else {
     hipLaunchKernelGGL((eq_direct_fd_kernel<NT, PREC, M, 1>), dim3(a.W), dim3(64), 0, s, a);
