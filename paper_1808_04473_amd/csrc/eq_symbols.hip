@@ -644,6 +644,7 @@ __device__ __forceinline__ void fd_direct_task(const FwdArgs &a, int w, DirectLd
         int r0, r1;
         cluster_rows<FwdArgs>(c, r0, r1);
         const float iw = 1.0f / ((float)(r1 - r0) / (float)a.B);
+        code = tiles_bad<2 * NT - 1>(G) ? -1 : 0;  // of G itself: 1 / w_c may overflow it
 #pragma unroll
         for (int b = 0; b < 2 * NT - 1; ++b) {
           G.re[b] *= iw;
@@ -656,7 +657,6 @@ __device__ __forceinline__ void fd_direct_task(const FwdArgs &a, int w, DirectLd
         }
         Tiles<1> T;
         tile_turn<NT>(sm.f, G, T);
-        code = tiles_bad<2 * NT - 1>(G) ? -1 : 0;
         const float tau = tile_lama<NT, M>(G, T, Y, a.U, a.n0 * iw, (float)a.U / (float)a.B * iw, a.es, a.lama_t, Z);
 #pragma unroll
         for (int t = 0; t < NT; ++t) s2[t] = tau;

@@ -303,3 +303,21 @@ def test_lama_symbols_waves_and_vectors(mode, shape, prec):
             ks = np.maximum(ks, np.abs(np.log(sp / sr)).max(1) / 1e-6)
         assert (err <= TOL_Z[prec] * kz).all(), (s, (err / kz).max())
         assert (db <= TOL_DB * ks).all(), (s, (db / ks).max())
+
+
+@pytest.mark.parametrize("U", [4, 20])
+@pytest.mark.parametrize("S", [2, 17])
+def test_lama_symbols_fd_info_is_of_the_gram_itself(U, S):
+    """A Gram that is finite, and not so divided by w_c = 1/2, is no bad input:
+    the single call's code, of the vector-by-vector calls and of the tiles."""
+    from paper_1808_04473_amd import api
+    b = _sym_batch((6, 64, U, 2, S), 4, seed=71)
+    H = b.H.copy()
+    H[2] *= 2.8e18 / np.abs(H[2])  # 32 |h|^2 = 2.5e38
+    H[4, 5, 1] = np.inf
+    args = (b.n0, b.cluster_off, 2, 4)
+    _, _, one = api.eq_fd_lama(dev(H), dev(b.Y[:, 0]), *args, return_info=True)
+    _, _, sym = api.eq_fd_lama_sym(dev(H), dev(b.Y), *args, return_info=True)
+    want = np.zeros((6, 2), np.int32)
+    want[4, 0] = -1
+    assert (host(one) == want).all() and (host(sym) == want).all()
