@@ -225,8 +225,13 @@ std::string key_rows(const eq_plan &p, int cls) {
   return buf;
 }
 
+bool is_launch_key(const std::string &k) { return k.size() >= 7 && k.compare(k.size() - 7, 7, "/launch") == 0; }
+bool is_fd_key(const std::string &k) { return k.find("/fd/") != std::string::npos; }
+
 // The cache is a JSON object with one entry per line:
 //   "<mode key>/launch": {"wpc": W},   "<mode key>/utNN": {"piece_rows": R},
+// FD launches also hold the waves of the workgroups that were timed, and are
+// tuned again where those were others: {"wpc": W, "waves": N}.
 std::map<std::string, int> read_cache(const std::string &path) {
   std::map<std::string, int> m;
   if (path.empty()) return m;
@@ -235,9 +240,9 @@ std::map<std::string, int> read_cache(const std::string &path) {
   char line[512];
   while (fgets(line, sizeof(line), f)) {
     char key[256];
-    int v = 0;
-    if (sscanf(line, " \"%255[^\"]\": {\"wpc\": %d}", key, &v) == 2) {
-      if (v >= 1 && v <= 64) m[key] = v;
+    int v = 0, waves = 1;
+    if (sscanf(line, " \"%255[^\"]\": {\"wpc\": %d, \"waves\": %d}", key, &v, &waves) >= 2) {
+      if (v >= 1 && v <= 64 && (!is_fd_key(key) || waves == kRaggedWaves)) m[key] = v;
     } else if (sscanf(line, " \"%255[^\"]\": {\"piece_rows\": %d}", key, &v) == 2) {
       if (v == 0 || (v >= 16 && v <= EQ_MAX_B)) m[key] = v;
     }
@@ -245,8 +250,6 @@ std::map<std::string, int> read_cache(const std::string &path) {
   fclose(f);
   return m;
 }
-
-bool is_launch_key(const std::string &k) { return k.size() >= 7 && k.compare(k.size() - 7, 7, "/launch") == 0; }
 
 void write_cache(const std::string &path, const std::map<std::string, int> &m) {
   if (path.empty()) return;
@@ -257,8 +260,10 @@ void write_cache(const std::string &path, const std::map<std::string, int> &m) {
   size_t n = 0;
   for (const auto &kv : m) {
     ++n;
-    fprintf(f, "  \"%s\": {\"%s\": %d}%s\n", kv.first.c_str(), is_launch_key(kv.first) ? "wpc" : "piece_rows",
-            kv.second, n < m.size() ? "," : "");
+    const bool launch = is_launch_key(kv.first);
+    fprintf(f, "  \"%s\": {\"%s\": %d", kv.first.c_str(), launch ? "wpc" : "piece_rows", kv.second);
+    if (launch && is_fd_key(kv.first)) fprintf(f, ", \"waves\": %d", kRaggedWaves);
+    fprintf(f, "}%s\n", n < m.size() ? "," : "");
   }
   fprintf(f, "}\n");
   fclose(f);

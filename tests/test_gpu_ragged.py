@@ -255,3 +255,20 @@ def test_ragged_extreme_shapes(fd, rows, tmp_path):
     assert ez <= 1e-4 and es <= TOL_DB
     assert np.all((host(info) & ~(1 << 30)) == 0)
     plan.close()
+
+
+@pytest.mark.parametrize("entry,kept", [('{"wpc": 3}', False), ('{"wpc": 3, "waves": 1}', False), ('{"wpc": 3, "waves": 2}', True)])
+def test_ragged_fd_launch_tuned_for_other_workgroups(rb, entry, kept, tmp_path):
+    """An FD launch entry that names no waves, or others than the workgroups
+    have, was timed with another launch: it is tuned again."""
+    from paper_1808_04473_amd import api
+    cache = tmp_path / "t.json"
+    cache.write_text('{\n  "gfx950/fd/p0/launch": ' + entry + '\n}\n')
+    plan = api.Plan.from_ragged(rb, fd=True, precision="fp32", tune_cache=cache)
+    plan.execute(dev(rb.H_pool), dev(rb.y_pool))
+    torch.cuda.synchronize()
+    c = json.load(open(cache))["gfx950/fd/p0/launch"]
+    assert c["waves"] == 2 and (c["wpc"] == 3) == kept
+    assert plan.describe()["grid"] == min(torch.cuda.get_device_properties(0).multi_processor_count * c["wpc"],
+                                          plan.describe()["tasks"])
+    plan.close()
