@@ -8,12 +8,15 @@ result needs far more before any VALU reads it.  The compiler inserts these
 for the DPP instructions it generates.  The fused row-broadcast FMACs of the
 factorisation are inline assembly, so the compiler does not see their DPP
 operand; this module verifies on the assembly of each build that none of
-them reads a register written too recently.
+them reads a register written too recently.  Nor does the compiler count a
+write inside inline assembly as one before its own DPP and permlane-swap
+instructions: their sources must be two wait states away from such a write.
 
 Wait states are counted as the ISA does: one per instruction issued in
 between, N + 1 for ``s_nop N``.  The walk back stops at a basic-block label,
 where the requirement must already be met (a label can have predecessors
-other than the fall-through).
+other than the fall-through); for a read outside inline assembly it goes on
+through the fall-through and every branch to the label.
 
     python -m paper_1808_04473_amd.isa_check <file.s> ...
 """
@@ -72,10 +75,69 @@ def _valu_writes(op: str, ops: list[str]) -> tuple[set[tuple[str, int]], bool]:
     return _regs(ops[0]), False
 
 
+def _is_label(line: str) -> bool:
+    return bool(re.match(r"^[.\w]+:", line))
+
+
+def _cross_lane_sources(op: str, ops: list[str]) -> set[tuple[str, int]]:
+    """Registers that a DPP or permlane-swap instruction reads across lanes."""
+    if "_dpp" in op and len(ops) >= 2:
+        return _regs(ops[1])
+    if op.startswith("v_permlane") and "swap" in op and len(ops) >= 2:
+        return _regs(ops[0]) | _regs(ops[1])
+    return set()
+
+
+def _check_outside(lines: list[str]) -> list[str]:
+    """Cross-lane reads outside inline assembly of registers that a vector
+    instruction inside it wrote less than two wait states before."""
+    errors = []
+    inside, jumps, in_asm = [], {}, False
+    for n, raw in enumerate(lines):
+        s = raw.strip()
+        if s.startswith(";;#ASMSTART"):
+            in_asm = True
+        elif s.startswith(";;#ASMEND"):
+            in_asm = False
+        inside.append(in_asm)
+        op, ops = _split(raw)
+        if op.startswith(("s_branch", "s_cbranch")) and ops:
+            jumps.setdefault(ops[0], []).append(n)
+
+    def writer(k, src, waited):
+        while k >= 0 and waited < DPP_SRC_WAIT:
+            s = lines[k].strip()
+            if _is_label(s):
+                for j in jumps.get(s.split(":")[0], []):
+                    w = writer(j, src, waited)
+                    if w is not None:
+                        return w
+            else:
+                op, ops = _split(lines[k])
+                if op and not op.startswith("."):
+                    if op in ("s_endpgm", "s_setpc_b64"):
+                        return None
+                    if inside[k] and _valu_writes(op, ops)[0] & src:
+                        return k
+                    waited += _wait_states(op, ops)
+            k -= 1
+        return None
+
+    for n, raw in enumerate(lines):
+        if inside[n]:
+            continue
+        src = _cross_lane_sources(*_split(raw))
+        k = writer(n - 1, src, 0) if src else None
+        if k is not None:
+            errors.append(f"line {n + 1}: {raw.strip()!r} reads across lanes what inline assembly wrote at line {k + 1}")
+    return errors
+
+
 def check_lines(lines: list[str]) -> list[str]:
     """Returns one message per hazard found in the inline-assembly DPP
-    instructions of the given assembly listing."""
-    errors = []
+    instructions of the given assembly listing, and in the cross-lane reads of
+    what inline assembly wrote."""
+    errors = _check_outside(lines)
     in_asm = False
     for n, raw in enumerate(lines):
         s = raw.strip()
@@ -98,7 +160,7 @@ def check_lines(lines: list[str]) -> list[str]:
         k = n - 1
         while k >= 0 and waited < MFMA_READ_WAIT:
             prev = lines[k].strip()
-            if re.match(r"^[.\w]+:", prev) and not prev.startswith(";"):
+            if _is_label(prev):
                 if waited < DPP_EXEC_WAIT:
                     errors.append(f"line {n + 1}: {s!r} follows block label {prev!r} "
                                   f"after only {waited} wait states")

@@ -97,3 +97,26 @@ def test_lama_fd_waves_per_simd():
         found += 1
         assert 168 < int(m.group(2)) <= 256, m.group(1)  # 512 per SIMD, in units of 8
     assert found
+
+
+WRITE = "\tv_fmac_f32_e32 v1, v3, v4"
+
+
+@pytest.mark.parametrize("read", ["\tv_mov_b32_dpp v7, v1 row_newbcast:3 row_mask:0xf bank_mask:0xf",
+                                  "\tv_permlane16_swap_b32 v1, v6", "\tv_permlane32_swap_b32 v6, v1"])
+def test_cross_lane_read_of_an_inline_assembly_write(read):
+    for sep in ([], ["\ts_nop 0"], ["\tv_add_f32_e32 v8, v9, v9"]):
+        errs = isa_check.check_lines(asm(*inline(WRITE), *sep, read))
+        assert len(errs) == 1 and "across lanes" in errs[0], sep
+    for sep in (["\ts_nop 1"], ["\tv_add_f32_e32 v8, v9, v9", "\ts_mov_b64 exec, s[2:3]"]):
+        assert isa_check.check_lines(asm(*inline(WRITE), *sep, read)) == [], sep
+    assert isa_check.check_lines(asm(*inline(WRITE.replace("v1,", "v2,")), read)) == []
+
+
+def test_cross_lane_read_after_a_branch():
+    read = "\tv_mov_b32_dpp v7, v1 row_newbcast:3 row_mask:0xf bank_mask:0xf"
+    loop = asm("\ts_nop 4", ".LBB0_1:", read, "\ts_nop 4", *inline(WRITE), "\ts_cbranch_scc1 .LBB0_1")
+    assert len(isa_check.check_lines(loop)) == 1
+    loop.insert(-1, "\ts_nop 0")
+    assert isa_check.check_lines(loop) == []
+    assert len(isa_check.check_lines(asm(*inline(WRITE), ".LBB0_1:", read))) == 1
