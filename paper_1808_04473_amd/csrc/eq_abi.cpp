@@ -225,7 +225,9 @@ eq_status forward_lama(const eq_problem *p, bool fd, int32_t t_max, int32_t qam_
 }
 
 // LAMA over several receive vectors: Y [W][nsym][B], Z and sigma2
-// [W][nsym][U]; passes of up to symbol_tile(U, fd) vectors, each reading H once.
+// [W][nsym][U]; passes of up to symbol_tile(U, fd) vectors, each reading H once,
+// or once per vector where the batch leaves SIMDs free for a wave each
+// (lama_by_vector).
 eq_status forward_lama_sym(const eq_problem *p, bool fd, int32_t nsym, int32_t t_max, int32_t qam_order,
                            const eq_c32 *H, const eq_c32 *Y, const float *nu, eq_c32 *Z, float *s2, int32_t *info,
                            void *stream) {

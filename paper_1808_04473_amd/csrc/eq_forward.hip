@@ -6,9 +6,11 @@
 // statistics are summed on chip and never leave the wave.
 //
 // FD (Section II-D, Section IV): a wave equalises all clusters of `spw`
-// subcarriers, NSYS local systems per round; after each round the local
-// estimates and variances go through LDS to the lanes that hold the fusion
-// sums of eq. (fusionrule) with the weights of Lemma 1 (eq. (opt_fusion)).
+// subcarriers, or up to four waves share those of one, NSYS local systems per
+// round; after each round the lane groups' estimates and variances are summed
+// across the wave in registers, with the weights of Lemma 1 (eq. (opt_fusion)),
+// into the fusion sums of eq. (fusionrule), which the waves of a subcarrier
+// exchange once, through LDS.
 //
 // The precision forms differ only in the Gram product (FP32 MFMA, BF16 MFMA,
 // or three BF16 MFMA products of split operands) and, for the BF16 forms, one
@@ -41,11 +43,11 @@ constexpr int pd_per() {
   return UT == 32 ? EQ_PD_PER32 : (refines(PREC) ? 2 : 64 / UT);
 }
 
-// Occupancy target.  UT = 16: 4 waves per SIMD (128 VGPRs) for the
-// one-pass forms; 3 (168 VGPRs) for the refining forms, which hold a factor
-// across the residual pass, and for FD with the split-BF16 Gram, whose
-// operand splits spill at 128.  UT = 32: 2 (256 VGPRs); the factor and the
-// inverse columns alone take 129.
+// Occupancy target, waves per SIMD.  UT = 16: 4 (128 VGPRs; FD takes 108, and
+// 124 with the split-BF16 Gram, without spills), 3 (168) for the refining forms,
+// which hold the solution across the residual pass.  UT = 32: 4 for PD, 3 for FD
+// (156; 168 with the split-BF16 Gram, which spills 76 bytes), 2 for the refining
+// forms.
 template <int UT, int PREC, bool FD>
 constexpr int waves_target() {
   if (UT == 32) return refines(PREC) ? 2 : (FD ? 3 : 4);

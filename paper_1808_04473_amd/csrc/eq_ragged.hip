@@ -55,7 +55,7 @@ __device__ __forceinline__ SysDesc &sys_desc(const RaggedArgs &a, int k) {
 }
 
 // Solve and outputs of a PD round whose n systems (sysk(s), s < n) have their
-// G + rho I and matched filters in sm.A / sm.M; seg re-streams them for the
+// G and matched filters in sm.A / sm.M (the elimination adds rho to the pivots); seg re-streams them for the
 // refinement step.
 template <int UT, int PREC, class SysK, class Seg>
 __device__ __forceinline__ void pd_solve_round(const RaggedArgs &a, SolveSmem<UT, refines(PREC)> &sm, int n, int U, SysK sysk,

@@ -31,8 +31,8 @@ __device__ __forceinline__ int slot_of(int g) {
 // LDS of one wave of the local solves: NSLOT packed matrix slots (one per
 // system of a round by default; fewer when the work items hold fewer systems
 // than there are lane groups) and, per system, every lane's share of the
-// matched filter: 10 KB at 16 users, so 16 waves per CU, and 13 KB (12 waves)
-// at 32.  R: right-hand sides of the refinement step.
+// matched filter: 10 KB at 16 users, so 16 waves per CU, and 13.3 KB at 32 (11
+// one-wave workgroups, 6 of two waves: LDS is given in units of 1,280 bytes).  R: right-hand sides of the refinement step.
 template <int UT, int NS>
 struct RefineRhs {
   float2 R[NS][UT];
