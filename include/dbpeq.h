@@ -116,7 +116,8 @@ typedef enum { EQ_LMMSE = 0, EQ_ZF = 1, EQ_MRC = 2, EQ_LMMSE_UNBIASED = 3 } eq_e
 
 /* Shared description of a batch of W systems. */
 typedef struct {
-  int32_t W;                  /* systems in the batch, >= 0 (0 = no-op)          */
+  int32_t W;                  /* systems in the batch, >= 0 (0 = no-op); FD fewer
+                                 than 2^26 (a launch's limit, EQ_EHIP)          */
   int32_t B;                  /* BS antennas, 1..EQ_MAX_B                        */
   int32_t U;                  /* single-antenna users, 1..EQ_MAX_U               */
   int32_t C;                  /* clusters, 1..min(B, EQ_MAX_C)                   */
